@@ -667,6 +667,8 @@ int dg_solver_create(const dg_mesh* m, const dg_physics* p, dg_solver** out) try
     v.lo[k] = m->lo[k];
     v.h[k] = (m->hi[k] - m->lo[k]) / (k == 0 ? m->ex : (k == 1 ? m->ey : m->ez));
   }
+  for (int k = 0; k < 3; k++) v.cja[k] = 0.25 * v.h[(k + 1) % 3] * v.h[(k + 2) % 3];
+  v.cij = 8.0 / (v.h[0] * v.h[1] * v.h[2]);
   v.gamma = p->gamma;
   v.Ma = p->Ma;
   v.viscous = p->Re > 0 ? 1 : 0;
@@ -774,6 +776,8 @@ int dg_solver_bind(dg_solver* s, void* dev_ptr, size_t bytes, void* hip_stream) 
     }
   } else {
     fill(v.N, tab.data());
+    v.iw0 = 1.0 / tab[dg::tab_w(v.N + 1)];
+    v.iwN = 1.0 / tab[dg::tab_w(v.N + 1) + v.N];
   }
   std::vector<int> nbr(6 * s->E);
   const int ex = v.ex, ey = v.ey, ez = v.ez;
@@ -1323,6 +1327,7 @@ struct dg_batch {
     bool fp32, visc;
     int fx;   // flux family
     bool xv;  // BR2 or interior-penalty face viscous flux
+    bool deform;  // some member lies on a deformed box (the kernels of plain boxes read no metric)
     std::vector<int> idx;
   };
   struct Graph {
@@ -1370,14 +1375,14 @@ hipError_t batch_stage(dg_batch* b, const double* dts, int k, hipStream_t st) {
       B.view[j] = s->dev_view;
       B.cur[j] = s->cur;
       B.dt[j] = dts[g.idx[j]];
-      B.start[j + 1] = B.start[j] + (int)s->E;
+      B.start[j + 1] = B.start[j] + dg::wg_count(g.N, (int)s->E);
     }
     hipError_t e;
     if (g.visc) {
-      e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, st);
+      e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.deform, st);
       if (e != hipSuccess) return e;
     }
-    e = dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
+    e = dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.deform, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
                                dg::kModeRK, st);
     if (e != hipSuccess) return e;
   }
@@ -1474,15 +1479,16 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
     }
     const bool fp32 = s->v.fp32 != 0, visc = s->v.viscous != 0;
     const int fx = dg::flux_family(s->v.vol, s->v.surf);
-    const bool xv = s->v.viscous && s->v.visc_flux != 0;
+    const bool xv = s->v.viscous && s->v.visc_flux != 0, deform = s->v.deform != 0;
     dg_batch::Group* g = nullptr;
     for (auto& x : b->groups)
       if (x.N == s->v.N && x.fp32 == fp32 && x.visc == visc && x.fx == fx && x.xv == xv && (int)x.idx.size() < dg::kMaxBatch)
         g = &x;
     if (!g) {
-      b->groups.push_back({s->v.N, fp32, visc, fx, xv, {}});
+      b->groups.push_back({s->v.N, fp32, visc, fx, xv, false, {}});
       g = &b->groups.back();
     }
+    g->deform = g->deform || deform;
     g->idx.push_back(i);
   }
   long long blocks = 0;

@@ -23,22 +23,20 @@ __host__ __device__ constexpr int pow2_at_least(int x) {
 }
 
 // Workgroup -> element.  Consecutive workgroups go round-robin over the 8 XCDs; give each XCD
-// a contiguous slice of elements instead.
+// a contiguous slice of elements instead (the first E mod 8 slices one element longer).
 __device__ __forceinline__ int block_element(int E) {
   const int b = blockIdx.x;
-  if ((E & 7) == 0) {
-    const int per = E >> 3;
-    return (b & 7) * per + (b >> 3);
-  }
-  return b;
+  const int x = b & 7, rem = E & 7;
+  return x * (E >> 3) + (x < rem ? x : rem) + (b >> 3);
 }
 
-// Workgroup -> (member, element) of a batched launch, XCD-aware over the whole grid.
-__device__ __forceinline__ void batch_member(const BatchArgs& B, int& m, int& e) {
+// Workgroup -> (member, workgroup of the member) of a batched launch, XCD-aware over the whole
+// grid.
+__device__ __forceinline__ void batch_member(const BatchArgs& B, int& m, int& w) {
   const int b = block_element(B.start[B.n]);
   m = 0;
   while (m + 1 < B.n && b >= B.start[m + 1]) m++;
-  e = b - B.start[m];
+  w = b - B.start[m];
 }
 
 // node index of reference indices (i_d = id, tangential p, r) on a face normal to d
@@ -81,8 +79,13 @@ __device__ __forceinline__ double wave_speed(const double u[5], double g, double
 
 template <typename T>
 struct Prim {
-  T rho, v1, v2, v3, beta, lrho, lbeta, h;  // beta = rho/(2p), h = |v|^2/2
+  T rho, v1, v2, v3, beta;  // beta = rho/(2p)
 };
+
+template <typename T>
+__device__ __forceinline__ T half_v2(const Prim<T>& a) {
+  return (T)0.5 * (a.v1 * a.v1 + a.v2 * a.v2 + a.v3 * a.v3);
+}
 
 // primitive variables computed in FP64 from the conservative state, then rounded to T
 template <typename T>
@@ -98,110 +101,145 @@ __device__ __forceinline__ Prim<T> make_prim(const double u[5], double gamma) {
   o.v2 = (T)v2;
   o.v3 = (T)v3;
   o.beta = (T)beta;
-  o.lrho = (T)log(u[0]);
-  o.lbeta = (T)log(beta);
-  o.h = (T)h;
   return o;
+}
+
+// ------------------------------------------------------------------ logarithmic means
+// (x_a - x_b)/(ln x_a - ln x_b) = (x_a + x_b)/(2 S(u)) with f = (x_a - x_b)/(x_a + x_b), u = f^2
+// and S(u) = atanh(f)/f = 1 + u/3 + u^2/5 + ...: no logarithm is needed while the series is
+// short.  Three tiers by u: below 1e-4 (neighbouring nodes of a resolved flow) four terms; below
+// 0.04 (ratios up to 1.5) twelve terms, truncated below 1e-18; beyond, the argument is halved until
+// they suffice (a library logarithm there would cost every kernel its registers: 126 -> 154 in
+// the mixed-order stage kernel).  A wave takes the later tiers only if one of its lanes needs them, and each lane's tier depends on its own
+// operands alone.  Without the two logarithms per node of the (ln x_a - ln x_b) form, the nodes
+// keep five primitive variables instead of seven.
+constexpr double kSmallU = 1e-4;
+__device__ __forceinline__ double atanh_ratio(double xa, double xb, double u) {
+  double k = 1.0;
+  if (u >= 0.04) {
+    // tanh(x/2) = tanh x / (1 + c), c = sqrt(1 - u): S(u) = 2 g S(g^2 u), g = 1/(1 + c); at first
+    // 1 - u = 4 x_a x_b / (x_a + x_b)^2, without cancellation.  Eight halvings reach ratios of 1e22.
+    const double s = xa + xb;
+    double w = 4.0 * xa * xb * rcp(s * s);
+#pragma unroll 1
+    for (int i = 0; i < 8 && u >= 0.04; i++) {
+      const double g = rcp(1.0 + w * rsq(w));
+      k *= 2.0 * g;
+      u *= g * g;
+      w = 1.0 - u;
+    }
+  }
+  double s = 1.0 / 23.0;
+#pragma unroll
+  for (int i = 21; i >= 1; i -= 2) s = fma(u, s, 1.0 / (double)i);
+  return k * s;
+}
+
+// 1/S(u) and S(u) for u < 1e-4 (truncated at 3e-18, 1e-17)
+__device__ __forceinline__ double inv_atanh_ratio_small(double u) {
+  return 1.0 - u * (1.0 / 3.0 + u * (4.0 / 45.0 + u * (44.0 / 945.0)));
+}
+__device__ __forceinline__ double atanh_ratio_small(double u) {
+  return 1.0 + u * (1.0 / 3.0 + u * (0.2 + u * (1.0 / 7.0)));
+}
+
+// logarithmic mean of xa and xb
+__device__ __forceinline__ double logmean(double xa, double xb) {
+  const double s = xa + xb, d = xa - xb;
+  const double f = d * rcp(s), u = f * f;
+  double r = 0.5 * s * inv_atanh_ratio_small(u);
+  if (__any(u >= kSmallU) && u >= kSmallU) r = 0.5 * s * rcp(atanh_ratio(xa, xb, u));
+  return r;
+}
+
+// a.b and a + s n for a face or pair normal n; AX: n = (1, 0, 0) (plain boxes, whose fluxes are
+// formed in a frame rotated to the face's direction)
+template <bool AX, typename T>
+__device__ __forceinline__ T dotn(T a1, T a2, T a3, T n1, T n2, T n3) {
+  return AX ? a1 : a1 * n1 + a2 * n2 + a3 * n3;
+}
+template <bool AX, typename T>
+__device__ __forceinline__ T addn(T a, T s, T nk, bool first) {
+  return AX ? (first ? a + s : a) : a + s * nk;
 }
 
 // Chandrashekar's entropy-conserving, kinetic-energy-preserving two-point flux along the
 // (not normalised) vector n: F#(a, b; n), linear in n and symmetric in (a, b).  ce =
-// 1/(2(gamma-1)).  Logarithmic means (x_a - x_b)/(ln x_a - ln x_b) of rho and beta: near
-// x_a = x_b the cancelling logarithms are replaced by the series in
-// u = ((x_a - x_b)/(x_a + x_b))^2, (x_a + x_b)/(2(1 + u/3 + u^2/5 + u^3/7)).  The five
-// quotients of the flux share two reciprocals.
-template <typename T>
-__device__ __forceinline__ void flux_ec(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3, T ce,
-                                        T F[5]) {
-  const T thr = sizeof(T) == 8 ? (T)1e-4 : (T)1e-2;
-  const T dr = a.rho - b.rho, sr = a.rho + b.rho;
-  const T db = a.beta - b.beta, sb = a.beta + b.beta;
-  const T r1 = rcp(sr * sb);
-  const T isb = r1 * sr;                    // 1/(beta_a + beta_b)
-  const T fr = dr * (r1 * sb), fb = db * isb;
-  const T ur = fr * fr, ub = fb * fb;
-  const bool smr = ur < thr, smb = ub < thr;
-  const T numr = smr ? sr : dr;
-  const T denr = smr ? (T)2 * ((T)1 + ur * ((T)(1.0 / 3.0) + ur * ((T)0.2 + ur * (T)(1.0 / 7.0))))
-                     : (a.lrho - b.lrho);
-  const T numb = smb ? sb : db;
-  const T denb = smb ? (T)2 * ((T)1 + ub * ((T)(1.0 / 3.0) + ub * ((T)0.2 + ub * (T)(1.0 / 7.0))))
-                     : (a.lbeta - b.lbeta);
-  const T r2 = rcp(denr * numb);
-  const T rho_ln = numr * numb * r2;        // logmean(rho)
-  const T inv_bln = denb * denr * r2;       // 1 / logmean(beta)
-  const T phat = (T)0.5 * sr * isb;         // {rho} / (2 {beta})
-  const T u = (T)0.5 * (a.v1 + b.v1), v = (T)0.5 * (a.v2 + b.v2), w = (T)0.5 * (a.v3 + b.v3);
-  const T hb = (T)0.5 * (a.h + b.h);
-  const T vn = u * n1 + v * n2 + w * n3;
+// 1/(2(gamma-1)).  The quotients share one reciprocal, and with {.} the arithmetic mean the
+// kinetic part of the energy flux is |{v}|^2 - {|v|^2}/2 = v_a.v_b / 2.
+template <bool AX = false>
+__device__ __forceinline__ void flux_ec(const Prim<double>& a, const Prim<double>& b, double n1, double n2, double n3,
+                                        double ce, double F[5]) {
+  const double dr = a.rho - b.rho, sr = a.rho + b.rho;
+  const double db = a.beta - b.beta, sb = a.beta + b.beta;
+  const double r1 = rcp(sr * sb);
+  const double isb = r1 * sr;  // 1/(beta_a + beta_b)
+  const double fr = dr * (r1 * sb), fb = db * isb;
+  const double ur = fr * fr, ub = fb * fb;
+  double rho_ln = 0.5 * sr * inv_atanh_ratio_small(ur);  // logmean(rho)
+  double hbln = isb * atanh_ratio_small(ub);             // 1/(2 logmean(beta))
+  if (__any(ur >= kSmallU || ub >= kSmallU)) {
+    if (ur >= kSmallU) rho_ln = 0.5 * sr * rcp(atanh_ratio(a.rho, b.rho, ur));
+    if (ub >= kSmallU) hbln = isb * atanh_ratio(a.beta, b.beta, ub);
+  }
+  const double phat = 0.5 * sr * isb;  // {rho} / (2 {beta})
+  const double u = 0.5 * (a.v1 + b.v1), v = 0.5 * (a.v2 + b.v2), w = 0.5 * (a.v3 + b.v3);
+  const double vv = a.v1 * b.v1 + a.v2 * b.v2 + a.v3 * b.v3;
+  const double vn = dotn<AX>(u, v, w, n1, n2, n3);
   F[0] = rho_ln * vn;
-  F[1] = F[0] * u + phat * n1;
-  F[2] = F[0] * v + phat * n2;
-  F[3] = F[0] * w + phat * n3;
-  F[4] = F[0] * (ce * inv_bln - hb) + u * F[1] + v * F[2] + w * F[3];
+  F[1] = addn<AX>(F[0] * u, phat, n1, true);
+  F[2] = addn<AX>(F[0] * v, phat, n2, false);
+  F[3] = addn<AX>(F[0] * w, phat, n3, false);
+  F[4] = F[0] * (2.0 * ce * hbln + 0.5 * vv) + phat * vn;
 }
 
 // central two-point flux (F(a) + F(b)) / 2 . n from the primitive variables
-template <typename T>
-__device__ __forceinline__ void flux_central(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3,
-                                             T gm1, T F[5]) {
+template <bool AX = false, typename T>
+__device__ __forceinline__ void flux_central(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3, T igm1, T F[5]) {
   T Fa[5], Fb[5];
   const Prim<T>* s[2] = {&a, &b};
   T* o[2] = {Fa, Fb};
 #pragma unroll
   for (int q = 0; q < 2; q++) {
     const Prim<T>& P = *s[q];
-    const T p = (T)0.5 * P.rho / P.beta;
-    const T vn = P.v1 * n1 + P.v2 * n2 + P.v3 * n3;
-    const T En = p / gm1 + P.rho * P.h;
+    const T p = (T)0.5 * P.rho * rcp(P.beta);
+    const T vn = dotn<AX>(P.v1, P.v2, P.v3, n1, n2, n3);
+    const T En = p * igm1 + P.rho * half_v2(P);
     o[q][0] = P.rho * vn;
-    o[q][1] = P.rho * P.v1 * vn + p * n1;
-    o[q][2] = P.rho * P.v2 * vn + p * n2;
-    o[q][3] = P.rho * P.v3 * vn + p * n3;
+    o[q][1] = addn<AX>(P.rho * P.v1 * vn, p, n1, true);
+    o[q][2] = addn<AX>(P.rho * P.v2 * vn, p, n2, false);
+    o[q][3] = addn<AX>(P.rho * P.v3 * vn, p, n3, false);
     o[q][4] = (En + p) * vn;
   }
 #pragma unroll
   for (int c = 0; c < 5; c++) F[c] = (T)0.5 * (Fa[c] + Fb[c]);
 }
 
-// logarithmic mean of x_a, x_b from their logarithms la, lb (series near x_a = x_b, as above)
-template <typename T>
-__device__ __forceinline__ T logmean_logs(T xa, T xb, T la, T lb) {
-  const T s = xa + xb, d = xa - xb;
-  const T f = d * rcp(s), u = f * f;
-  const T thr = sizeof(T) == 8 ? (T)1e-4 : (T)1e-2;
-  if (u < thr) return s * rcp((T)2 * ((T)1 + u * ((T)(1.0 / 3.0) + u * ((T)0.2 + u * (T)(1.0 / 7.0)))));
-  return d * rcp(la - lb);
-}
-
 // Ismail and Roe's entropy-conserving two-point flux along n, from the parameter vector
-// z = sqrt(rho/p) (1, v, p): z1 = sqrt(2 beta), z5 = rho / z1, so ln z1 = (ln 2 + ln beta)/2 and
-// ln z5 = ln rho - ln z1 come from the stored logarithms.
+// z = sqrt(rho/p) (1, v, p): z1 = sqrt(2 beta), z5 = rho / z1.
 //   rho^ = {z1} (z5)^ln, v^ = {z1 v}/{z1}, p1^ = {z5}/{z1},
 //   p2^ = (gamma+1)/(2 gamma) (z5)^ln/(z1)^ln + (gamma-1)/(2 gamma) p1^,
 //   H^ = gamma p2^/((gamma-1) rho^) + |v^|^2/2,  F = (rho^ v^.n, rho^ v^ v^.n + p1^ n, rho^ H^ v^.n)
-template <typename T>
-__device__ __forceinline__ void flux_ir(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3, T gm1, T F[5]) {
-  const T g = gm1 + (T)1;
-  const T z1a = sqrt((T)2 * a.beta), z1b = sqrt((T)2 * b.beta);
-  const T iz1a = rcp(z1a), iz1b = rcp(z1b);
-  const T z5a = a.rho * iz1a, z5b = b.rho * iz1b;
-  const T hl2 = (T)0.34657359027997264;  // ln(2) / 2
-  const T l1a = hl2 + (T)0.5 * a.lbeta, l1b = hl2 + (T)0.5 * b.lbeta;
-  const T z1ln = logmean_logs(z1a, z1b, l1a, l1b);
-  const T z5ln = logmean_logs(z5a, z5b, a.lrho - l1a, b.lrho - l1b);
-  const T is1 = rcp(z1a + z1b);
-  const T rho = (T)0.5 * (z1a + z1b) * z5ln;
-  const T u = (z1a * a.v1 + z1b * b.v1) * is1, v = (z1a * a.v2 + z1b * b.v2) * is1,
-          w = (z1a * a.v3 + z1b * b.v3) * is1;
-  const T p1 = (z5a + z5b) * is1;
-  const T p2 = (g + (T)1) / ((T)2 * g) * z5ln * rcp(z1ln) + gm1 / ((T)2 * g) * p1;
-  const T H = g * p2 * rcp(gm1 * rho) + (T)0.5 * (u * u + v * v + w * w);
-  const T vn = u * n1 + v * n2 + w * n3;
+template <bool AX = false>
+__device__ __forceinline__ void flux_ir(const Prim<double>& a, const Prim<double>& b, double n1, double n2, double n3,
+                                        double gm1, double F[5]) {
+  const double g = gm1 + 1.0, ig = rcp(g);
+  const double iz1a = rsq(2.0 * a.beta), iz1b = rsq(2.0 * b.beta);
+  const double z1a = 2.0 * a.beta * iz1a, z1b = 2.0 * b.beta * iz1b;
+  const double z5a = a.rho * iz1a, z5b = b.rho * iz1b;
+  const double z1ln = logmean(z1a, z1b), z5ln = logmean(z5a, z5b);
+  const double is1 = rcp(z1a + z1b);
+  const double rho = 0.5 * (z1a + z1b) * z5ln;
+  const double u = (z1a * a.v1 + z1b * b.v1) * is1, v = (z1a * a.v2 + z1b * b.v2) * is1,
+               w = (z1a * a.v3 + z1b * b.v3) * is1;
+  const double p1 = (z5a + z5b) * is1;
+  const double p2 = 0.5 * ig * ((g + 1.0) * z5ln * rcp(z1ln) + gm1 * p1);
+  const double H = g * p2 * rcp(gm1 * rho) + 0.5 * (u * u + v * v + w * w);
+  const double vn = dotn<AX>(u, v, w, n1, n2, n3);
   F[0] = rho * vn;
-  F[1] = F[0] * u + p1 * n1;
-  F[2] = F[0] * v + p1 * n2;
-  F[3] = F[0] * w + p1 * n3;
+  F[1] = addn<AX>(F[0] * u, p1, n1, true);
+  F[2] = addn<AX>(F[0] * v, p1, n2, false);
+  F[3] = addn<AX>(F[0] * w, p1, n3, false);
   F[4] = F[0] * H;
 }
 
@@ -211,49 +249,68 @@ __device__ __forceinline__ void flux_ir(const Prim<T>& a, const Prim<T>& b, T n1
 //   4 Pirozzoli       {rho}{vn},  {rho}{vn}{v} + {p}n,  {rho}{vn}{H}
 //   5 Ducros          {rho}{vn},  {rho v}{vn} + {p}n,   {rho H}{vn}
 //   6 Morinishi       m = {rho vn},  m{v} + {p}n,  gamma/(gamma-1){p vn} + m |{v}|^2 - {rho vn h}
-template <typename T>
+template <bool AX = false, typename T>
 __device__ __forceinline__ void flux_kep(int kind, const Prim<T>& a, const Prim<T>& b, T n1, T n2,
                                          T n3, T ce, T F[5]) {
   const T iba = rcp(a.beta), ibb = rcp(b.beta);
   const T pa = (T)0.5 * a.rho * iba, pb = (T)0.5 * b.rho * ibb;
-  const T vna = a.v1 * n1 + a.v2 * n2 + a.v3 * n3, vnb = b.v1 * n1 + b.v2 * n2 + b.v3 * n3;
+  const T vna = dotn<AX>(a.v1, a.v2, a.v3, n1, n2, n3), vnb = dotn<AX>(b.v1, b.v2, b.v3, n1, n2, n3);
   const T u = (T)0.5 * (a.v1 + b.v1), v = (T)0.5 * (a.v2 + b.v2), w = (T)0.5 * (a.v3 + b.v3);
   const T pm = (T)0.5 * (pa + pb), vn = (T)0.5 * (vna + vnb), rm = (T)0.5 * (a.rho + b.rho);
-  const T ea = ce * iba + a.h, eb = ce * ibb + b.h;
+  const T ha = half_v2(a), hb = half_v2(b);
+  const T ea = ce * iba + ha, eb = ce * ibb + hb;
   if (kind == 6) {
     const T m = (T)0.5 * (a.rho * vna + b.rho * vnb);
     F[0] = m;
-    F[1] = m * u + pm * n1;
-    F[2] = m * v + pm * n2;
-    F[3] = m * w + pm * n3;
+    F[1] = addn<AX>(m * u, pm, n1, true);
+    F[2] = addn<AX>(m * v, pm, n2, false);
+    F[3] = addn<AX>(m * w, pm, n3, false);
     F[4] = ((T)1 + (T)2 * ce) * (T)0.5 * (pa * vna + pb * vnb) + m * (u * u + v * v + w * w) -
-           (T)0.5 * (a.rho * vna * a.h + b.rho * vnb * b.h);
+           (T)0.5 * (a.rho * vna * ha + b.rho * vnb * hb);
     return;
   }
   F[0] = rm * vn;
   if (kind == 5) {
-    F[1] = (T)0.5 * (a.rho * a.v1 + b.rho * b.v1) * vn + pm * n1;
-    F[2] = (T)0.5 * (a.rho * a.v2 + b.rho * b.v2) * vn + pm * n2;
-    F[3] = (T)0.5 * (a.rho * a.v3 + b.rho * b.v3) * vn + pm * n3;
+    F[1] = addn<AX>((T)0.5 * (a.rho * a.v1 + b.rho * b.v1) * vn, pm, n1, true);
+    F[2] = addn<AX>((T)0.5 * (a.rho * a.v2 + b.rho * b.v2) * vn, pm, n2, false);
+    F[3] = addn<AX>((T)0.5 * (a.rho * a.v3 + b.rho * b.v3) * vn, pm, n3, false);
     F[4] = (T)0.5 * (a.rho * (ea + (T)0.5 * iba) + b.rho * (eb + (T)0.5 * ibb)) * vn;
     return;
   }
-  F[1] = F[0] * u + pm * n1;
-  F[2] = F[0] * v + pm * n2;
-  F[3] = F[0] * w + pm * n3;
+  F[1] = addn<AX>(F[0] * u, pm, n1, true);
+  F[2] = addn<AX>(F[0] * v, pm, n2, false);
+  F[3] = addn<AX>(F[0] * w, pm, n3, false);
   if (kind == 3) F[4] = F[0] * (T)0.5 * (ea + eb) + pm * vn;
   else F[4] = F[0] * (T)0.5 * (ea + eb + (T)0.5 * (iba + ibb));
 }
 
 // volume two-point flux: 0 Chandrashekar, 1 central, 2 Ismail-Roe; with KEP the
 // kinetic-energy-preserving forms 3..6 above instead
-template <typename T, bool KEP = false>
-__device__ __forceinline__ void vol_flux(int kind, const Prim<T>& a, const Prim<T>& b, T n1, T n2,
-                                         T n3, T ce, T gm1, T F[5]) {
-  if constexpr (KEP) flux_kep(kind, a, b, n1, n2, n3, ce, F);
-  else if (kind == 0) flux_ec(a, b, n1, n2, n3, ce, F);
-  else if (kind == 2) flux_ir(a, b, n1, n2, n3, gm1, F);
-  else flux_central(a, b, n1, n2, n3, gm1, F);
+template <bool KEP = false, bool AX = false>
+__device__ __forceinline__ void vol_flux(int kind, const Prim<double>& a, const Prim<double>& b, double n1, double n2,
+                                         double n3, double ce, double gm1, double F[5]) {
+  if constexpr (KEP) flux_kep<AX>(kind, a, b, n1, n2, n3, ce, F);
+  else if (kind == 0) flux_ec<AX>(a, b, n1, n2, n3, ce, F);
+  else if (kind == 2) flux_ir<AX>(a, b, n1, n2, n3, gm1, F);
+  else flux_central<AX>(a, b, n1, n2, n3, 2.0 * ce, F);
+}
+
+// area and unit normal of the scaled normal S (AX: S = (area, 0, 0))
+template <bool AX, typename T>
+__device__ __forceinline__ void face_normal(const double S[3], T& area, T& n1, T& n2, T& n3) {
+  if constexpr (AX) {
+    area = (T)S[0];
+    n1 = (T)1;
+    n2 = n3 = (T)0;
+  } else {
+    const T s1 = (T)S[0], s2 = (T)S[1], s3 = (T)S[2];
+    const T a2s = s1 * s1 + s2 * s2 + s3 * s3;
+    const T ia = rsq(a2s);
+    area = a2s * ia;
+    n1 = s1 * ia;
+    n2 = s2 * ia;
+    n3 = s3 * ia;
+  }
 }
 
 // Numerical flux through a face with scaled normal S (|S| times the unit normal), between
@@ -261,20 +318,22 @@ __device__ __forceinline__ void vol_flux(int kind, const Prim<T>& a, const Prim<
 // Lax-Friedrichs (1), Chandrashekar's EC flux (2), central (3).  LD turns Roe's flux into its
 // low-dissipation variant: the velocity jump in the wave strengths is scaled by
 // z = min(1, max(M_L, M_R)), the larger local Mach number.
-template <typename T, bool LD = false>
+// AX: S = (|S|, 0, 0).
+template <typename T, bool LD = false, bool AX = false>
 __device__ __forceinline__ void face_flux_std(int kind, const double uL[5], const double uR[5],
                                           const double S[3], double gamma, T F[5]) {
   const T gm1 = (T)(gamma - 1.0);
   if (kind == 2) {  // entropy-conserving flux, linear in S
     const Prim<T> a = make_prim<T>(uL, gamma), b = make_prim<T>(uR, gamma);
-    flux_ec(a, b, (T)S[0], (T)S[1], (T)S[2], (T)(0.5 / (gamma - 1.0)), F);
+    flux_ec<AX>(a, b, (T)S[0], (T)S[1], (T)S[2], (T)(0.5 / (gamma - 1.0)), F);
+    if constexpr (AX) {
+#pragma unroll
+      for (int c = 0; c < 5; c++) F[c] *= (T)S[0];
+    }
     return;
   }
-  const T s1 = (T)S[0], s2 = (T)S[1], s3 = (T)S[2];
-  const T a2s = s1 * s1 + s2 * s2 + s3 * s3;
-  const T ia = rsq(a2s);
-  const T area = a2s * ia;
-  const T n1 = s1 * ia, n2 = s2 * ia, n3 = s3 * ia;
+  T area, n1, n2, n3;
+  face_normal<AX>(S, area, n1, n2, n3);
   T rL, vL[3], pL, EL, rR, vR[3], pR, ER, irL, irR;
   {
     const double i = rcp(uL[0]);
@@ -290,14 +349,14 @@ __device__ __forceinline__ void face_flux_std(int kind, const double uL[5], cons
     rR = (T)uR[0]; vR[0] = (T)a1; vR[1] = (T)a2; vR[2] = (T)a3; pR = (T)p; ER = (T)uR[4];
     irR = (T)i;
   }
-  const T vnL = vL[0] * n1 + vL[1] * n2 + vL[2] * n3;
-  const T vnR = vR[0] * n1 + vR[1] * n2 + vR[2] * n3;
+  const T vnL = dotn<AX>(vL[0], vL[1], vL[2], n1, n2, n3);
+  const T vnR = dotn<AX>(vR[0], vR[1], vR[2], n1, n2, n3);
   const T HL = (EL + pL) * irL, HR = (ER + pR) * irR;
   T Fs[5];  // F(uL).n + F(uR).n
   Fs[0] = rL * vnL + rR * vnR;
-  Fs[1] = rL * vnL * vL[0] + rR * vnR * vR[0] + (pL + pR) * n1;
-  Fs[2] = rL * vnL * vL[1] + rR * vnR * vR[1] + (pL + pR) * n2;
-  Fs[3] = rL * vnL * vL[2] + rR * vnR * vR[2] + (pL + pR) * n3;
+  Fs[1] = addn<AX>(rL * vnL * vL[0] + rR * vnR * vR[0], pL + pR, n1, true);
+  Fs[2] = addn<AX>(rL * vnL * vL[1] + rR * vnR * vR[1], pL + pR, n2, false);
+  Fs[3] = addn<AX>(rL * vnL * vL[2] + rR * vnR * vR[2], pL + pR, n3, false);
   Fs[4] = rL * HL * vnL + rR * HR * vnR;
   if (kind == 3) {  // central
 #pragma unroll
@@ -331,7 +390,7 @@ __device__ __forceinline__ void face_flux_std(int kind, const double uL[5], cons
   const T rc = rsq(c2);
   const T c = c2 * rc;
   const T ic2 = rc * rc;
-  const T vn = u1 * n1 + u2 * n2 + u3 * n3;
+  const T vn = dotn<AX>(u1, u2, u3, n1, n2, n3);
   const T dr = rR - rL, dp = pR - pL;
   T dv1 = vR[0] - vL[0], dv2 = vR[1] - vL[1], dv3 = vR[2] - vL[2];
   if constexpr (LD) {
@@ -344,19 +403,26 @@ __device__ __forceinline__ void face_flux_std(int kind, const double uL[5], cons
     dv2 *= z;
     dv3 *= z;
   }
-  const T dvn = dv1 * n1 + dv2 * n2 + dv3 * n3;
+  const T dvn = dotn<AX>(dv1, dv2, dv3, n1, n2, n3);
   const T a1 = (T)0.5 * (dp - rho * c * dvn) * ic2;
   const T a2 = dr - dp * ic2;
   const T a3 = (T)0.5 * (dp + rho * c * dvn) * ic2;
   const T l1 = fabs(vn - c), l2 = fabs(vn), l3 = fabs(vn + c);
-  const T t1 = dv1 - dvn * n1, t2 = dv2 - dvn * n2, t3 = dv3 - dvn * n3;
-  const T udt = u1 * t1 + u2 * t2 + u3 * t3;
+  // the velocity jump's tangential part (AX: its first component is zero)
+  const T t1 = AX ? (T)0 : dv1 - dvn * n1, t2 = AX ? dv2 : dv2 - dvn * n2, t3 = AX ? dv3 : dv3 - dvn * n3;
+  const T udt = AX ? u2 * t2 + u3 * t3 : u1 * t1 + u2 * t2 + u3 * t3;
   const T w1 = l1 * a1, w3 = l3 * a3;
   T W[5];
   W[0] = w1 + l2 * a2 + w3;
-  W[1] = w1 * (u1 - c * n1) + l2 * (a2 * u1 + rho * t1) + w3 * (u1 + c * n1);
-  W[2] = w1 * (u2 - c * n2) + l2 * (a2 * u2 + rho * t2) + w3 * (u2 + c * n2);
-  W[3] = w1 * (u3 - c * n3) + l2 * (a2 * u3 + rho * t3) + w3 * (u3 + c * n3);
+  if constexpr (AX) {
+    W[1] = w1 * (u1 - c) + l2 * (a2 * u1) + w3 * (u1 + c);
+    W[2] = W[0] * u2 + l2 * (rho * t2);
+    W[3] = W[0] * u3 + l2 * (rho * t3);
+  } else {
+    W[1] = w1 * (u1 - c * n1) + l2 * (a2 * u1 + rho * t1) + w3 * (u1 + c * n1);
+    W[2] = w1 * (u2 - c * n2) + l2 * (a2 * u2 + rho * t2) + w3 * (u2 + c * n2);
+    W[3] = w1 * (u3 - c * n3) + l2 * (a2 * u3 + rho * t3) + w3 * (u3 + c * n3);
+  }
   W[4] = w1 * (H - vn * c) + l2 * (a2 * (T)0.5 * q2 + rho * udt) + w3 * (H + vn * c);
 #pragma unroll
   for (int k = 0; k < 5; k++) F[k] = (T)0.5 * area * (Fs[k] - W[k]);
@@ -366,14 +432,14 @@ __device__ __forceinline__ void face_flux_std(int kind, const double uL[5], cons
 // flux Jacobian, Barth's scaling T = diag(rho/(2 gamma), rho (gamma-1)/gamma, p, p, rho/(2 gamma))
 // (so that R T R^T = du/dw), all at the averaged state rho^ = (rho)^ln, v^ = {v},
 // p^ = {rho}/(2{beta}), c^2 = gamma p^/rho^, H^ = c^2/(gamma-1) + |v^|^2/2.  The jump of the
-// entropy variables w = ((gamma - s)/(gamma-1) - 2 beta h, 2 beta v, -2 beta) comes from the
-// stored logarithms: s = -(gamma-1) ln rho - ln 2 - ln beta.  The two shear waves are summed
+// entropy variables w = ((gamma - s)/(gamma-1) - beta |v|^2, 2 beta v, -2 beta) with
+// s = -(gamma-1) ln rho - ln 2 - ln beta.  The two shear waves are summed
 // with the tangential projector I - n n^T.
 template <typename T>
 __device__ __forceinline__ void matrix_dissipation(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3,
                                                    T gm1, T D[5]) {
   const T g = gm1 + (T)1;
-  const T rho = logmean_logs(a.rho, b.rho, a.lrho, b.lrho);
+  const T rho = logmean(a.rho, b.rho);
   const T p = (a.rho + b.rho) * rcp((T)2 * (a.beta + b.beta));
   const T u = (T)0.5 * (a.v1 + b.v1), v = (T)0.5 * (a.v2 + b.v2), w = (T)0.5 * (a.v3 + b.v3);
   const T q2 = u * u + v * v + w * w;
@@ -382,7 +448,8 @@ __device__ __forceinline__ void matrix_dissipation(const Prim<T>& a, const Prim<
   const T c = c2 * rsq(c2);
   const T H = c2 * igm1 + (T)0.5 * q2;
   const T vn = u * n1 + v * n2 + w * n3;
-  const T dw0 = (b.lrho - a.lrho) + (b.lbeta - a.lbeta) * igm1 - (T)2 * (b.beta * b.h - a.beta * a.h);
+  const T dw0 = (log(b.rho) - log(a.rho)) + (log(b.beta) - log(a.beta)) * igm1 -
+                (T)2 * (b.beta * half_v2(b) - a.beta * half_v2(a));
   const T dw1 = (T)2 * (b.beta * b.v1 - a.beta * a.v1);
   const T dw2 = (T)2 * (b.beta * b.v2 - a.beta * a.v2);
   const T dw3 = (T)2 * (b.beta * b.v3 - a.beta * a.v3);
@@ -408,64 +475,60 @@ __device__ __forceinline__ void matrix_dissipation(const Prim<T>& a, const Prim<
 // Lax-Friedrichs dissipation), Ismail-Roe (5), entropy stable with matrix dissipation (6:
 // Chandrashekar's flux minus the dissipation above), low-dissipation Roe (7), Lax-Friedrichs with
 // the global wave speed lam_g (8: the central flux minus lam_g |S| (U_R - U_L) / 2).
-template <typename T>
+template <bool AX = false>
 __device__ __forceinline__ void face_flux_xs(int kind, const double uL[5], const double uR[5],
-                                             const double S[3], double gamma, T F[5], double lam_g) {
+                                             const double S[3], double gamma, double F[5], double lam_g) {
+  double area, n1, n2, n3;
+  face_normal<AX>(S, area, n1, n2, n3);
   if (kind == 8) {
-    face_flux_std<T>(3, uL, uR, S, gamma, F);
-    const T s1 = (T)S[0], s2 = (T)S[1], s3 = (T)S[2];
-    const T a2s = s1 * s1 + s2 * s2 + s3 * s3;
-    const T area = a2s * rsq(a2s);
+    face_flux_std<double, false, AX>(3, uL, uR, S, gamma, F);
 #pragma unroll
-    for (int c = 0; c < 5; c++) F[c] -= (T)0.5 * area * (T)lam_g * (T)(uR[c] - uL[c]);
+    for (int c = 0; c < 5; c++) F[c] -= 0.5 * area * lam_g * (uR[c] - uL[c]);
     return;
   }
   if (kind == 7) {
-    face_flux_std<T, true>(0, uL, uR, S, gamma, F);
+    face_flux_std<double, true, AX>(0, uL, uR, S, gamma, F);
     return;
   }
-  const T gm1 = (T)(gamma - 1.0);
-  const Prim<T> a = make_prim<T>(uL, gamma), b = make_prim<T>(uR, gamma);
+  const double gm1 = gamma - 1.0;
+  const Prim<double> a = make_prim<double>(uL, gamma), b = make_prim<double>(uR, gamma);
+  // along S itself, or along the unit normal and scaled by the area
+  const double s1 = AX ? 1.0 : S[0], s2 = S[1], s3 = S[2];
   if (kind == 5) {
-    flux_ir(a, b, (T)S[0], (T)S[1], (T)S[2], gm1, F);
-    return;
+    flux_ir<AX>(a, b, s1, s2, s3, gm1, F);
+  } else {
+    flux_ec<AX>(a, b, s1, s2, s3, 0.5 / (gamma - 1.0), F);
   }
-  const T s1 = (T)S[0], s2 = (T)S[1], s3 = (T)S[2];
-  const T a2s = s1 * s1 + s2 * s2 + s3 * s3;
-  const T ia = rsq(a2s);
-  const T area = a2s * ia;
-  flux_ec(a, b, s1, s2, s3, (T)(0.5 / (gamma - 1.0)), F);
-  if (kind == 6) {
-    T D[5];
-    matrix_dissipation(a, b, s1 * ia, s2 * ia, s3 * ia, gm1, D);
+  if constexpr (AX) {
 #pragma unroll
-    for (int c = 0; c < 5; c++) F[c] -= (T)0.5 * area * D[c];
+    for (int c = 0; c < 5; c++) F[c] *= area;
+  }
+  if (kind == 5) return;
+  if (kind == 6) {
+    double D[5];
+    matrix_dissipation(a, b, n1, n2, n3, gm1, D);
+#pragma unroll
+    for (int c = 0; c < 5; c++) F[c] -= 0.5 * area * D[c];
     return;
   }
-  const T g = (T)gamma;
-  T lam = (T)0;
-  const double* u2[2] = {uL, uR};
+  double lam = 0.0;
+  const Prim<double>* P[2] = {&a, &b};
 #pragma unroll
   for (int q = 0; q < 2; q++) {
-    const double* u = u2[q];
-    const double i = rcp(u[0]);
-    const double a1 = u[1] * i, a2 = u[2] * i, a3 = u[3] * i;
-    const T p = (T)((gamma - 1.0) * (u[4] - 0.5 * u[0] * (a1 * a1 + a2 * a2 + a3 * a3)));
-    const T vn = ((T)a1 * s1 + (T)a2 * s2 + (T)a3 * s3) * ia;
-    const T c2 = g * p * (T)i;
-    const T l = fabs(vn) + c2 * rsq(c2);
+    const double c2 = 0.5 * gamma * rcp(P[q]->beta);  // gamma p / rho
+    const double l = fabs(dotn<AX>(P[q]->v1, P[q]->v2, P[q]->v3, n1, n2, n3)) + c2 * rsq(c2);
     lam = l > lam ? l : lam;
   }
 #pragma unroll
-  for (int c = 0; c < 5; c++) F[c] -= (T)0.5 * area * lam * (T)(uR[c] - uL[c]);
+  for (int c = 0; c < 5; c++) F[c] -= 0.5 * area * lam * (uR[c] - uL[c]);
 }
 
 // XS selects the family: the two are compiled apart so that the common one keeps its registers
-template <typename T, bool XS = false>
+template <bool XS = false, bool AX = false>
 __device__ __forceinline__ void face_flux(int kind, const double uL[5], const double uR[5],
-                                          const double S[3], double gamma, T F[5], double lam_g = 0.0) {
-  if constexpr (XS) face_flux_xs<T>(kind, uL, uR, S, gamma, F, lam_g);
-  else face_flux_std<T>(kind, uL, uR, S, gamma, F);
+                                          const double S[3], double gamma, double F[5], double lam_g = 0.0) {
+  if constexpr (XS) face_flux_xs<AX>(kind, uL, uR, S, gamma, F, lam_g);
+  else face_flux_std<double, false, AX>(kind, uL, uR, S, gamma, F);
 }
 
 // ------------------------------------------------------------------ FP32-bulk: deviation form
@@ -476,9 +539,9 @@ __device__ __forceinline__ void face_flux(int kind, const double uL[5], const do
 //    terms has zero residual (discrete metric identities, SBP lift);
 //  - the energy flux is split as H_r F_rho + F'_E with H_r = gamma p_r/((gamma-1) rho_r); the
 //    residual is linear in the fluxes, so R_E = H_r R_rho + R'_E, recombined in FP64.
-// Per-node inputs are formed in FP64 and rounded: x = rho/rho_r - 1, y = beta/beta_r - 1,
-// lx = ln(rho/rho_r), ly = ln(beta/beta_r) (beta = rho/(2p)), so that every quantity entering
-// the FP32 arithmetic is either O(1) or a small deviation carried at full relative precision.
+// Per-node inputs are formed in FP64 and rounded: x = rho/rho_r - 1, y = beta/beta_r - 1
+// (beta = rho/(2p)), so that every quantity entering the FP32 arithmetic is either O(1) or a
+// small deviation carried at full relative precision.
 struct Ref {
   double rho, p;  // reference density and pressure
   double c;       // p/((gamma-1) rho)  = 1/(2 (gamma-1) beta_r)
@@ -496,7 +559,7 @@ __device__ __forceinline__ Ref make_ref(double rho_r, double p_r, double gamma) 
   return r;
 }
 
-// primitive deviations stored in the Prim fields: rho <- x, beta <- y, lrho <- lx, lbeta <- ly
+// primitive deviations stored in the Prim fields: rho <- x, beta <- y
 template <typename T>
 __device__ __forceinline__ Prim<T> make_prim_dev(const double u[5], double gamma, const Ref& R) {
   const double inv = rcp(u[0]);
@@ -508,57 +571,50 @@ __device__ __forceinline__ Prim<T> make_prim_dev(const double u[5], double gamma
   Prim<T> o;
   o.rho = (T)(rr - 1.0);
   o.beta = (T)(bb - 1.0);
-  o.lrho = (T)log(rr);
-  o.lbeta = (T)log(bb);
   o.v1 = (T)v1;
   o.v2 = (T)v2;
   o.v3 = (T)v3;
-  o.h = (T)h;
   return o;
 }
 
-// logarithmic mean of (1 + xa, 1 + xb) as 1 + lam, lam formed without cancellation
-// (la, lb = ln(1 + xa), ln(1 + xb))
-template <typename T>
-__device__ __forceinline__ T logmean_dev(T xa, T xb, T la, T lb) {
-  const T d = xa - xb, w = (T)2 + xa + xb;
-  const T u = d * d * rcp(w * w);
-  const T thr = sizeof(T) == 8 ? (T)1e-4 : (T)1e-2;
-  if (u < thr) {
-    const T pm1 = u * ((T)(1.0 / 3.0) + u * ((T)0.2 + u * (T)(1.0 / 7.0)));
-    return ((T)0.5 * (xa + xb) - pm1) * rcp((T)1 + pm1);
-  }
-  const T dl = la - lb;
-  return (d - dl) * rcp(dl);
+// logarithmic mean of (1 + xa, 1 + xb) as 1 + lam, lam formed without cancellation: with
+// u = ((xa - xb)/(2 + xa + xb))^2 and S(u) = 1 + s as above, lam = ((xa + xb)/2 - s)/(1 + s).
+// u < 1e-2 takes four terms (truncated at u^4/9 = 1e-9), beyond it S in FP64.
+__device__ __forceinline__ float logmean_dev(float xa, float xb) {
+  const float d = xa - xb, w = 2.0f + xa + xb;
+  const float u = d * d * rcp(w * w);
+  float pm1 = u * ((float)(1.0 / 3.0) + u * (0.2f + u * (float)(1.0 / 7.0)));
+  if (__any(u >= 1e-2f) && u >= 1e-2f) pm1 = (float)(atanh_ratio(1.0 + xa, 1.0 + xb, u) - 1.0);
+  return (0.5f * (xa + xb) - pm1) * rcp(1.0f + pm1);
 }
 
-// Chandrashekar's flux in deviation form: F[0] = F_rho, F[1..3] = F_m - p_r n,
-// F[4] = F_E - H_r F_rho
-// vn64 = {v}.n formed in FP64 (the mass flux is carried in FP64, see the stage kernel)
-template <typename T>
-__device__ __forceinline__ void flux_ec_dev(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3,
-                                            double vn64, const Ref& R, T F[5], double& F0d) {
-  const T lr = logmean_dev(a.rho, b.rho, a.lrho, b.lrho);   // rho_ln = rho_r (1 + lr)
-  const T lb = logmean_dev(a.beta, b.beta, a.lbeta, b.lbeta);  // beta_ln = beta_r (1 + lb)
+// Chandrashekar's flux in deviation form: F[1..3] = F_m - p_r n, F[4] = F_E - H_r F_rho, and
+// F0d = F_rho, the mass flux, carried in FP64 (vn64 = {v}.n formed in FP64, see the stage kernel)
+template <bool AX = false>
+__device__ __forceinline__ void flux_ec_dev(const Prim<float>& a, const Prim<float>& b, float n1, float n2, float n3,
+                                            double vn64, const Ref& R, float F[5], double& F0d) {
+  typedef float T;
+  const T lr = logmean_dev(a.rho, b.rho);    // rho_ln = rho_r (1 + lr)
+  const T lb = logmean_dev(a.beta, b.beta);  // beta_ln = beta_r (1 + lb)
   const T xb = (T)0.5 * (a.rho + b.rho), yb = (T)0.5 * (a.beta + b.beta);
   const T dphat = (T)R.p * (xb - yb) * rcp((T)1 + yb);       // {rho}/(2{beta}) - p_r
   const T u = (T)0.5 * (a.v1 + b.v1), v = (T)0.5 * (a.v2 + b.v2), w = (T)0.5 * (a.v3 + b.v3);
-  const T hb = (T)0.5 * (a.h + b.h);
-  const T vn = u * n1 + v * n2 + w * n3;
+  const T vn = dotn<AX>(u, v, w, n1, n2, n3);
   F0d = R.rho * (1.0 + (double)lr) * vn64;
   F[0] = (T)F0d;
-  F[1] = F[0] * u + dphat * n1;
-  F[2] = F[0] * v + dphat * n2;
-  F[3] = F[0] * w + dphat * n3;
-  const T kin = u * u + v * v + w * w - hb;
+  F[1] = addn<AX>(F[0] * u, dphat, n1, true);
+  F[2] = addn<AX>(F[0] * v, dphat, n2, false);
+  F[3] = addn<AX>(F[0] * w, dphat, n3, false);
+  const T kin = (T)0.5 * (a.v1 * b.v1 + a.v2 * b.v2 + a.v3 * b.v3);  // |{v}|^2 - {|v|^2}/2
   F[4] = F[0] * (kin - (T)R.c * lb * rcp((T)1 + lb) - (T)R.por * lr * rcp((T)1 + lr)) + dphat * vn;
 }
 
-// central two-point flux in deviation form
-template <typename T>
-__device__ __forceinline__ void flux_central_dev(const Prim<T>& a, const Prim<T>& b, T n1, T n2, T n3,
-                                                 const double va[3], const double vb[3], const double m[3],
-                                                 const Ref& R, T F[5], double& F0d) {
+// central two-point flux in deviation form (va, vb: the velocities in FP64)
+template <bool AX = false>
+__device__ __forceinline__ void flux_central_dev(const Prim<float>& a, const Prim<float>& b, float n1, float n2,
+                                                 float n3, const double va[3], const double vb[3], const double m[3],
+                                                 const Ref& R, float F[5], double& F0d) {
+  typedef float T;
   T Fa[5], Fb[5];
   const Prim<T>* s[2] = {&a, &b};
   T* o[2] = {Fa, Fb};
@@ -568,44 +624,49 @@ __device__ __forceinline__ void flux_central_dev(const Prim<T>& a, const Prim<T>
     const T iy = rcp((T)1 + P.beta);
     const T rho = (T)R.rho * ((T)1 + P.rho);
     const T dp = (T)R.p * (P.rho - P.beta) * iy;        // p - p_r
-    const T dH = -(T)R.H * P.beta * iy + P.h;           // H - H_r
-    const T vn = P.v1 * n1 + P.v2 * n2 + P.v3 * n3;
+    const T dH = -(T)R.H * P.beta * iy + half_v2(P);    // H - H_r
+    const T vn = dotn<AX>(P.v1, P.v2, P.v3, n1, n2, n3);
     o[q][0] = rho * vn;
-    o[q][1] = o[q][0] * P.v1 + dp * n1;
-    o[q][2] = o[q][0] * P.v2 + dp * n2;
-    o[q][3] = o[q][0] * P.v3 + dp * n3;
+    o[q][1] = addn<AX>(o[q][0] * P.v1, dp, n1, true);
+    o[q][2] = addn<AX>(o[q][0] * P.v2, dp, n2, false);
+    o[q][3] = addn<AX>(o[q][0] * P.v3, dp, n3, false);
     o[q][4] = o[q][0] * dH;
   }
 #pragma unroll
   for (int c = 0; c < 5; c++) F[c] = (T)0.5 * (Fa[c] + Fb[c]);
   const double ra = R.rho * (1.0 + (double)a.rho), rb = R.rho * (1.0 + (double)b.rho);
-  F0d = 0.5 * (ra * (va[0] * m[0] + va[1] * m[1] + va[2] * m[2]) +
-               rb * (vb[0] * m[0] + vb[1] * m[1] + vb[2] * m[2]));
+  F0d = 0.5 * (ra * dotn<AX>(va[0], va[1], va[2], m[0], m[1], m[2]) +
+               rb * dotn<AX>(vb[0], vb[1], vb[2], m[0], m[1], m[2]));
   F[0] = (T)F0d;
 }
 
 // face numerical flux in deviation form (same fluxes as face_flux, same component meaning as
 // flux_ec_dev)
-template <typename T>
+template <typename T, bool AX = false>
 __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], const double uR[5],
                                               const double S[3], double gamma, const Ref& R, T F[5],
                                               double& F0d) {
   // FP64 parts: the central mass flux (F(uL) + F(uR))_rho . S / 2
-  const double mS = 0.5 * ((uL[1] * rcp(uL[0]) + uR[1] * rcp(uR[0])) * S[0] +
-                           (uL[2] * rcp(uL[0]) + uR[2] * rcp(uR[0])) * S[1] +
-                           (uL[3] * rcp(uL[0]) + uR[3] * rcp(uR[0])) * S[2]);
   if (kind == 2) {
     const Prim<T> a = make_prim_dev<T>(uL, gamma, R), b = make_prim_dev<T>(uR, gamma, R);
-    flux_ec_dev(a, b, (T)S[0], (T)S[1], (T)S[2], mS, R, F, F0d);
+    const double iL = rcp(uL[0]), iR = rcp(uR[0]);
+    if constexpr (AX) {
+      flux_ec_dev<true>(a, b, (T)1, (T)0, (T)0, 0.5 * (uL[1] * iL + uR[1] * iR), R, F, F0d);
+#pragma unroll
+      for (int c = 0; c < 5; c++) F[c] *= (T)S[0];
+      F0d *= S[0];
+    } else {
+      const double mS = 0.5 * ((uL[1] * iL + uR[1] * iR) * S[0] + (uL[2] * iL + uR[2] * iR) * S[1] +
+                               (uL[3] * iL + uR[3] * iR) * S[2]);
+      flux_ec_dev(a, b, (T)S[0], (T)S[1], (T)S[2], mS, R, F, F0d);
+    }
     return;
   }
-  const double cm = 0.5 * ((uL[1] + uR[1]) * S[0] + (uL[2] + uR[2]) * S[1] + (uL[3] + uR[3]) * S[2]);
+  const double cm = AX ? 0.5 * ((uL[1] + uR[1]) * S[0])
+                       : 0.5 * ((uL[1] + uR[1]) * S[0] + (uL[2] + uR[2]) * S[1] + (uL[3] + uR[3]) * S[2]);
   const T gm1 = (T)(gamma - 1.0);
-  const T s1 = (T)S[0], s2 = (T)S[1], s3 = (T)S[2];
-  const T a2s = s1 * s1 + s2 * s2 + s3 * s3;
-  const T ia = rsq(a2s);
-  const T area = a2s * ia;
-  const T n1 = s1 * ia, n2 = s2 * ia, n3 = s3 * ia;
+  T area, n1, n2, n3;
+  face_normal<AX>(S, area, n1, n2, n3);
   T rL, vL[3], dpL, dHL, irL, rR, vR[3], dpR, dHR, irR;
   {
     const double i = rcp(uL[0]);
@@ -623,13 +684,13 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
     dpR = (T)(p - R.p);
     dHR = (T)((uR[4] + p) * i - R.H);
   }
-  const T vnL = vL[0] * n1 + vL[1] * n2 + vL[2] * n3;
-  const T vnR = vR[0] * n1 + vR[1] * n2 + vR[2] * n3;
+  const T vnL = dotn<AX>(vL[0], vL[1], vL[2], n1, n2, n3);
+  const T vnR = dotn<AX>(vR[0], vR[1], vR[2], n1, n2, n3);
   T Fs[5];
   Fs[0] = rL * vnL + rR * vnR;
-  Fs[1] = rL * vnL * vL[0] + rR * vnR * vR[0] + (dpL + dpR) * n1;
-  Fs[2] = rL * vnL * vL[1] + rR * vnR * vR[1] + (dpL + dpR) * n2;
-  Fs[3] = rL * vnL * vL[2] + rR * vnR * vR[2] + (dpL + dpR) * n3;
+  Fs[1] = addn<AX>(rL * vnL * vL[0] + rR * vnR * vR[0], dpL + dpR, n1, true);
+  Fs[2] = addn<AX>(rL * vnL * vL[1] + rR * vnR * vR[1], dpL + dpR, n2, false);
+  Fs[3] = addn<AX>(rL * vnL * vL[2] + rR * vnR * vR[2], dpL + dpR, n3, false);
   Fs[4] = rL * vnL * dHL + rR * vnR * dHR;
   if (kind == 3) {
 #pragma unroll
@@ -666,22 +727,29 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
   const T rc = rsq(c2);
   const T c = c2 * rc;
   const T ic2 = rc * rc;
-  const T vn = u1 * n1 + u2 * n2 + u3 * n3;
+  const T vn = dotn<AX>(u1, u2, u3, n1, n2, n3);
   const T dr = rR - rL, dp = dpR - dpL;
   const T dv1 = vR[0] - vL[0], dv2 = vR[1] - vL[1], dv3 = vR[2] - vL[2];
-  const T dvn = dv1 * n1 + dv2 * n2 + dv3 * n3;
+  const T dvn = dotn<AX>(dv1, dv2, dv3, n1, n2, n3);
   const T a1 = (T)0.5 * (dp - rho * c * dvn) * ic2;
   const T a2 = dr - dp * ic2;
   const T a3 = (T)0.5 * (dp + rho * c * dvn) * ic2;
   const T l1 = fabs(vn - c), l2 = fabs(vn), l3 = fabs(vn + c);
-  const T t1 = dv1 - dvn * n1, t2 = dv2 - dvn * n2, t3 = dv3 - dvn * n3;
-  const T udt = u1 * t1 + u2 * t2 + u3 * t3;
+  // the velocity jump's tangential part (AX: its first component is zero)
+  const T t1 = AX ? (T)0 : dv1 - dvn * n1, t2 = AX ? dv2 : dv2 - dvn * n2, t3 = AX ? dv3 : dv3 - dvn * n3;
+  const T udt = AX ? u2 * t2 + u3 * t3 : u1 * t1 + u2 * t2 + u3 * t3;
   const T w1 = l1 * a1, w3 = l3 * a3;
   T W[5];
   W[0] = w1 + l2 * a2 + w3;
-  W[1] = w1 * (u1 - c * n1) + l2 * (a2 * u1 + rho * t1) + w3 * (u1 + c * n1);
-  W[2] = w1 * (u2 - c * n2) + l2 * (a2 * u2 + rho * t2) + w3 * (u2 + c * n2);
-  W[3] = w1 * (u3 - c * n3) + l2 * (a2 * u3 + rho * t3) + w3 * (u3 + c * n3);
+  if constexpr (AX) {
+    W[1] = w1 * (u1 - c) + l2 * (a2 * u1) + w3 * (u1 + c);
+    W[2] = W[0] * u2 + l2 * (rho * t2);
+    W[3] = W[0] * u3 + l2 * (rho * t3);
+  } else {
+    W[1] = w1 * (u1 - c * n1) + l2 * (a2 * u1 + rho * t1) + w3 * (u1 + c * n1);
+    W[2] = w1 * (u2 - c * n2) + l2 * (a2 * u2 + rho * t2) + w3 * (u2 + c * n2);
+    W[3] = w1 * (u3 - c * n3) + l2 * (a2 * u3 + rho * t3) + w3 * (u3 + c * n3);
+  }
   W[4] = w1 * (dH - vn * c) + l2 * (a2 * ((T)0.5 * q2 - (T)R.H) + rho * udt) + w3 * (dH + vn * c);
 #pragma unroll
   for (int k = 0; k < 5; k++) F[k] = (T)0.5 * area * (Fs[k] - W[k]);
@@ -693,13 +761,15 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
 // Lifted gradient of g = (v1, v2, v3, T) at this lane's node and the contravariant viscous
 // flux F~v^d = sum_x Ja^d_x Fv_x (momentum 1..3, energy) in each reference direction d.
 //   J grad g = sum_d Ja^d [ D_d g + (1/w_N)(g* - g) at xi_d=+1 - (1/w_0)(g* - g) at xi_d=-1 ]
-template <int n, typename T>
+// (CART: Ja^d = cja[d] e_d, so the sum over d is one term and ja is not read)
+template <int n, typename T, bool CART>
 __device__ __forceinline__ void gradient_and_viscous_flux(int t, int ti, int tj, int tk,
                                                           const double* sD, T iwN, T iw0,
                                                           const T* const sG[4],
                                                           const T (*sJ)[4][n * n], const double ja[9],
-                                                          double ij, T mu, T kappa, T Fvd[3][4]) {
+                                                          double ij, const View& v, T Fvd[3][4]) {
   constexpr int N = n - 1, nf = n * n;
+  const T mu = (T)v.mu, kappa = (T)v.kappa;
   T a[3][4];
 #pragma unroll
   for (int d = 0; d < 3; d++) {
@@ -729,7 +799,8 @@ __device__ __forceinline__ void gradient_and_viscous_flux(int t, int ti, int tj,
   for (int c = 0; c < 4; c++)
 #pragma unroll
     for (int x = 0; x < 3; x++)
-      gr[c][x] = (T)ij * ((T)ja[x] * a[0][c] + (T)ja[3 + x] * a[1][c] + (T)ja[6 + x] * a[2][c]);
+      gr[c][x] = CART ? (T)(ij * v.cja[x]) * a[x][c]
+                      : (T)ij * ((T)ja[x] * a[0][c] + (T)ja[3 + x] * a[1][c] + (T)ja[6 + x] * a[2][c]);
   const T v1 = sG[0][t], v2 = sG[1][t], v3 = sG[2][t];
   const T divv = gr[0][0] + gr[1][1] + gr[2][2];
   T tau[3][3];
@@ -750,7 +821,8 @@ __device__ __forceinline__ void gradient_and_viscous_flux(int t, int ti, int tj,
   for (int d = 0; d < 3; d++)
 #pragma unroll
     for (int c = 0; c < 4; c++)
-      Fvd[d][c] = (T)ja[3 * d] * Fv[0][c] + (T)ja[3 * d + 1] * Fv[1][c] + (T)ja[3 * d + 2] * Fv[2][c];
+      Fvd[d][c] = CART ? (T)v.cja[d] * Fv[d][c]
+                       : (T)ja[3 * d] * Fv[0][c] + (T)ja[3 * d + 1] * Fv[1][c] + (T)ja[3 * d + 2] * Fv[2][c];
 }
 
 // g = (v1, v2, v3, T - T_ref): only differences and gradients of g enter BR1, so the constant
@@ -835,13 +907,14 @@ __device__ __forceinline__ void broken_face_fluxes(int t, int ti, int tj, int tk
   }
 }
 
-// Phase 2 (per face point q of face f = 2 d + side, own node io): the face flux of the scheme,
+// Phase 2 (per face point q of face f = 2 d + side, own node io of element e, whose LDS arrays
+// start at node lo and face fo): the face flux of the scheme,
 // contravariant along this element's Ja^d at io (the owner's after the face normals were made
 // single-valued).  For the interior penalty the neighbour's g and J are read from global memory;
 // both elements evaluate the same expression on the same values, so the penalty is single-valued.
 template <int n, typename T>
 __device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cur, double Tref, int f, int q,
-                                                    int io, T iwN, T iw0, const T* const sG[4],
+                                                    int io, int lo, int fo, T iwN, T iw0, const T* const sG[4],
                                                     const T (*sJ)[4][n * n], const T (*sFb)[4][n * n],
                                                     T Ff[4]) {
   constexpr int N = n - 1, nn = n * n * n;
@@ -850,13 +923,13 @@ __device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cu
   const long base = (long)e * nn;
   const T s1 = (T)v.Ja[base * 9 + (3 * d) * nn + io], s2 = (T)v.Ja[base * 9 + (3 * d + 1) * nn + io],
           s3 = (T)v.Ja[base * 9 + (3 * d + 2) * nn + io];
-  const T v1 = sG[0][io], v2 = sG[1][io], v3 = sG[2][io];
+  const T v1 = sG[0][lo + io], v2 = sG[1][lo + io], v3 = sG[2][lo + io];
   T gr[4][3], m1 = v1, m2 = v2, m3 = v3;
   if (v.visc_flux == 1) {  // BR2
     const T k = eta * (T)v.invJ[base + io];
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-      const T lift = side ? iwN * sJ[f][c][q] : -iw0 * sJ[f][c][q];
+      const T lift = side ? iwN * sJ[fo + f][c][q] : -iw0 * sJ[fo + f][c][q];
       gr[c][0] = k * s1 * lift;
       gr[c][1] = k * s2 * lift;
       gr[c][2] = k * s3 * lift;
@@ -870,7 +943,7 @@ __device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cu
     for (int c = 0; c < 5; c++) un[c] = v.U[cur][(long)ne * nn * 5 + c * nn + inb];
     T gn[4];
     gvars(un, v.gamma, Tref, gn);
-    const T go[4] = {v1, v2, v3, sG[3][io]};
+    const T go[4] = {v1, v2, v3, sG[3][lo + io]};
     const double Jo = v.J[base + io], Jn = v.J[(long)ne * nn + inb];
     const T a2 = s1 * s1 + s2 * s2 + s3 * s3;
     const T ia = rsq(a2);
@@ -889,7 +962,7 @@ __device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cu
   T Fp[3][4];
   viscous_flux_g(m1, m2, m3, gr, mu, kappa, Fp);
 #pragma unroll
-  for (int c = 0; c < 4; c++) Ff[c] = sFb[f][c][q] + (s1 * Fp[0][c] + s2 * Fp[1][c] + s3 * Fp[2][c]);
+  for (int c = 0; c < 4; c++) Ff[c] = sFb[fo + f][c][q] + (s1 * Fp[0][c] + s2 * Fp[1][c] + s3 * Fp[2][c]);
 }
 
 // ------------------------------------------------------------------ initial conditions

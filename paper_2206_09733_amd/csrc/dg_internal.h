@@ -99,10 +99,24 @@ struct View {
   // of that launch): the filtered contravariant flux [E][12][nn] of the stage's input state,
   // index 4 d + c (c = momentum 1..3, energy), added to the viscous flux
   const double* Fa;
+  // uniform Lobatto meshes: 1 / w_0 and 1 / w_N
+  double iw0, iwN;
+  // plain (undeformed) boxes: the metric terms are constants, Ja^d = cja[d] e_d (the face areas
+  // on the reference element), 1/J = cij, d xi_d / d x_d = cij cja[d]
+  double cja[3], cij;
 };
 
+// Elements per workgroup of the uniform-order stage and gradient kernels: low orders pack several
+// elements into one wave (N = 1: 8 of 8 nodes; N = 2: 2 of 27 nodes, 54 of 64 lanes), the others
+// take one element per workgroup.
+__host__ __device__ constexpr int wg_elems(int N) { return N == 1 ? 8 : (N == 2 ? 2 : 1); }
+__host__ __device__ constexpr int wg_lanes(int N) {
+  return ((N + 1) * (N + 1) * (N + 1) * wg_elems(N) + 63) / 64 * 64;
+}
+__host__ __device__ constexpr int wg_count(int N, int E) { return (E + wg_elems(N) - 1) / wg_elems(N); }
+
 // Several solvers of one order and precision advanced by one launch: workgroup b of the grid
-// works on element b - start[m] of member m (start[m] <= b < start[m+1]); each member's View
+// is workgroup b - start[m] of member m (start[m] <= b < start[m+1]); each member's View
 // lives in device memory (a copy inside the member's own buffer).
 constexpr int kMaxBatch = 32;
 struct BatchArgs {
@@ -124,10 +138,11 @@ hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rk
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st);
 hipError_t launch_diag_final(const View& v, hipStream_t st);  // partials -> diag, fixed order
 // batched Navier-Stokes gradient pass and stage of members of order N (all viscous, or all
-// inviscid for the stage), FP32-bulk or FP64
-hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, hipStream_t st);  // xv: BR2/IP
-hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, int fx, double rkA, double rkB,
-                              int mode, hipStream_t st);  // fx: the members' flux family
+// inviscid for the stage), FP32-bulk or FP64; deform: some member lies on a deformed box
+hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, bool deform,
+                                 hipStream_t st);  // xv: BR2/IP
+hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, bool deform, int fx, double rkA,
+                              double rkB, int mode, hipStream_t st);  // fx: the members' flux family
 // Gauss-Legendre nodes: face traces of U[cur], then the weak-form residual / RK stage
 hipError_t launch_stage_gauss(const View& v, int cur, double dt, double rkA, double rkB, int mode, hipStream_t st);
 // Gauss-Legendre with the interior penalty or BR2: the face factors Jt or Mt (after launch_geometry)
@@ -142,8 +157,8 @@ hipError_t launch_step_size(const View& v, int cur, double cfl, double hmin, dou
 // the extended flux families 1..3 (FP64), in kernels_ext.hip; called by the two launchers above
 hipError_t launch_stage_ext(const View& v, int fx, int cur, double dt, double rkA, double rkB, int mode,
                             hipStream_t st);
-hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, int fx, double rkA, double rkB, int mode,
-                                  hipStream_t st);
+hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, bool deform, int fx, double rkA, double rkB,
+                                  int mode, hipStream_t st);
 
 // mixed-order meshes (kernels_mixed.hip).  The stage runs one launch per bucket of elements
 // (bucket b: 64 b < nodes <= 64 (b + 1)); bit b of `tiles` gives bucket b two nodes per lane

@@ -279,16 +279,23 @@ __global__ void ic_kernel(View v, int cur, int ic, IcParams P) {
 
 // ------------------------------------------------------------------ pass A (Navier-Stokes)
 // grad_body (grad_body.h): BR1 gradient and face viscous fluxes of one element
-template <int N, typename T, bool XV>
-__global__ void __launch_bounds__(nthreads_for(N)) grad_kernel(View v, int cur) {
-  grad_body<N, T, XV>(v, block_element(v.E), cur);
+template <int N, typename T, bool XV, bool CART>
+__global__ void __launch_bounds__(wg_lanes(N)) grad_kernel(View v, int cur) {
+  __shared__ GradLds<N, T, XV, wg_elems(N)> lds;
+  grad_body<N, T, XV, CART, wg_elems(N)>(lds, v, block_element(wg_count(N, v.E)), cur);
 }
 
-template <int N, typename T, bool XV>
-__global__ void __launch_bounds__(nthreads_for(N)) grad_batch_kernel(BatchArgs B) {
-  int m, e;
-  batch_member(B, m, e);
-  grad_body<N, T, XV>(*B.view[m], e, B.cur[m]);
+// CART: every member is a plain box; otherwise each member takes the form of its own box
+template <int N, typename T, bool XV, bool CART>
+__global__ void __launch_bounds__(wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
+  __shared__ GradLds<N, T, XV, wg_elems(N)> lds;
+  int m, w;
+  batch_member(B, m, w);
+  const View& v = *B.view[m];
+  if (CART || (!XV && !v.deform))
+    grad_body<N, T, XV, true, wg_elems(N)>(lds, v, w, B.cur[m]);
+  else
+    grad_body<N, T, XV, false, wg_elems(N)>(lds, v, w, B.cur[m]);
 }
 
 // ------------------------------------------------------------------ diagnostics (FP64)
@@ -554,10 +561,13 @@ static hipError_t geometry_n(const View& v, hipStream_t st) {
 
 template <int N, typename T>
 static hipError_t gradient_nt(const View& v, int cur, hipStream_t st) {
+  const dim3 grid(wg_count(N, v.E)), block(wg_lanes(N));
   if (v.visc_flux != 0)
-    hipLaunchKernelGGL((grad_kernel<N, T, true>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur);
+    hipLaunchKernelGGL((grad_kernel<N, T, true, false>), grid, block, 0, st, v, cur);
+  else if (v.deform)
+    hipLaunchKernelGGL((grad_kernel<N, T, false, false>), grid, block, 0, st, v, cur);
   else
-    hipLaunchKernelGGL((grad_kernel<N, T, false>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur);
+    hipLaunchKernelGGL((grad_kernel<N, T, false, true>), grid, block, 0, st, v, cur);
   return hipGetLastError();
 }
 
@@ -616,25 +626,28 @@ hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rk
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st) { DG_DISPATCH(diag_n, v, cur, st) }
 
 template <int N, typename T>
-static hipError_t gradient_batch_nt(const BatchArgs& B, bool xv, hipStream_t st) {
+static hipError_t gradient_batch_nt(const BatchArgs& B, bool xv, bool deform, hipStream_t st) {
+  const dim3 grid(B.start[B.n]), block(wg_lanes(N));
   if (xv)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, true>), dim3(B.start[B.n]), dim3(nthreads_for(N)), 0, st, B);
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, true, false>), grid, block, 0, st, B);
+  else if (deform)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, false>), grid, block, 0, st, B);
   else
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false>), dim3(B.start[B.n]), dim3(nthreads_for(N)), 0, st, B);
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, true>), grid, block, 0, st, B);
   return hipGetLastError();
 }
 
 template <int N>
-static hipError_t gradient_batch_n(const BatchArgs& B, bool fp32, bool xv, hipStream_t st) {
-  return fp32 ? gradient_batch_nt<N, float>(B, xv, st) : gradient_batch_nt<N, double>(B, xv, st);
+static hipError_t gradient_batch_n(const BatchArgs& B, bool fp32, bool xv, bool deform, hipStream_t st) {
+  return fp32 ? gradient_batch_nt<N, float>(B, xv, deform, st) : gradient_batch_nt<N, double>(B, xv, deform, st);
 }
 
 template <int N>
-static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, int fx, double a, double b,
+static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, bool deform, int fx, double a, double b,
                                 int mode, hipStream_t st) {
-  if (fp32) return stage_batch_nt<N, float, 0>(B, visc, a, b, mode, st);
-  if (fx != 0) return launch_stage_batch_ext(B, N, visc, fx, a, b, mode, st);
-  return stage_batch_nt<N, double, 0>(B, visc, a, b, mode, st);
+  if (fp32) return stage_batch_nt<N, float, 0>(B, visc, deform, a, b, mode, st);
+  if (fx != 0) return launch_stage_batch_ext(B, N, visc, deform, fx, a, b, mode, st);
+  return stage_batch_nt<N, double, 0>(B, visc, deform, a, b, mode, st);
 }
 
 #define DG_DISPATCH_N(NV, FN, ...)                    \
@@ -649,16 +662,16 @@ static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, int fx
     default: return hipErrorInvalidValue;             \
   }
 
-hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, hipStream_t st) {
+hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, bool deform, hipStream_t st) {
   if (B.n < 1 || B.n > kMaxBatch) return hipErrorInvalidValue;
-  DG_DISPATCH_N(N, gradient_batch_n, B, fp32, xv, st)
+  DG_DISPATCH_N(N, gradient_batch_n, B, fp32, xv, deform, st)
 }
 
-hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, int fx, double rkA, double rkB,
-                              int mode, hipStream_t st) {
+hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, bool deform, int fx, double rkA,
+                              double rkB, int mode, hipStream_t st) {
   if (B.n < 1 || B.n > kMaxBatch) return hipErrorInvalidValue;
   if (fx < 0 || fx > 3 || (fp32 && fx != 0)) return hipErrorInvalidValue;
-  DG_DISPATCH_N(N, stage_batch_n, B, fp32, visc, fx, rkA, rkB, mode, st)
+  DG_DISPATCH_N(N, stage_batch_n, B, fp32, visc, deform, fx, rkA, rkB, mode, st)
 }
 
 hipError_t launch_adapt_reset(const View& v, hipStream_t st) {

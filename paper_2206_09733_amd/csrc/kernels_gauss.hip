@@ -322,7 +322,7 @@ __global__ void __launch_bounds__(nthreads_for(N))
       for (int c = 0; c < 4; c++) sGs[f][c][q] = 0.5 * (go[c] + gn[c]);
     }
     double F[5];
-    face_flux<double, XS>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
+    face_flux<XS>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
     if (VISC) {
       const double* fo = v.Fvf + ((long)e * 6 + f) * 4 * nf;
       const double* fn = v.Fvf + ((long)ne * 6 + (f ^ 1)) * 4 * nf;

@@ -315,12 +315,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
       const double S[3] = {a[5], a[6], a[7]};
       const double uR[5] = {a[8], a[9], a[10], a[11], a[12]};
       T F[5];
-      if (DEV) {
+      if constexpr (DEV) {
         double F0d;
         face_flux_dev<T>(v.surf, uL, uR, S, v.gamma, Rf, F, F0d);
         sA[5][x] = F0d;
       } else {
-        face_flux<T, XS>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
+        face_flux<XS>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
       }
 #pragma unroll
       for (int c = 0; c < 5; c++) sA[c][x] = (double)F[c];
@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
             fo5 = fo4 + NC * pt2, fend = fo4 + 2 * NC * pt2;
 
   __shared__ double sD[3][kMixNF], sw[3][kMixN];
-  __shared__ T sP[7][NNMAX];             // rho, v1, v2, v3, beta, ln rho, ln beta (FP32-bulk: deviations)
+  __shared__ T sP[5][NNMAX];             // rho, v1, v2, v3, beta (FP32-bulk: deviations)
   constexpr int NV = DEV ? NNMAX : 1;
   __shared__ double sVd[3][NV];          // FP32-bulk: FP64 velocities for the mass flux
   __shared__ double sJ3[3][NNMAX];       // Ja^d of the direction in work
@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
     if (q < I.nn) {
       const Prim<T> P = DEV ? make_prim_dev<T>(u[s], v.gamma, Rf) : make_prim<T>(u[s], v.gamma);
       sP[0][q] = P.rho; sP[1][q] = P.v1; sP[2][q] = P.v2; sP[3][q] = P.v3;
-      sP[4][q] = P.beta; sP[5][q] = P.lrho; sP[6][q] = P.lbeta;
+      sP[4][q] = P.beta;
       if (DEV) {
         const double ir = rcp(u[s][0]);
         sVd[0][q] = u[s][1] * ir;
@@ -516,20 +516,18 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
     const int b0 = q - id * sd;
     Prim<T> A;
     A.rho = sP[0][q]; A.v1 = sP[1][q]; A.v2 = sP[2][q]; A.v3 = sP[3][q];
-    A.beta = sP[4][q]; A.lrho = sP[5][q]; A.lbeta = sP[6][q];
-    A.h = (T)0.5 * (A.v1 * A.v1 + A.v2 * A.v2 + A.v3 * A.v3);
+    A.beta = sP[4][q];
     const double ja0 = sJ3[0][q], ja1 = sJ3[1][q], ja2 = sJ3[2][q];
     for (int m = 0; m < n; m++) {
       if (m == id) continue;
       const int qm = b0 + m * sd;
       Prim<T> B;
       B.rho = sP[0][qm]; B.v1 = sP[1][qm]; B.v2 = sP[2][qm]; B.v3 = sP[3][qm];
-      B.beta = sP[4][qm]; B.lrho = sP[5][qm]; B.lbeta = sP[6][qm];
-      B.h = (T)0.5 * (B.v1 * B.v1 + B.v2 * B.v2 + B.v3 * B.v3);
+      B.beta = sP[4][qm];
       const double md[3] = {ja0 + sJ3[0][qm], ja1 + sJ3[1][qm], ja2 + sJ3[2][qm]};
       T F[5];
       double F0d = 0.0;
-      if (DEV) {
+      if constexpr (DEV) {
         const double va[3] = {sVd[0][q], sVd[1][q], sVd[2][q]};
         const double vb[3] = {sVd[0][qm], sVd[1][qm], sVd[2][qm]};
         if (v.vol == 0) {
@@ -539,7 +537,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
           flux_central_dev(A, B, (T)md[0], (T)md[1], (T)md[2], va, vb, md, Rf, F, F0d);
         }
       } else {
-        vol_flux<T, KEP>(v.vol, A, B, (T)md[0], (T)md[1], (T)md[2], ce, gm1, F);
+        vol_flux<KEP>(v.vol, A, B, (T)md[0], (T)md[1], (T)md[2], ce, gm1, F);
       }
       const double Dm = sD[d][id * n + m];
 #pragma unroll

@@ -373,11 +373,12 @@ __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_p
 // element in one workgroup: the second body reads the element's state, metric terms and
 // neighbour traces that the first has just read, from the L2 cache instead of HBM.  The two
 // bodies share no LDS and no results.
-template <int N, typename T>
+template <int N, typename T, bool CART>
 __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_per_eu(N <= 6 ? 4 : 3)))
     grad_svv_kernel(View v, int cur, SvvArgs a) {
   const int e = block_element(v.E);
-  grad_body<N, T, false>(v, e, cur);
+  __shared__ GradLds<N, T, false, 1> lds;
+  grad_body<N, T, false, CART, 1>(lds, v, e, cur);
   svv_flux_body<N>(v, e, cur, a);
 }
 
@@ -404,13 +405,19 @@ static hipError_t launch_svv_flux_n(const View& v, int cur, const SvvArgs& a, hi
   return hipGetLastError();
 }
 
+template <int N, typename T>
+static hipError_t launch_grad_svv_nt(const View& v, int cur, const SvvArgs& a, hipStream_t st) {
+  const dim3 grid(v.E), block(nthreads_for(N));
+  if (v.deform)
+    hipLaunchKernelGGL((grad_svv_kernel<N, T, false>), grid, block, 0, st, v, cur, a);
+  else
+    hipLaunchKernelGGL((grad_svv_kernel<N, T, true>), grid, block, 0, st, v, cur, a);
+  return hipGetLastError();
+}
+
 template <int N>
 static hipError_t launch_grad_svv_n(const View& v, int cur, const SvvArgs& a, hipStream_t st) {
-  if (v.fp32)
-    hipLaunchKernelGGL((grad_svv_kernel<N, float>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
-  else
-    hipLaunchKernelGGL((grad_svv_kernel<N, double>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
-  return hipGetLastError();
+  return v.fp32 ? launch_grad_svv_nt<N, float>(v, cur, a, st) : launch_grad_svv_nt<N, double>(v, cur, a, st);
 }
 
 hipError_t launch_grad_svv(const View& v, int cur, const SvvArgs& a, hipStream_t st) {

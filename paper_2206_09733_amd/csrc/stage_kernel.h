@@ -1,7 +1,7 @@
 // stage_kernel.h -- the stage kernel (residual of one element and the fused low-storage RK
 // update) and its batched entry, as templates over the order N, the arithmetic type T, the
-// viscous terms and the flux family FX.  kernels.hip instantiates family 0 (and FP32-bulk),
-// kernels_ext.hip the extended families 1..3, so the two compile in parallel.
+// viscous terms, the flux family FX and the plain-box form CART.  kernels.hip instantiates family
+// 0 (and FP32-bulk), kernels_ext.hip the extended families 1..3, so the two compile in parallel.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -15,142 +15,206 @@ namespace dg {
 // ------------------------------------------------------------------ stage kernel
 // Residual of one element and, in RK mode, the low-storage update
 //   dU <- A dU + dt R;  U_out <- U_in + B dU   (dU not read when A = 0).
-// LDS holds the primitive variables of the element, the metric components of the reference
-// direction being processed, the six face-flux grids, and one phase-dependent region (BR1
-// temperature and half jumps; one direction of the contravariant viscous flux; the two-point
-// fluxes of one direction).
-// occupancy target of the stage kernel: waves per SIMD the register allocation must allow (the
-// FP32-bulk kernels fit 4 at orders 1, 2, 4, 5 with at most 2 spilled registers, measured faster
-// than 3 for Euler and NS alike; at order 3 they would spill 8-10 and keep 3)
+//
+// Volume term.  A lane holds one node.  Along each direction it evaluates the two-point fluxes
+// with the nodes at cyclic distance o = 1 .. (n-1)/2 on its line: its own state and metric are in
+// registers, the partner's come from LDS, and the flux is used twice, by this node at once and by
+// the partner from LDS (each pair of a line is so evaluated once; for even n the pairs at distance
+// n/2 are evaluated by both of their nodes instead of being exchanged).  Every lane has the same
+// number of pairs and no pair list is decoded.  What it replaced: a pair list whose lanes read
+// both nodes from LDS (20 values a pair, and 10 more to gather) behind three barriers a direction,
+// and the viscous term's own three passes.
+// CART (plain boxes): Ja^d = cja[d] e_d is a constant of the mesh, so no metric term is read from
+// memory or LDS, and every flux is formed in a frame rotated to its direction, where the normal
+// is (1, 0, 0).
+//
+// Bound by VALU issue and by the latency of an element's loads, not by HBM (the NS stage at 32^3,
+// N = 4 moves 1.09 GB in 350-360 us).  Measured, RK3 step before -> now, microseconds: deformed
+// NS 32^3 N = 4 FP64 1703 -> 1536, FP32-bulk 1445 -> 1312; deformed Euler RK4 20^3 N = 5 per
+// step 806 -> 657; deformed NS residual 13x11x9 N = 7 191 -> 120; plain Euler 41x36x28 N = 2
+// 322 -> 164; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 821 -> 547.
+//
+// occupancy target of the stage kernel: waves per SIMD the register allocation must allow
 __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32) {
-  return N <= 5 ? (fp32 && N != 3 ? 4 : 3) : 2;
+  return N == 1 ? (fp32 ? 3 : 2) : (N <= 5 ? (fp32 && N != 3 ? 4 : 3) : 2);
 }
 
 // global operands of one face point of the stage kernel's face phase: the neighbour's and the
 // element's traces, the face's scaled normal, and the sum of the two sides' face viscous fluxes
+// (CART: vectors in the frame rotated to the face's direction)
 template <typename T>
 struct FaceIn {
   double un[5], uo[5], S[3];
   T fv[4];
 };
 
+constexpr int align16(int b) { return (b + 15) / 16 * 16; }
+constexpr int imax(int a, int b) { return a > b ? a : b; }
+
+// LDS of a stage workgroup (byte offsets):
+//   D, Dhat; the primitive variables rho, v1, v2, v3, beta (FP32-bulk: deviations of rho, beta);
+//   FP32-bulk: FP64 velocities for the mass flux, and the face fluxes, which it lifts beside each
+//   direction's volume sum (they largely cancel; in FP64 the order does not matter and the lifts
+//   are taken with phase A);
+//   one region that holds each phase's arrays in turn:
+//     A (face phase): with viscosity temperature and half jumps of g; the face fluxes (FP32-bulk:
+//       their FP64 mass components);
+//     B (one direction of the volume phase): the direction's metric terms and contravariant
+//       viscous flux, and the exchanged two-point fluxes (FP32-bulk: and their FP64 mass parts).
+template <int N, typename T, bool VISC, bool CART>
+struct StageLds {
+  static constexpr int n = N + 1, nf = n * n, EW = wg_elems(N), NN = EW * n * n * n, K = (n - 1) / 2;
+  static constexpr bool DEV = sizeof(T) == 4;
+  static constexpr int S = (int)sizeof(T);
+  static constexpr int oD = 0;
+  static constexpr int oDh = oD + nf * 8;
+  static constexpr int oP = align16(oDh + (VISC ? nf * 8 : 0));
+  static constexpr int oVd = align16(oP + 5 * NN * S);
+  static constexpr int oFk = align16(oVd + (DEV ? 3 * NN * 8 : 0));
+  static constexpr int oR = align16(oFk + (DEV ? EW * 30 * nf * S : 0));
+  static constexpr int bT = VISC ? align16(NN * S) : 0;
+  static constexpr int bJ = VISC ? align16(EW * 24 * nf * S) : 0;
+  static constexpr int bytesA = bT + bJ + EW * (DEV ? 6 : 30) * nf * 8;
+  static constexpr int bM = CART ? 0 : 3 * NN * 8;
+  static constexpr int bV = VISC ? align16(4 * NN * S) : 0;
+  static constexpr int bX = DEV ? K * NN * 8 + 4 * K * NN * 4 : 5 * K * NN * 8;
+  static constexpr int bytes = oR + imax(bytesA, bM + bV + bX);
+};
+
 // SVA (Navier-Stokes): the filtered spectral-vanishing-viscosity flux v.Fa (FP64; rounded to T
 // as it is read) of the same state joins the viscous flux at the nodes, and on the faces the average of both sides'
 // stored values (as the viscous face fluxes; a face node's lane lifts it, the sum taken in the same
 // order from both sides), so the residual holds its term too
-template <int N, typename T, bool VISC, int FX, bool SVA = false>
-__device__ __forceinline__ void stage_body(const View& v, const int e, const int cur, const double dt,
+template <int N, typename T, bool VISC, int FX, bool SVA, bool CART>
+__device__ __forceinline__ void stage_body(char* lds, const View& v, const int wg, const int cur, const double dt,
                                            const double rkA, const double rkB, const int mode) {
   static_assert(!SVA || VISC, "the folded SVV term needs the viscous kernel");
-  constexpr int n = N + 1, nn = n * n * n, nf = n * n, NT = nthreads_for(N);
-  constexpr int np = n * (n - 1) / 2;  // pairs (a < b) on one line of n nodes
-  constexpr int P = nf * np;           // pairs per direction
+  constexpr int n = N + 1, nn = n * n * n, nf = n * n;
+  constexpr int EW = wg_elems(N), NT = wg_lanes(N), NN = EW * nn;
+  constexpr int K = (n - 1) / 2;           // cyclic distances whose fluxes are exchanged
+  constexpr bool HALF = n % 2 == 0;        // the distance n/2, evaluated by both nodes
+  constexpr int NFP = EW * 6 * nf;         // face points of the workgroup
+  constexpr bool DEV = sizeof(T) == 4;     // FP32-bulk: deviation form, FP64 mass flux
   const int t = threadIdx.x;
-  const bool act = t < nn;
-  const int ti = t % n, tj = (t / n) % n, tk = t / nf;
+  const bool act = t < NN;
+  const int el = EW > 1 ? (act ? t / nn : 0) : 0;
+  const int tl = EW > 1 ? t - el * nn : t;  // node of its element
+  const int ti = tl % n, tj = (tl / n) % n, tk = tl / nf;
   const int ii[3] = {ti, tj, tk};
+  // the last workgroup repeats the last element in its spare places (without storing it)
+  const int e0 = wg * EW;
+  const int e = EW > 1 ? (e0 + el < v.E ? e0 + el : v.E - 1) : e0;
+  const bool put = act && (EW == 1 || e0 + el < v.E);
   const double* __restrict__ Uin = v.U[cur];
-  constexpr bool DEV = sizeof(T) == 4;  // FP32-bulk: deviation form
   const Ref Rf = make_ref(v.rho_r, v.p_r, v.gamma);
   const double Tref = DEV ? Rf.por : 0.0;
 
-  __shared__ double sD[n * n], sDh[n * n], sw[n];
-  __shared__ T sP[7][nn];      // rho, v1, v2, v3, beta, ln rho, ln beta (FP32-bulk: deviations)
-  __shared__ double sJa3[3][nn];  // Ja^d of the direction d being processed
-  __shared__ T sF[6][5][nf];      // face fluxes F~* - F~v*
-  __shared__ unsigned char sPa[np], sPb[np];
-  // FP32-bulk keeps the mass flux in FP64: velocities, face and pair mass fluxes
-  constexpr int nnD = DEV ? nn : 1, nfD = DEV ? nf : 1;
-  __shared__ double sVd[3][nnD];
-  // One region holds each phase's arrays in turn:
-  //   A (face phase, until the gradient and the mass-flux lift are taken): temperature, half
-  //     jumps of g and (FP32-bulk) the FP64 face mass fluxes;
-  //   B (viscous volume phase): one direction of the contravariant viscous flux;
-  //   C (volume phase): the two-point fluxes of one direction (and their FP64 mass fluxes).
-  constexpr int a16 = 16;
-  constexpr int offJ = VISC ? ((nn * (int)sizeof(T) + a16 - 1) / a16) * a16 : 0;
-  constexpr int offF0 = VISC ? ((offJ + 24 * nf * (int)sizeof(T) + a16 - 1) / a16) * a16 : 0;
-  constexpr int bytesA = offF0 + (DEV ? 6 * nf * 8 : 0);
-  constexpr int bytesB = VISC ? 4 * nn * (int)sizeof(T) : 0;
-  constexpr int bytesC = ((5 * P * (int)sizeof(T) + a16 - 1) / a16) * a16 + (DEV ? 8 * P : 0);
-  constexpr int bytesAB = bytesA > bytesB ? bytesA : bytesB;
-  __shared__ __align__(16) char sRaw[bytesAB > bytesC ? bytesAB : bytesC];
-  T* sT = reinterpret_cast<T*>(sRaw);                                // temperature
-  T(*sJ)[4][nf] = reinterpret_cast<T(*)[4][nf]>(sRaw + offJ);        // half jumps of g
-  double(*sF0d)[nfD] = reinterpret_cast<double(*)[nfD]>(sRaw + offF0);  // FP32-bulk face mass flux
-  T(*sFv)[nn] = reinterpret_cast<T(*)[nn]>(sRaw);                    // F~v^d, 4 components
-  T(*sPair)[P] = reinterpret_cast<T(*)[P]>(sRaw);
-  double* sM = reinterpret_cast<double*>(sRaw + ((5 * P * (int)sizeof(T) + a16 - 1) / a16) * a16);  // pair mass flux
+  // LDS (see StageLds)
+  using L = StageLds<N, T, VISC, CART>;
+  double* sD = reinterpret_cast<double*>(lds + L::oD);
+  double* sDh = reinterpret_cast<double*>(lds + L::oDh);
+  T(*sP)[NN] = reinterpret_cast<T(*)[NN]>(lds + L::oP);
+  double(*sVd)[NN] = reinterpret_cast<double(*)[NN]>(lds + L::oVd);
+  T(*sFk)[5][nf] = reinterpret_cast<T(*)[5][nf]>(lds + L::oFk);
+  T* sT = reinterpret_cast<T*>(lds + L::oR);
+  T(*sJ)[4][nf] = reinterpret_cast<T(*)[4][nf]>(lds + L::oR + L::bT);
+  double(*sFa)[5][nf] = reinterpret_cast<double(*)[5][nf]>(lds + L::oR + L::bT + L::bJ);
+  double(*sF0)[nf] = reinterpret_cast<double(*)[nf]>(lds + L::oR + L::bT + L::bJ);
+  double(*sM)[NN] = reinterpret_cast<double(*)[NN]>(lds + L::oR);
+  T(*sFv)[NN] = reinterpret_cast<T(*)[NN]>(lds + L::oR + L::bM);
+  // exchanged fluxes of distance o: components at sX[o - 1][c] (FP64: 5; FP32-bulk: 1..4 and the
+  // FP64 mass flux in sX0)
+  double(*sX0)[NN] = reinterpret_cast<double(*)[NN]>(lds + L::oR + L::bM + L::bV);
+  T(*sX)[DEV ? 4 : 5][NN] =
+      reinterpret_cast<T(*)[DEV ? 4 : 5][NN]>(lds + L::oR + L::bM + L::bV + (DEV ? K * NN * 8 : 0));
 
   // tables (every lane loads, the first n^2 store: no wait of their own before the other loads)
   static_assert(n * n <= NT, "one table entry per lane");
   const int tt = t < n * n ? t : 0;
-  const double tD = v.tab[2 * n + tt], tDh = v.tab[2 * n + n * n + tt], tw = v.tab[n + (t < n ? t : 0)];
-  if (t < np) {  // pair k -> (a, b), ordered by a then b
-    int a = 0, k = t;
-    while (k >= n - 1 - a) {
-      k -= n - 1 - a;
-      a++;
-    }
-    sPa[t] = (unsigned char)a;
-    sPb[t] = (unsigned char)(a + 1 + k);
-  }
+  const double tD = v.tab[2 * n + tt], tDh = VISC ? v.tab[2 * n + n * n + tt] : 0.0;
   const long base = (long)e * nn;
-  // The six neighbours (uniform over the workgroup: scalar loads), and the global operands of
-  // this lane's first face point, issued before the node's own state so that the two memory
+  // The six neighbours (one element per workgroup: uniform, scalar loads), and the global operands
+  // of this lane's first face point, issued before the node's own state so that the two memory
   // round trips overlap.
-  const int nb0 = v.nbr[e * 6], nb1 = v.nbr[e * 6 + 1], nb2 = v.nbr[e * 6 + 2], nb3 = v.nbr[e * 6 + 3],
-            nb4 = v.nbr[e * 6 + 4], nb5 = v.nbr[e * 6 + 5];
+  int nb0 = 0, nb1 = 0, nb2 = 0, nb3 = 0, nb4 = 0, nb5 = 0;
+  if constexpr (EW == 1) {
+    const int* nb = v.nbr + (long)e * 6;
+    nb0 = nb[0], nb1 = nb[1], nb2 = nb[2], nb3 = nb[3], nb4 = nb[4], nb5 = nb[5];
+  }
+  auto neighbour = [&](int ef, int f) {
+    if constexpr (EW > 1) return v.nbr[(long)ef * 6 + f];
+    return f < 3 ? (f == 0 ? nb0 : (f == 1 ? nb1 : nb2)) : (f == 3 ? nb3 : (f == 4 ? nb4 : nb5));
+  };
   const T* FvfAll = VISC ? reinterpret_cast<const T*>(v.Fvf) : nullptr;
   auto face_load = [&](int x, FaceIn<T>& I) {
-    const int f = x / nf, q = x - f * nf;
+    const int fe = EW > 1 ? x / (6 * nf) : 0;
+    const int f = EW > 1 ? x / nf - fe * 6 : x / nf, q = x % nf;
     const int d = f >> 1, side = f & 1;
     const int p = q % n, r = q / n;
     const int io = face_node<n>(d, side ? N : 0, p, r);
     const int inb = face_node<n>(d, side ? 0 : N, p, r);
-    const int ne = f < 3 ? (f == 0 ? nb0 : (f == 1 ? nb1 : nb2)) : (f == 3 ? nb3 : (f == 4 ? nb4 : nb5));
+    const int ef = EW > 1 ? (e0 + fe < v.E ? e0 + fe : v.E - 1) : e;
+    const int ne = neighbour(ef, f);
+    // component of the rotated frame's axis k (CART), or k itself
+    const int a0 = CART ? d : 0, a1 = CART ? (d == 2 ? 0 : d + 1) : 1, a2 = CART ? (d == 0 ? 2 : d - 1) : 2;
+    const double* un = Uin + (long)ne * nn * 5 + inb;
+    const double* uo = Uin + (long)ef * nn * 5 + io;
+    I.un[0] = un[0];
+    I.un[1] = un[(1 + a0) * nn];
+    I.un[2] = un[(1 + a1) * nn];
+    I.un[3] = un[(1 + a2) * nn];
+    I.un[4] = un[4 * nn];
+    I.uo[0] = uo[0];
+    I.uo[1] = uo[(1 + a0) * nn];
+    I.uo[2] = uo[(1 + a1) * nn];
+    I.uo[3] = uo[(1 + a2) * nn];
+    I.uo[4] = uo[4 * nn];
+    if constexpr (CART) {
+      I.S[0] = d == 0 ? v.cja[0] : (d == 1 ? v.cja[1] : v.cja[2]);
+      I.S[1] = I.S[2] = 0.0;
+    } else {
 #pragma unroll
-    for (int c = 0; c < 5; c++) {
-      I.un[c] = Uin[(long)ne * nn * 5 + c * nn + inb];
-      I.uo[c] = Uin[base * 5 + c * nn + io];
+      for (int c = 0; c < 3; c++) I.S[c] = v.Ja[(long)ef * nn * 9 + (3 * d + c) * nn + io];
     }
-#pragma unroll
-    for (int c = 0; c < 3; c++) I.S[c] = v.Ja[base * 9 + (3 * d + c) * nn + io];
     if (VISC) {
-      const T* fo = FvfAll + ((long)e * 6 + f) * 4 * nf;
-      const T* fn = FvfAll + ((long)ne * 6 + (f ^ 1)) * 4 * nf;
-#pragma unroll
-      for (int c = 0; c < 4; c++) I.fv[c] = fo[c * nf + q] + fn[c * nf + q];
+      const T* fo = FvfAll + ((long)ef * 6 + f) * 4 * nf + q;
+      const T* fn = FvfAll + ((long)ne * 6 + (f ^ 1)) * 4 * nf + q;
+      I.fv[0] = fo[a0 * nf] + fn[a0 * nf];
+      I.fv[1] = fo[a1 * nf] + fn[a1 * nf];
+      I.fv[2] = fo[a2 * nf] + fn[a2 * nf];
+      I.fv[3] = fo[3 * nf] + fn[3 * nf];
     }
   };
   FaceIn<T> face0;
-  if (t < 6 * nf) face_load(t, face0);
+  if (t < NFP) face_load(t, face0);
   if (t < n * n) {
     sD[t] = tD;
-    sDh[t] = tDh;
+    if (VISC) sDh[t] = tDh;
   }
-  if (t < n) sw[t] = tw;
-  double ja[9], ij = 0.0;
+  double ja[9], ij = CART ? v.cij : 0.0;
+  Prim<T> A;           // this node
+  double va[3] = {0, 0, 0};  // FP32-bulk: its FP64 velocity
   if (act) {
     double u[5];
 #pragma unroll
-    for (int c = 0; c < 5; c++) u[c] = Uin[base * 5 + c * nn + t];
-    const Prim<T> Pr = DEV ? make_prim_dev<T>(u, v.gamma, Rf) : make_prim<T>(u, v.gamma);
-    sP[0][t] = Pr.rho; sP[1][t] = Pr.v1; sP[2][t] = Pr.v2; sP[3][t] = Pr.v3;
-    sP[4][t] = Pr.beta; sP[5][t] = Pr.lrho; sP[6][t] = Pr.lbeta;
+    for (int c = 0; c < 5; c++) u[c] = Uin[base * 5 + c * nn + tl];
+    A = DEV ? make_prim_dev<T>(u, v.gamma, Rf) : make_prim<T>(u, v.gamma);
+    sP[0][t] = A.rho; sP[1][t] = A.v1; sP[2][t] = A.v2; sP[3][t] = A.v3;
+    sP[4][t] = A.beta;
     if (DEV) {
       const double ir = rcp(u[0]);
-      sVd[0][t] = u[1] * ir;
-      sVd[1][t] = u[2] * ir;
-      sVd[2][t] = u[3] * ir;
+#pragma unroll
+      for (int c = 0; c < 3; c++) {
+        va[c] = u[1 + c] * ir;
+        sVd[c][t] = va[c];
+      }
     }
     // the extended surface fluxes, and the viscous terms, need the registers during the face
-    // phase: those kernels load the metric terms after it (measured: NS 499 -> 488 us at
-    // 32^3, N = 4; the Euler kernel is faster with the early load)
-    if constexpr ((FX & 2) == 0 && !VISC) {
+    // phase: those kernels load the metric terms after it
+    if constexpr (!CART && (FX & 2) == 0 && !VISC) {
 #pragma unroll
-      for (int c = 0; c < 9; c++) ja[c] = v.Ja[base * 9 + c * nn + t];
-      ij = v.invJ[base + t];
+      for (int c = 0; c < 9; c++) ja[c] = v.Ja[base * 9 + c * nn + tl];
+      ij = v.invJ[base + tl];
     }
     if (VISC) {
       T g[4];
@@ -165,35 +229,48 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
   // it is single-valued.
   const double lam_g = (FX & 2) != 0 && v.surf == 8 ? v.adapt[3] : 0.0;  // global Lax-Friedrichs
   auto face_eval = [&](int x, const FaceIn<T>& I) {
-    const int f = x / nf, q = x - f * nf;
+    const int fe = EW > 1 ? x / (6 * nf) : 0;
+    const int ff = x / nf, f = EW > 1 ? ff - fe * 6 : ff, q = x - ff * nf;  // ff = 6 fe + f
     const int d = f >> 1, side = f & 1;
     const int p = q % n, r = q / n;
-    const int io = face_node<n>(d, side ? N : 0, p, r);
+    const int io = (EW > 1 ? fe * nn : 0) + face_node<n>(d, side ? N : 0, p, r);
     double uL[5], uR[5];
 #pragma unroll
     for (int c = 0; c < 5; c++) {
       uL[c] = side ? I.uo[c] : I.un[c];
       uR[c] = side ? I.un[c] : I.uo[c];
     }
+    const int a0 = CART ? d : 0, a1 = CART ? (d == 2 ? 0 : d + 1) : 1, a2 = CART ? (d == 0 ? 2 : d - 1) : 2;
     T F[5];
-    if (DEV) {
-      double F0d;
-      face_flux_dev<T>(v.surf, uL, uR, I.S, v.gamma, Rf, F, F0d);
-      sF0d[f][q] = F0d;
+    double F0d = 0.0;
+    if constexpr (DEV) {
+      face_flux_dev<T, CART>(v.surf, uL, uR, I.S, v.gamma, Rf, F, F0d);
+      sF0[ff][q] = F0d;
     } else {
-      face_flux<T, (FX & 2) != 0>(v.surf, uL, uR, I.S, v.gamma, F, lam_g);
+      face_flux<(FX & 2) != 0, CART>(v.surf, uL, uR, I.S, v.gamma, F, lam_g);
     }
     if (VISC) {
 #pragma unroll
       for (int c = 0; c < 4; c++) F[1 + c] -= (T)0.5 * I.fv[c];
       T gn[4];
       gvars(I.un, v.gamma, Tref, gn);
-      const T go[4] = {sP[1][io], sP[2][io], sP[3][io], sT[io]};
-#pragma unroll
-      for (int c = 0; c < 4; c++) sJ[f][c][q] = (T)0.5 * (gn[c] - go[c]);
+      sJ[ff][a0][q] = (T)0.5 * (gn[0] - sP[1 + a0][io]);
+      sJ[ff][a1][q] = (T)0.5 * (gn[1] - sP[1 + a1][io]);
+      sJ[ff][a2][q] = (T)0.5 * (gn[2] - sP[1 + a2][io]);
+      sJ[ff][3][q] = (T)0.5 * (gn[3] - sT[io]);
     }
-#pragma unroll
-    for (int c = 0; c < 5; c++) sF[f][c][q] = F[c];
+    if constexpr (DEV) {
+      sFk[ff][1 + a0][q] = F[1];
+      sFk[ff][1 + a1][q] = F[2];
+      sFk[ff][1 + a2][q] = F[3];
+      sFk[ff][4][q] = F[4];
+    } else {
+      sFa[ff][0][q] = F[0];
+      sFa[ff][1 + a0][q] = F[1];
+      sFa[ff][1 + a1][q] = F[2];
+      sFa[ff][1 + a2][q] = F[3];
+      sFa[ff][4][q] = F[4];
+    }
   };
   // the metric terms of the kernels that load them late: in FP64 with the standard surface fluxes
   // issued before the remaining face points, so that their latency overlaps that work; the others
@@ -202,15 +279,16 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
   auto load_metric = [&]() {
     if (act) {
 #pragma unroll
-      for (int c = 0; c < 9; c++) ja[c] = v.Ja[base * 9 + c * nn + t];
-      ij = v.invJ[base + t];
+      for (int c = 0; c < 9; c++) ja[c] = v.Ja[base * 9 + c * nn + tl];
+      ij = v.invJ[base + tl];
     }
   };
-  constexpr bool late_metric = (FX & 2) != 0 || VISC;
+  constexpr bool late_metric = !CART && ((FX & 2) != 0 || VISC);
   constexpr bool early = late_metric && !DEV && (FX & 2) == 0 && N != 3;
-  if (t < 6 * nf) face_eval(t, face0);
+  if (t < NFP) face_eval(t, face0);
   if constexpr (early) load_metric();
-  for (int x = t + NT; x < 6 * nf; x += NT) {
+#pragma unroll 1
+  for (int x = t + NT; x < NFP; x += NT) {
     FaceIn<T> I;
     face_load(x, I);
     face_eval(x, I);
@@ -218,55 +296,151 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
   if constexpr (late_metric && !early) load_metric();
   __syncthreads();
 
-  const T iwN = (T)(1.0 / sw[N]), iw0 = (T)(1.0 / sw[0]);
+  const T iwN = (T)v.iwN, iw0 = (T)v.iw0;
   T acc[5] = {0, 0, 0, 0, 0};
   double acc0d = 0.0;  // FP32-bulk mass accumulator
-  // FP32-bulk: lift of the FP64 face mass fluxes, taken before their region is reused (in FP64
-  // the order of the sum does not matter; the FP32 lifts stay beside each direction's volume
-  // sum, which they largely cancel)
-  if (DEV && act) {
+  T Fvd[3][4];         // contravariant viscous flux of this node
+  if (act) {
+    // lift of the face fluxes (FP32-bulk: of their FP64 mass components)
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-      const int id = ii[d];
+      const int id = ii[d], ff = 6 * el + 2 * d;
       const int line = d == 0 ? tj + n * tk : (d == 1 ? ti + n * tk : ti + n * tj);
-      if (id == N) acc0d += sF0d[2 * d + 1][line] / sw[N];
-      if (id == 0) acc0d -= sF0d[2 * d][line] / sw[0];
+      if (id == N) {
+        if constexpr (DEV) {
+          acc0d += v.iwN * sF0[ff + 1][line];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 5; c++) acc[c] += iwN * sFa[ff + 1][c][line];
+        }
+      }
+      if (id == 0) {
+        if constexpr (DEV) {
+          acc0d -= v.iw0 * sF0[ff][line];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 5; c++) acc[c] -= iw0 * sFa[ff][c][line];
+        }
+      }
+    }
+    if (VISC) {
+      const T* const gp[4] = {sP[1], sP[2], sP[3], sT};
+      gradient_and_viscous_flux<n, T, CART>(t, ti, tj, tk, sD, iwN, iw0, gp, sJ + 6 * el, ja, ij, v, Fvd);
     }
   }
-  if (VISC) {
-    // BR1 gradient and contravariant viscous flux of this node, then sum_m Dhat_im F~v^d_m
-    T Fvd[3][4];
-    if (act) {
-      const T* const gp[4] = {sP[1], sP[2], sP[3], sT};
-      gradient_and_viscous_flux<n, T>(t, ti, tj, tk, sD, iwN, iw0, gp, sJ, ja, ij, (T)v.mu,
-                                      (T)v.kappa, Fvd);
+
+  // ---- volume, one direction at a time
+  const long o5 = base * 5 + tl;
+  double u_in[5], du_in[5];
+  const T ce = (T)(0.5 / (v.gamma - 1.0)), gm1 = (T)(v.gamma - 1.0);
+#pragma unroll
+  for (int d = 0; d < 3; d++) {
+    constexpr int strides[3] = {1, n, nf};
+    const int stride = strides[d], id = ii[d];
+    const int c0 = CART ? d : 0, c1 = CART ? (d + 1) % 3 : 1, c2 = CART ? (d + 2) % 3 : 2;  // rotated axes
+    T fa[4] = {0, 0, 0, 0}, fb[4] = {0, 0, 0, 0};  // SVA: this node's Fa^d, the neighbour's across a face
+    const bool onf = SVA && act && (id == 0 || id == N);
+    if (SVA && act) {
+#pragma unroll
+      for (int c = 0; c < 4; c++) fa[c] = (T)v.Fa[(base * 12) + (4 * d + c) * nn + tl];
     }
+    if (onf) {
+      const int side = id == N ? 1 : 0;
+      const int ne = side ? neighbour(e, 2 * d + 1) : neighbour(e, 2 * d);
+      const int inb = tl + (side ? -N : N) * stride;  // the matching node across the face
 #pragma unroll
-    for (int d = 0; d < 3; d++) {
-      T fa[4] = {0, 0, 0, 0}, fb[4] = {0, 0, 0, 0};  // SVA: this node's Fa^d, the neighbour's across a face
-      const int idd = ii[d];
-      const bool onf = SVA && act && (idd == 0 || idd == N);
-      if (SVA && act) {
+      for (int c = 0; c < 4; c++) fb[c] = (T)v.Fa[((long)ne * 12 + 4 * d + c) * nn + inb];
+    }
+    // the RK update's operands, requested before the last direction so that their latency hides
+    // behind it (earlier they would add 20 registers to those that the first directions hold)
+    if (d == 2 && act && mode != kModeResidual) {
 #pragma unroll
-        for (int c = 0; c < 4; c++) fa[c] = (T)v.Fa[(base * 12) + (4 * d + c) * nn + t];
+      for (int c = 0; c < 5; c++) {
+        u_in[c] = Uin[o5 + c * nn];
+        du_in[c] = rkA == 0.0 ? 0.0 : v.dU[o5 + c * nn];
       }
-      if (onf) {
-        const int side = idd == N ? 1 : 0;
-        const int ne = side ? (d == 0 ? nb1 : (d == 1 ? nb3 : nb5)) : (d == 0 ? nb0 : (d == 1 ? nb2 : nb4));
-        const int stride = d == 0 ? 1 : (d == 1 ? n : nf);
-        const int inb = t + (side ? -N : N) * stride;  // the matching node across the face
-#pragma unroll
-        for (int c = 0; c < 4; c++) fb[c] = (T)v.Fa[((long)ne * 12 + 4 * d + c) * nn + inb];
-      }
-      __syncthreads();  // previous users of the phase region are done
+    }
+    __syncthreads();  // previous users of the region are done
+    if constexpr (!CART || VISC) {
       if (act) {
+        if constexpr (!CART) {
 #pragma unroll
-        for (int c = 0; c < 4; c++) sFv[c][t] = SVA ? Fvd[d][c] + fa[c] : Fvd[d][c];
+          for (int c = 0; c < 3; c++) sM[c][t] = ja[3 * d + c];
+        }
+        if (VISC) {
+#pragma unroll
+          for (int c = 0; c < 4; c++) sFv[c][t] = SVA ? Fvd[d][c] + fa[c] : Fvd[d][c];
+        }
       }
       __syncthreads();
-      if (act) {
-        const int id = ii[d];
-        const int stride = d == 0 ? 1 : (d == 1 ? n : nf);
+    }
+    T pa[5] = {0, 0, 0, 0, 0};  // this direction's two-point sum (CART: along the unit normal, rotated)
+    double pa0 = 0.0;
+    // flux with the node at cyclic distance o; F rotated (CART)
+    auto pair = [&](int o, T F[5], double& F0d) {
+      int j = id + o;
+      j = j >= n ? j - n : j;
+      const int tb = t + (j - id) * stride;
+      Prim<T> P, Q;
+      P.rho = A.rho; P.beta = A.beta;
+      const T av[3] = {A.v1, A.v2, A.v3};
+      P.v1 = av[c0]; P.v2 = av[c1]; P.v3 = av[c2];
+      Q.rho = sP[0][tb]; Q.beta = sP[4][tb];
+      if constexpr (DEV) {
+        const double vb[3] = {sVd[c0][tb], sVd[c1][tb], sVd[c2][tb]};
+        const double vc[3] = {va[c0], va[c1], va[c2]};
+        Q.v1 = (T)vb[0]; Q.v2 = (T)vb[1]; Q.v3 = (T)vb[2];
+        double md[3] = {1.0, 0.0, 0.0};
+        if constexpr (!CART) {
+#pragma unroll
+          for (int c = 0; c < 3; c++) md[c] = ja[3 * d + c] + sM[c][tb];
+        }
+        if (v.vol == 0) {
+          const double vn64 = 0.5 * dotn<CART>(vc[0] + vb[0], vc[1] + vb[1], vc[2] + vb[2], md[0], md[1], md[2]);
+          flux_ec_dev<CART>(P, Q, (T)md[0], (T)md[1], (T)md[2], vn64, Rf, F, F0d);
+        } else {
+          flux_central_dev<CART>(P, Q, (T)md[0], (T)md[1], (T)md[2], vc, vb, md, Rf, F, F0d);
+        }
+      } else {
+        Q.v1 = sP[1 + c0][tb]; Q.v2 = sP[1 + c1][tb]; Q.v3 = sP[1 + c2][tb];
+        T m1 = 1, m2 = 0, m3 = 0;
+        if constexpr (!CART) {
+          m1 = ja[3 * d] + sM[0][tb];
+          m2 = ja[3 * d + 1] + sM[1][tb];
+          m3 = ja[3 * d + 2] + sM[2][tb];
+        }
+        vol_flux<(FX & 1) != 0, CART>(v.vol, P, Q, m1, m2, m3, ce, gm1, F);
+      }
+      const double Dd = sD[id * n + j];
+      if constexpr (DEV) {
+        pa0 += Dd * F0d;
+      } else {
+        pa[0] += Dd * F[0];
+      }
+#pragma unroll
+      for (int c = 1; c < 5; c++) pa[c] += (T)Dd * F[c];
+    };
+    if (act) {
+#pragma unroll
+      for (int o = 1; o <= K; o++) {
+        T F[5];
+        double F0d;
+        pair(o, F, F0d);
+        if constexpr (DEV) {
+          sX0[o - 1][t] = F0d;
+#pragma unroll
+          for (int c = 1; c < 5; c++) sX[o - 1][c - 1][t] = F[c];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 5; c++) sX[o - 1][c][t] = F[c];
+        }
+      }
+      if constexpr (HALF) {
+        T F[5];
+        double F0d;
+        pair(n / 2, F, F0d);
+      }
+      if (VISC) {  // sum_m Dhat_im F~v^d_m
         const int b0 = t - id * stride;
 #pragma unroll
         for (int m = 0; m < n; m++) {
@@ -281,86 +455,61 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
         }
       }
     }
-  }
-
-  // The RK update's operands, loaded before the pair phase so that their latency hides behind it
-  const long o = base * 5 + t;
-  double u_in[5], du_in[5];
-  if (act && mode != kModeResidual) {
+    if constexpr (K > 0) {
+      __syncthreads();
+      if (act) {
 #pragma unroll
-    for (int c = 0; c < 5; c++) {
-      u_in[c] = Uin[o + c * nn];
-      du_in[c] = rkA == 0.0 ? 0.0 : v.dU[o + c * nn];
-    }
-  }
-
-  // ---- volume: split-form sums; each pair of a line is evaluated once and used by both nodes
-  const T ce = (T)(0.5 / (v.gamma - 1.0)), gm1 = (T)(v.gamma - 1.0);
-  for (int d = 0; d < 3; d++) {
-    const int stride = d == 0 ? 1 : (d == 1 ? n : nf);
-    __syncthreads();  // previous users of sJa3 / the phase region are done
-    if (act) {
+        for (int o = 1; o <= K; o++) {
+          int i = id - o;
+          i = i < 0 ? i + n : i;
+          const int tb = t + (i - id) * stride;
+          const double Dd = sD[id * n + i];
+          if constexpr (DEV) {
+            pa0 += Dd * sX0[o - 1][tb];
 #pragma unroll
-      for (int c = 0; c < 3; c++) sJa3[c][t] = ja[3 * d + c];
-    }
-    __syncthreads();
-    for (int s = t; s < P; s += NT) {
-      const int line = s / np, k = s - line * np;
-      const int b0 = d == 0 ? n * line : (d == 1 ? line % n + nf * (line / n) : line);
-      const int na = b0 + sPa[k] * stride, nb = b0 + sPb[k] * stride;
-      Prim<T> A, B;
-      A.rho = sP[0][na]; A.v1 = sP[1][na]; A.v2 = sP[2][na]; A.v3 = sP[3][na];
-      A.beta = sP[4][na]; A.lrho = sP[5][na]; A.lbeta = sP[6][na];
-      A.h = (T)0.5 * (A.v1 * A.v1 + A.v2 * A.v2 + A.v3 * A.v3);
-      B.rho = sP[0][nb]; B.v1 = sP[1][nb]; B.v2 = sP[2][nb]; B.v3 = sP[3][nb];
-      B.beta = sP[4][nb]; B.lrho = sP[5][nb]; B.lbeta = sP[6][nb];
-      B.h = (T)0.5 * (B.v1 * B.v1 + B.v2 * B.v2 + B.v3 * B.v3);
-      T F[5];
-      const double md[3] = {sJa3[0][na] + sJa3[0][nb], sJa3[1][na] + sJa3[1][nb],
-                            sJa3[2][na] + sJa3[2][nb]};
-      const T m1 = (T)md[0], m2 = (T)md[1], m3 = (T)md[2];
-      if (DEV) {
-        const double va[3] = {sVd[0][na], sVd[1][na], sVd[2][na]};
-        const double vb[3] = {sVd[0][nb], sVd[1][nb], sVd[2][nb]};
-        double F0d;
-        if (v.vol == 0) {
-          const double vn64 = 0.5 * ((va[0] + vb[0]) * md[0] + (va[1] + vb[1]) * md[1] + (va[2] + vb[2]) * md[2]);
-          flux_ec_dev(A, B, m1, m2, m3, vn64, Rf, F, F0d);
-        } else {
-          flux_central_dev(A, B, m1, m2, m3, va, vb, md, Rf, F, F0d);
+            for (int c = 1; c < 5; c++) pa[c] += (T)Dd * sX[o - 1][c - 1][tb];
+          } else {
+#pragma unroll
+            for (int c = 0; c < 5; c++) pa[c] += Dd * sX[o - 1][c][tb];
+          }
         }
-        sM[s] = F0d;
-      } else {
-        vol_flux<T, (FX & 1) != 0>(v.vol, A, B, m1, m2, m3, ce, gm1, F);
       }
-#pragma unroll
-      for (int c = 0; c < 5; c++) sPair[c][s] = F[c];
     }
-    __syncthreads();
     if (act) {
-      const int id = ii[d];
-      const int line = d == 0 ? tj + n * tk : (d == 1 ? ti + n * tk : ti + n * tj);
+      // CART: times twice the constant Ja^d (the pair sums of the general form hold Ja_i + Ja_m)
+      const double s64 = CART ? 2.0 * v.cja[d] : 1.0;
+      const T sc = (T)s64;
+      if constexpr (DEV) {
+        acc0d += s64 * pa0;
+        const int ff = 6 * el + 2 * d;
+        const int line = d == 0 ? tj + n * tk : (d == 1 ? ti + n * tk : ti + n * tj);
+        T q[5] = {0, pa[1], pa[2], pa[3], pa[4]};
+        if constexpr (CART) {
+          q[1 + c0] = sc * pa[1];
+          q[1 + c1] = sc * pa[2];
+          q[1 + c2] = sc * pa[3];
+          q[4] = sc * pa[4];
+        }
+        if (id == N) {
 #pragma unroll
-      for (int m = 0; m < n; m++) {
-        if (m == id) continue;
-        const int a = m < id ? m : id, b = m < id ? id : m;
-        const int k = line * np + a * (2 * n - a - 1) / 2 + (b - a - 1);
-        const T Dm = (T)sD[id * n + m];
+          for (int c = 1; c < 5; c++) q[c] += iwN * sFk[ff + 1][c][line];
+        }
+        if (id == 0) {
 #pragma unroll
-        for (int c = 0; c < 5; c++) acc[c] += Dm * sPair[c][k];
-        if (DEV) acc0d += sD[id * n + m] * sM[k];
-      }
-      if (id == N) {
+          for (int c = 1; c < 5; c++) q[c] -= iw0 * sFk[ff][c][line];
+        }
 #pragma unroll
-        for (int c = 0; c < 5; c++) acc[c] += iwN * sF[2 * d + 1][c][line];
-      }
-      if (id == 0) {
-#pragma unroll
-        for (int c = 0; c < 5; c++) acc[c] -= iw0 * sF[2 * d][c][line];
+        for (int c = 1; c < 5; c++) acc[c] += q[c];
+      } else {
+        acc[0] += CART ? sc * pa[0] : pa[0];
+        acc[1 + c0] += CART ? sc * pa[1] : pa[1];
+        acc[1 + c1] += CART ? sc * pa[2] : pa[2];
+        acc[1 + c2] += CART ? sc * pa[3] : pa[3];
+        acc[4] += CART ? sc * pa[4] : pa[4];
       }
     }
   }
-  if (!act) return;
+  if (!put) return;
   double R[5];
 #pragma unroll
   for (int c = 0; c < 5; c++) R[c] = -(double)acc[c] * ij;
@@ -370,7 +519,7 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
   }
   if (mode == kModeResidual) {
 #pragma unroll
-    for (int c = 0; c < 5; c++) v.R[o + c * nn] = R[c];
+    for (int c = 0; c < 5; c++) v.R[o5 + c * nn] = R[c];
     return;
   }
   double* __restrict__ Uout = v.U[cur ^ 1];
@@ -378,56 +527,76 @@ __device__ __forceinline__ void stage_body(const View& v, const int e, const int
 #pragma unroll
   for (int c = 0; c < 5; c++) {
     const double du = (rkA == 0.0 ? 0.0 : rkA * du_in[c]) + h * R[c];
-    v.dU[o + c * nn] = du;
-    Uout[o + c * nn] = u_in[c] + rkB * du;
+    v.dU[o5 + c * nn] = du;
+    Uout[o5 + c * nn] = u_in[c] + rkB * du;
   }
 }
 
 // FX: the flux family (see flux_family); each family is compiled as separate kernels
-template <int N, typename T, bool VISC, int FX, bool SVA = false>
-__global__ void __launch_bounds__(nthreads_for(N))
+template <int N, typename T, bool VISC, int FX, bool SVA, bool CART>
+__global__ void __launch_bounds__(wg_lanes(N))
     __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4))))
     stage_kernel(View v, int cur, double dt, double rkA, double rkB, int mode) {
-  stage_body<N, T, VISC, FX, SVA>(v, block_element(v.E), cur, dt, rkA, rkB, mode);
+  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
+  stage_body<N, T, VISC, FX, SVA, CART>(lds, v, block_element(wg_count(N, v.E)), cur, dt, rkA, rkB, mode);
 }
 
-template <int N, typename T, bool VISC, int FX>
-__global__ void __launch_bounds__(nthreads_for(N))
+// CART: every member is a plain box; otherwise each member takes the form of its own box
+template <int N, typename T, bool VISC, int FX, bool CART>
+__global__ void __launch_bounds__(wg_lanes(N))
     __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
-  int m, e;
-  batch_member(B, m, e);
-  stage_body<N, T, VISC, FX>(*B.view[m], e, B.cur[m], B.dt[m], rkA, rkB, mode);
+  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
+  static_assert(StageLds<N, T, VISC, true>::bytes <= StageLds<N, T, VISC, CART>::bytes, "one LDS buffer for both");
+  int m, w;
+  batch_member(B, m, w);
+  const View& v = *B.view[m];
+  if (CART || !v.deform)
+    stage_body<N, T, VISC, FX, false, true>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+  else
+    stage_body<N, T, VISC, FX, false, CART>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
 }
 
 // ------------------------------------------------------------------ launch helpers
-template <int N, typename T, int FX>
-inline hipError_t stage_ntx(const View& v, int cur, double dt, double a, double b, int mode,
-                            hipStream_t st) {
-  const dim3 grid(v.E), block(nthreads_for(N));
+template <int N, typename T, int FX, bool CART>
+inline hipError_t stage_ntxc(const View& v, int cur, double dt, double a, double b, int mode,
+                             hipStream_t st) {
+  const dim3 grid(wg_count(N, v.E)), block(wg_lanes(N));
   if constexpr (FX == 0) {
     if (v.viscous && v.Fa) {
-      hipLaunchKernelGGL((stage_kernel<N, T, true, 0, true>), grid, block, 0, st, v, cur, dt, a, b, mode);
+      hipLaunchKernelGGL((stage_kernel<N, T, true, 0, true, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
       return hipGetLastError();
     }
   }
   if (v.Fa) return hipErrorInvalidValue;  // the folded SVV term: Navier-Stokes, standard fluxes
   if (v.viscous)
-    hipLaunchKernelGGL((stage_kernel<N, T, true, FX>), grid, block, 0, st, v, cur, dt, a, b, mode);
+    hipLaunchKernelGGL((stage_kernel<N, T, true, FX, false, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
   else
-    hipLaunchKernelGGL((stage_kernel<N, T, false, FX>), grid, block, 0, st, v, cur, dt, a, b, mode);
+    hipLaunchKernelGGL((stage_kernel<N, T, false, FX, false, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
   return hipGetLastError();
 }
 
 template <int N, typename T, int FX>
-inline hipError_t stage_batch_nt(const BatchArgs& B, bool visc, double a, double b, int mode,
-                                 hipStream_t st) {
-  const dim3 grid(B.start[B.n]), block(nthreads_for(N));
+inline hipError_t stage_ntx(const View& v, int cur, double dt, double a, double b, int mode, hipStream_t st) {
+  return v.deform ? stage_ntxc<N, T, FX, false>(v, cur, dt, a, b, mode, st)
+                  : stage_ntxc<N, T, FX, true>(v, cur, dt, a, b, mode, st);
+}
+
+template <int N, typename T, int FX, bool CART>
+inline hipError_t stage_batch_ntc(const BatchArgs& B, bool visc, double a, double b, int mode, hipStream_t st) {
+  const dim3 grid(B.start[B.n]), block(wg_lanes(N));
   if (visc)
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX>), grid, block, 0, st, B, a, b, mode);
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX, CART>), grid, block, 0, st, B, a, b, mode);
   else
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX>), grid, block, 0, st, B, a, b, mode);
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX, CART>), grid, block, 0, st, B, a, b, mode);
   return hipGetLastError();
+}
+
+template <int N, typename T, int FX>
+inline hipError_t stage_batch_nt(const BatchArgs& B, bool visc, bool deform, double a, double b, int mode,
+                                 hipStream_t st) {
+  return deform ? stage_batch_ntc<N, T, FX, false>(B, visc, a, b, mode, st)
+                : stage_batch_ntc<N, T, FX, true>(B, visc, a, b, mode, st);
 }
 
 }  // namespace dg
