@@ -581,7 +581,7 @@ __device__ __forceinline__ Prim<T> make_prim_dev(const double u[5], double gamma
 // u = ((xa - xb)/(2 + xa + xb))^2 and S(u) = 1 + s as above, lam = ((xa + xb)/2 - s)/(1 + s).
 // u < 1e-2 takes four terms (truncated at u^4/9 = 1e-9), beyond it S in FP64.
 __device__ __forceinline__ float logmean_dev(float xa, float xb) {
-  const float d = xa - xb, w = 2.0f + xa + xb;
+  const float d = xa - xb, w = 2.0f + (xa + xb);  // (the same for (b, a): pairs may be evaluated twice)
   const float u = d * d * rcp(w * w);
   float pm1 = u * ((float)(1.0 / 3.0) + u * (0.2f + u * (float)(1.0 / 7.0)));
   if (__any(u >= 1e-2f) && u >= 1e-2f) pm1 = (float)(atanh_ratio(1.0 + xa, 1.0 + xb, u) - 1.0);
