@@ -965,6 +965,65 @@ __device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cu
   for (int c = 0; c < 4; c++) Ff[c] = sFb[fo + f][c][q] + (s1 * Fp[0][c] + s2 * Fp[1][c] + s3 * Fp[2][c]);
 }
 
+// ------------------------------------------------------------------ diagnostics (FP64)
+// slots: 0-4 integral of U, 5 integral of -rho s, 6 integral of -rho s/(gamma-1), 7 integral of
+// rho|v|^2/2, 8 integral of rho|curl v|^2/2, 9 max(|v|+c), 10 min rho, 11 min p,
+// 12 number of non-finite values, 13 volume, 14 integral of p
+constexpr int kDiagUsed = 15;
+
+__device__ __forceinline__ double diag_combine(int k, double a, double b) {
+  return k == 9 ? fmax(a, b) : ((k == 10 || k == 11) ? fmin(a, b) : a + b);
+}
+__device__ __forceinline__ double diag_identity(int k) {
+  return k == 9 ? -INFINITY : ((k == 10 || k == 11) ? INFINITY : 0.0);
+}
+
+// adds one node (state u, quadrature weight times J wq, vorticity o) to the lane's slots
+__device__ __forceinline__ void diag_add(double s[kDiagUsed], const double u[5], double gamma, double wq, double o1,
+                                         double o2, double o3) {
+  const double rho = u[0];
+  double p;
+  const double lam = wave_speed(u, gamma, p);
+  const double v1 = u[1] / rho, v2 = u[2] / rho, v3 = u[3] / rho;
+  int bad = 0;
+#pragma unroll
+  for (int c = 0; c < 5; c++) {
+    s[c] += wq * u[c];
+    bad += isfinite(u[c]) ? 0 : 1;
+  }
+  const double e = wq * (-rho * (log(p) - gamma * log(rho)));
+  s[5] += e;
+  s[6] += e / (gamma - 1);
+  s[7] += wq * 0.5 * rho * (v1 * v1 + v2 * v2 + v3 * v3);
+  s[8] += wq * 0.5 * rho * (o1 * o1 + o2 * o2 + o3 * o3);
+  s[9] = fmax(s[9], lam);
+  s[10] = fmin(s[10], rho);
+  s[11] = fmin(s[11], p);
+  s[12] += (double)bad;
+  s[13] += wq;
+  s[14] += wq * p;
+}
+
+// the workgroup's slots into part[k * parts + b], in a fixed order (lanes of a wave, then the waves)
+template <int NW>
+__device__ __forceinline__ void diag_store(const double s[kDiagUsed], double* part, int parts, int b) {
+  __shared__ double red[NW][kDiagUsed];
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kDiagUsed; k++) {
+    double a = s[k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a = diag_combine(k, a, __shfl_xor(a, o));
+    if ((t & 63) == 0) red[t >> 6][k] = a;
+  }
+  __syncthreads();
+  if (t < kDiagUsed) {
+    double a = red[0][t];
+    for (int w = 1; w < NW; w++) a = diag_combine(t, a, red[w][t]);
+    part[(long)t * parts + b] = a;
+  }
+}
+
 // ------------------------------------------------------------------ initial conditions
 struct IcParams {
   double p[9];

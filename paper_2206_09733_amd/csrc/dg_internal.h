@@ -11,6 +11,7 @@ namespace dg {
 
 constexpr int kMaxOrder = 7;            // largest polynomial order with a compiled kernel
 constexpr int kDiagSlots = 16;          // doubles per diagnostics partial
+constexpr int kDiagBlocks = 2048;       // diagnostics partials at most (8 workgroups per CU)
 constexpr int kTabStride = (kMaxOrder + 1) * (kMaxOrder + 1);
 
 // Flux family of the stage kernels, compiled apart so that each kernel holds only the flux code
@@ -66,7 +67,7 @@ struct View {
   double* dU;     // RK register [E][5][nn]
   double* R;      // residual [E][5][nn]
   double* Fvf;    // [E][6][4][nf] contravariant viscous flux on the element's faces
-  double* part;   // diagnostics partials [E][kDiagSlots]
+  double* part;   // diagnostics partials [kDiagSlots][workgroups], at most one per element
   double* diag;   // final diagnostics [kDiagSlots]
   // adaptive step size: while dtp is set the stage kernels take the step size from *dtp (written
   // on the device by dt_kernel) instead of their dt argument; adapt[0] the step size,
@@ -136,7 +137,7 @@ hipError_t launch_gradient(const View& v, int cur, hipStream_t st);
 hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rkB, int mode,
                         hipStream_t st);
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st);
-hipError_t launch_diag_final(const View& v, hipStream_t st);  // partials -> diag, fixed order
+hipError_t launch_diag_final(const View& v, int parts, hipStream_t st);  // partials -> diag, fixed order
 // batched Navier-Stokes gradient pass and stage of members of order N (all viscous, or all
 // inviscid for the stage), FP32-bulk or FP64; deform: some member lies on a deformed box
 hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, bool deform,

@@ -613,60 +613,45 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
 }
 
 // ------------------------------------------------------------------ diagnostics (FP64)
-// same slots as the uniform-order diagnostics
-__global__ void __launch_bounds__(512) diag_mixed_kernel(View v, int cur) {
-  const int e = blockIdx.x;
-  const ElemInfo I = elem_info(v, e);
+// as the uniform-order kernel: a grid of at most kDiagBlocks workgroups walks over the elements,
+// every lane adding its nodes to its own slots
+constexpr int kMixDiagLanes = (kMixNN + 63) / 64 * 64;
+__global__ void __launch_bounds__(kMixDiagLanes) diag_mixed_kernel(View v, int cur, int parts) {
   const int t = threadIdx.x;
-  const bool act = t < I.nn;
-  const long off = I.off, nn = I.nn;
-  const int ii[3] = {t % I.n[0], (t / I.n[0]) % I.n[1], t / (I.n[0] * I.n[1])};
-  __shared__ double sD[3][kMixNF], sw[3][kMixN];
-  __shared__ double sV[3][512];
-  __shared__ double red[512];
-  for (int d = 0; d < 3; d++) {
-    const int n = I.n[d];
-    for (int x = t; x < n * n; x += blockDim.x) sD[d][x] = tab_D(v, n)[x];
-    if (t < n) sw[d][t] = tab_w(v, n)[t];
-  }
-  double u[5] = {0, 0, 0, 0, 0};
-  if (act) {
-    for (int c = 0; c < 5; c++) u[c] = v.U[cur][off * 5 + c * nn + t];
-    for (int c = 0; c < 3; c++) sV[c][t] = u[1 + c] / u[0];
-  }
-  __syncthreads();
-  double s[kDiagSlots];
-  for (int k = 0; k < kDiagSlots; k++) s[k] = 0.0;
-  s[9] = -INFINITY;
-  s[10] = INFINITY;
-  s[11] = INFINITY;
-  if (act) {
-    const double g = v.gamma;
-    const double wq = sw[0][ii[0]] * sw[1][ii[1]] * sw[2][ii[2]] * v.J[off + t];
-    const double ij = v.invJ[off + t];
-    const double rho = u[0];
-    const double v1 = sV[0][t], v2 = sV[1][t], v3 = sV[2][t];
-    const double q2 = v1 * v1 + v2 * v2 + v3 * v3;
-    const double p = (g - 1) * (u[4] - 0.5 * rho * q2);
-    int bad = 0;
-    for (int c = 0; c < 5; c++) {
-      s[c] = wq * u[c];
-      bad += isfinite(u[c]) ? 0 : 1;
+  __shared__ double sD[2][3][kMixNF], sw[2][3][kMixN];
+  __shared__ double sV[2][3][kMixNN];
+  double s[kDiagUsed];
+#pragma unroll
+  for (int k = 0; k < kDiagUsed; k++) s[k] = diag_identity(k);
+  int buf = 0;
+  for (int e = blockIdx.x; e < v.E; e += gridDim.x, buf ^= 1) {
+    const ElemInfo I = elem_info(v, e);
+    const bool act = t < I.nn;
+    const long off = I.off, nn = I.nn;
+    const int ii[3] = {t % I.n[0], (t / I.n[0]) % I.n[1], t / (I.n[0] * I.n[1])};
+    for (int d = 0; d < 3; d++) {
+      const int n = I.n[d];
+      if (t < n * n) sD[buf][d][t] = tab_D(v, n)[t];
+      if (t < n) sw[buf][d][t] = tab_w(v, n)[t];
     }
-    const double sp = log(p) - g * log(rho);
-    s[5] = wq * (-rho * sp);
-    s[6] = s[5] / (g - 1);
-    s[7] = wq * 0.5 * rho * q2;
+    double u[5] = {0, 0, 0, 0, 0};
+    if (act) {
+      for (int c = 0; c < 5; c++) u[c] = v.U[cur][off * 5 + c * nn + t];
+      for (int c = 0; c < 3; c++) sV[buf][c][t] = u[1 + c] / u[0];
+    }
+    __syncthreads();
+    if (!act) continue;
+    const double wq = sw[buf][0][ii[0]] * sw[buf][1][ii[1]] * sw[buf][2][ii[2]] * v.J[off + t];
+    const double ij = v.invJ[off + t];
     double dv[3][3];
     for (int d = 0; d < 3; d++) {
       const int n = I.n[d];
       const int stride = d == 0 ? 1 : (d == 1 ? I.n[0] : I.n[0] * I.n[1]);
       const int b0 = t - ii[d] * stride;
-      for (int c = 0; c < 3; c++) {
-        double a = 0.0;
-        for (int m = 0; m < n; m++) a += sD[d][ii[d] * n + m] * sV[c][b0 + m * stride];
-        dv[d][c] = a;
-      }
+      double a[3] = {0.0, 0.0, 0.0};
+      for (int m = 0; m < n; m++)
+        for (int c = 0; c < 3; c++) a[c] += sD[buf][d][ii[d] * n + m] * sV[buf][c][b0 + m * stride];
+      for (int c = 0; c < 3; c++) dv[d][c] = a[c];
     }
     double gv[3][3];
     for (int c = 0; c < 3; c++)
@@ -675,29 +660,9 @@ __global__ void __launch_bounds__(512) diag_mixed_kernel(View v, int cur) {
         for (int d = 0; d < 3; d++) a += v.Ja[off * 9 + (3 * d + x) * nn + t] * dv[d][c];
         gv[c][x] = a * ij;
       }
-    const double o1 = gv[2][1] - gv[1][2], o2 = gv[0][2] - gv[2][0], o3 = gv[1][0] - gv[0][1];
-    s[8] = wq * 0.5 * rho * (o1 * o1 + o2 * o2 + o3 * o3);
-    double pw;
-    s[9] = wave_speed(u, g, pw);
-    s[10] = rho;
-    s[11] = p;
-    s[12] = (double)bad;
-    s[13] = wq;
-    s[14] = wq * p;
+    diag_add(s, u, v.gamma, wq, gv[2][1] - gv[1][2], gv[0][2] - gv[2][0], gv[1][0] - gv[0][1]);
   }
-  for (int k = 0; k < 15; k++) {
-    red[t] = s[k];
-    __syncthreads();
-    for (int w = 256; w > 0; w >>= 1) {
-      if (t < w) {
-        const double a = red[t], b = red[t + w];
-        red[t] = k == 9 ? fmax(a, b) : ((k == 10 || k == 11) ? fmin(a, b) : a + b);
-      }
-      __syncthreads();
-    }
-    if (t == 0) v.part[(long)e * kDiagSlots + k] = red[0];
-    __syncthreads();
-  }
+  diag_store<kMixDiagLanes / 64>(s, v.part, parts, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -795,10 +760,11 @@ hipError_t launch_stage_mixed(const View& v, int cur, double dt, double rkA, dou
 }
 
 hipError_t launch_diagnostics_mixed(const View& v, int cur, hipStream_t st) {
-  hipLaunchKernelGGL(diag_mixed_kernel, dim3(v.E), dim3(512), 0, st, v, cur);
+  const int parts = v.E < kDiagBlocks ? v.E : kDiagBlocks;
+  hipLaunchKernelGGL(diag_mixed_kernel, dim3(parts), dim3(kMixDiagLanes), 0, st, v, cur, parts);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  return launch_diag_final(v, st);
+  return launch_diag_final(v, parts, st);
 }
 
 }  // namespace dg
