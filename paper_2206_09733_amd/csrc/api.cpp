@@ -166,7 +166,7 @@ Plan make_plan(const dg_solver* s) {
     for (int N = 1; N <= dg::kMaxOrder; N++)
       for (int M = N + 1; M <= dg::kMaxOrder; M++) p.mtab_n += 2 * (N + 1) * (M + 1);
   } else {
-    p.tab_n = dg::tab_size((int)n) + (s->mesh.gauss ? dg::tab_gauss_geo_size((int)n) : 0);
+    p.tab_n = s->mesh.gauss ? dg::tab_gauss_size((int)n) : dg::tab_size((int)n);
   }
   p.tab = take(sizeof(double) * p.tab_n);
   p.nbr = take(sizeof(int) * 6 * E);
@@ -763,6 +763,11 @@ int dg_solver_bind(dg_solver* s, void* dev_ptr, size_t bytes, void* hip_stream) 
       dg::gl_tables(N, t + dg::tab_xi(n), t + dg::tab_w(n), t + dg::tab_D(n), t + dg::tab_Dh(n));
       double* g = t + dg::tab_size(n);
       dg::lobatto_to_gauss(N, g, g + n, g + n + n * n);
+      const double *w = t + dg::tab_w(n), *Dg = t + dg::tab_D(n), *ends = t + dg::tab_Dh(n);
+      for (int i = 0; i < n; i++) {
+        for (int m = 0; m < n; m++) t[dg::tab_gauss_Dw(n) + i * n + m] = -Dg[m * n + i] * w[m] / w[i];
+        for (int e = 0; e < 2; e++) t[dg::tab_gauss_lift(n) + e * n + i] = ends[e * n + i] / w[i];
+      }
     }
     else
       dg::gll_tables(N, t + dg::tab_xi(n), t + dg::tab_w(n), t + dg::tab_D(n), t + dg::tab_Dh(n));

@@ -33,8 +33,13 @@ inline int tab_size(int n) { return 2 * n + 2 * n * n; }
 // Gauss-Legendre meshes (whose geometry is the Lobatto grid's, evaluated at the Gauss points)
 // append the Lobatto nodes [g, g+n), the Lobatto derivative matrix [g+n, g+n+n^2) and the
 // interpolation matrix from the Lobatto to the Gauss points [g+n+n^2, g+n+2n^2), I[q*n+l] the
-// Lobatto basis function l at Gauss point q, g = tab_size(n)
+// Lobatto basis function l at Gauss point q, g = tab_size(n); then, formed from the tables above,
+// the weak derivative matrix Dw_im = -D_mi w_m / w_i [g + n + 2n^2, + n^2) and the lift factors
+// l_i(-1)/w_i, l_i(+1)/w_i (2 n)
 inline int tab_gauss_geo_size(int n) { return n + 2 * n * n; }
+__host__ __device__ constexpr int tab_gauss_Dw(int n) { return 2 * n + 2 * n * n + n + 2 * n * n; }
+__host__ __device__ constexpr int tab_gauss_lift(int n) { return tab_gauss_Dw(n) + n * n; }
+__host__ __device__ constexpr int tab_gauss_size(int n) { return tab_gauss_lift(n) + 2 * n; }
 
 // Everything a kernel needs to know about one bound uniform-order solver.
 struct View {
