@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -113,14 +114,12 @@ struct dg_solver {
   int mix_tiles = 0;                 // mixed-order stage: bit b = two nodes per lane in bucket b
   bool mix_concurrent = false;       // mixed-order stage: buckets on the side streams of `mix`
   dg::MixStreams mix{};
-  // RK-step graphs: graph[p] advances one step starting from state buffer p with step graph_dt[p]
+  // RK-step graphs: graph[k][p] advances 1 << k steps (k = 0..3; more steps per launch for small
+  // solves) starting from state buffer p with step graph_dt[k][p]
   bool use_graphs = true;
   hipStream_t cap_stream = nullptr;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
-  double graph_dt[2] = {0.0, 0.0};
-  // kMultiSteps steps in one graph (fewer graph launches for small solves), same keys as graph[]
-  hipGraphExec_t mgraph[2] = {nullptr, nullptr};
-  double mgraph_dt[2] = {0.0, 0.0};
+  hipGraphExec_t graph[4][2] = {};
+  double graph_dt[4][2] = {};
   double last_dt = 0.0;
   // adaptive-step graphs: agraph[p] advances one step from buffer p with the step size chosen on
   // the device for CFL number agraph_cfl[p]
@@ -405,15 +404,18 @@ const RkScheme kRk[2] = {
 
 // (waits for the solver's stream first, so that no replay of a graph is still in flight)
 void drop_graphs(dg_solver* s) {
-  if (!s->graph[0] && !s->graph[1] && !s->agraph[0] && !s->agraph[1] && !s->mgraph[0] && !s->mgraph[1]) return;
+  hipGraphExec_t* all[10];
+  int n = 0;
+  for (auto& g : s->graph)
+    for (hipGraphExec_t& e : g) all[n++] = &e;
+  for (hipGraphExec_t& e : s->agraph) all[n++] = &e;
+  bool any = false;
+  for (hipGraphExec_t* e : all) any = any || *e;
+  if (!any) return;
   (void)hipStreamSynchronize(s->stream);
-  for (int k = 0; k < 2; k++) {
-    if (s->graph[k]) (void)hipGraphExecDestroy(s->graph[k]);
-    if (s->agraph[k]) (void)hipGraphExecDestroy(s->agraph[k]);
-    if (s->mgraph[k]) (void)hipGraphExecDestroy(s->mgraph[k]);
-    s->graph[k] = nullptr;
-    s->agraph[k] = nullptr;
-    s->mgraph[k] = nullptr;
+  for (hipGraphExec_t* e : all) {
+    if (*e) (void)hipGraphExecDestroy(*e);
+    *e = nullptr;
   }
 }
 
@@ -500,24 +502,25 @@ int capture_into(dg_solver* s, hipGraphExec_t* slot, F record) {
   return DG_OK;
 }
 
-int capture_step(dg_solver* s, double dt) {
+// 1 << lg consecutive steps in one graph
+int capture_steps(dg_solver* s, double dt, int lg) {
   const int parity = s->cur;
-  const int rc = capture_into(s, &s->graph[parity], [&] { return run_step(s, dt); });
-  if (rc == DG_OK) s->graph_dt[parity] = dt;
+  const int rc = capture_into(s, &s->graph[lg][parity], [&] {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 1 << lg && e == hipSuccess; k++) e = run_step(s, dt);
+    return e;
+  });
+  if (rc == DG_OK) s->graph_dt[lg][parity] = dt;
   return rc;
 }
 
-// kMultiSteps consecutive steps in one graph
-constexpr int kMultiSteps = 8;
-int capture_multi_step(dg_solver* s, double dt) {
-  const int parity = s->cur;
-  const int rc = capture_into(s, &s->mgraph[parity], [&] {
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < kMultiSteps && e == hipSuccess; k++) e = run_step(s, dt);
-    return e;
-  });
-  if (rc == DG_OK) s->mgraph_dt[parity] = dt;
-  return rc;
+// The graphs of a call of nsteps steps: eight steps each while that many remain, then the rest in
+// powers of two (few graph launches, and few different graphs whatever numbers of steps recur).
+std::vector<int> graph_chunks(int nsteps) {
+  std::vector<int> c(nsteps / 8, 8);
+  for (int k = 4; k >= 1; k /= 2)
+    if (nsteps % 8 & k) c.push_back(k);
+  return c;
 }
 
 // the launches of one adaptive step: step size, then the stages (s->v.dtp is set by the caller)
@@ -1022,31 +1025,19 @@ int dg_rk_step(dg_solver* s, double dt, int nsteps) try {
   // as the previous call); a step size seen once runs eagerly
   const bool replay = s->use_graphs && !s->profiling && nsteps > 0 && (nsteps > 1 || dt == s->last_dt);
   s->last_dt = dt;
-  // every stage moves the state to the other buffer
-  const int flips = kRk[s->scheme].stages & 1;
-  for (int it = 0; it < nsteps;) {
-    if (replay && nsteps - it >= kMultiSteps) {  // kMultiSteps steps per graph launch
-      const int par = s->cur;
-      if (!s->mgraph[par] || s->mgraph_dt[par] != dt) {
-        rc = capture_multi_step(s, dt);
-        if (rc) return rc;
-      }
-      DG_HIP(hipGraphLaunch(s->mgraph[par], s->stream), "RK multi-step graph launch");
-      s->cur ^= (kMultiSteps * flips) & 1;
-      it += kMultiSteps;
-    } else if (replay) {
-      const int par = s->cur;
-      if (!s->graph[par] || s->graph_dt[par] != dt) {
-        rc = capture_step(s, dt);
-        if (rc) return rc;
-      }
-      DG_HIP(hipGraphLaunch(s->graph[par], s->stream), "RK-step graph launch");
-      s->cur ^= flips;
-      it++;
-    } else {
-      DG_HIP(run_step(s, dt), "RK stage kernels");
-      it++;
+  if (!replay) {
+    for (int it = 0; it < nsteps; it++) DG_HIP(run_step(s, dt), "RK stage kernels");
+    return DG_OK;
+  }
+  for (int steps : graph_chunks(nsteps)) {
+    const int lg = steps == 8 ? 3 : (steps == 4 ? 2 : steps - 1);
+    const int par = s->cur;
+    if (!s->graph[lg][par] || s->graph_dt[lg][par] != dt) {
+      rc = capture_steps(s, dt, lg);
+      if (rc) return rc;
     }
+    DG_HIP(hipGraphLaunch(s->graph[lg][par], s->stream), "RK-step graph launch");
+    s->cur ^= (steps * kRk[s->scheme].stages) & 1;  // every stage moves the state to the other buffer
   }
   return DG_OK;
 } catch (...) {
@@ -1338,12 +1329,19 @@ struct dg_batch {
   struct Graph {
     std::vector<int> par;       // state buffer of every member at the step start
     std::vector<double> dts;
-    int steps;                  // RK steps in the graph: 1 or kMultiSteps
-    hipGraphExec_t exec;
+    int steps;                  // RK steps in the graph: 1, 2, 4 or 8
+    std::vector<hipGraphExec_t> exec;  // one linear graph per lane
   };
   std::vector<dg_solver*> m;
   std::vector<Group> groups;    // each with at most kMaxBatch members
   std::vector<int> solo;        // mixed-order and Gauss-Legendre members: launches of their own
+  // The groups and solo members are independent of each other, so they are dealt to up to
+  // 1 + kBatchSide lanes, each of which runs all the stages of its units on a stream of its own:
+  // one launch of a small group leaves most of the chip idle.
+  static constexpr int kBatchSide = 3;
+  std::vector<std::vector<int>> lanes;  // unit indices: groups first, then solo members
+  hipStream_t side[kBatchSide] = {};
+  hipEvent_t fork = nullptr, join[kBatchSide] = {};
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
   std::vector<Graph> graphs;    // most recent last
@@ -1359,67 +1357,105 @@ constexpr size_t kBatchGraphs = 8;  // one- and multi-step graphs of both pariti
 void batch_drop_graphs(dg_batch* b) {
   if (b->graphs.empty()) return;
   (void)hipStreamSynchronize(b->stream);
-  for (auto& g : b->graphs) (void)hipGraphExecDestroy(g.exec);
+  for (auto& g : b->graphs)
+    for (hipGraphExec_t e : g.exec) (void)hipGraphExecDestroy(e);
   b->graphs.clear();
 }
 
-// one RK stage of every member on stream st; afterwards every member's state has moved to its
-// other buffer
-hipError_t batch_stage(dg_batch* b, const double* dts, int k, hipStream_t st) {
-  for (dg_solver* s : b->m) {
-    hipError_t e = pre_stage(s, s->cur, st);
+// one RK stage k of a group on stream st, from the members' state buffers cur ^ par
+hipError_t batch_group_stage(dg_batch* b, const dg_batch::Group& g, const double* dts, int k, int par,
+                             hipStream_t st) {
+  for (int i : g.idx) {
+    hipError_t e = pre_stage(b->m[i], b->m[i]->cur ^ par, st);
     if (e != hipSuccess) return e;
   }
-  for (const auto& g : b->groups) {
-    dg::BatchArgs B;
-    std::memset(&B, 0, sizeof(B));
-    B.n = (int)g.idx.size();
-    B.start[0] = 0;
-    for (int j = 0; j < B.n; j++) {
-      dg_solver* s = b->m[g.idx[j]];
-      B.view[j] = s->dev_view;
-      B.cur[j] = s->cur;
-      B.dt[j] = dts[g.idx[j]];
-      B.start[j + 1] = B.start[j] + dg::wg_count(g.N, (int)s->E);
+  dg::BatchArgs B;
+  std::memset(&B, 0, sizeof(B));
+  B.n = (int)g.idx.size();
+  B.start[0] = 0;
+  for (int j = 0; j < B.n; j++) {
+    dg_solver* s = b->m[g.idx[j]];
+    B.view[j] = s->dev_view;
+    B.cur[j] = s->cur ^ par;
+    B.dt[j] = dts[g.idx[j]];
+    B.start[j + 1] = B.start[j] + dg::wg_count(g.N, (int)s->E);
+  }
+  if (g.visc) {
+    hipError_t e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.deform, st);
+    if (e != hipSuccess) return e;
+  }
+  return dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.deform, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
+                                dg::kModeRK, st);
+}
+
+// the same of a member with launches of its own
+hipError_t batch_solo_stage(dg_batch* b, int i, const double* dts, int k, int par, hipStream_t st) {
+  dg_solver* s = b->m[i];
+  const int cur = s->cur ^ par;
+  const double A = kRk[b->scheme].A[k], Bk = kRk[b->scheme].B[k];
+  hipError_t e = pre_stage(s, cur, st);
+  if (e != hipSuccess) return e;
+  if (s->v.mixed)
+    return dg::launch_stage_mixed(s->v, cur, dts[i], A, Bk, dg::kModeRK, s->mix_tiles, st,
+                                  s->mix_concurrent ? &s->mix : nullptr);
+  if (s->v.gauss) return dg::launch_stage_gauss(s->v, cur, dts[i], A, Bk, dg::kModeRK, st);
+  // spectral vanishing viscosity: the solver's own stage sequence
+  if (svv_folded(s)) {
+    if (s->v.visc_flux == DG_VISC_BR1) {
+      e = dg::launch_grad_svv(s->v, cur, s->svv, st);
+    } else {
+      e = dg::launch_gradient(s->v, cur, st);
+      if (e == hipSuccess) e = dg::launch_svv_flux(s->v, cur, s->svv, st);
     }
-    hipError_t e;
-    if (g.visc) {
-      e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.deform, st);
+    dg::View vf = s->v;
+    vf.Fa = s->svv.Fa;
+    if (e == hipSuccess) e = dg::launch_stage(vf, cur, dts[i], A, Bk, dg::kModeRK, st);
+    return e;
+  }
+  e = s->v.viscous ? dg::launch_gradient(s->v, cur, st) : hipSuccess;
+  if (e == hipSuccess) e = dg::launch_stage(s->v, cur, dts[i], A, Bk, dg::kModeRK, st);
+  if (e == hipSuccess) e = dg::launch_svv(s->v, cur, s->svv, dts[i], Bk, dg::kModeRK, st);
+  return e;
+}
+
+// RK steps first .. first + steps - 1 of a call, of lane l's units, on stream st
+hipError_t batch_lane(dg_batch* b, int l, const double* dts, int first, int steps, hipStream_t st) {
+  const int stages = kRk[b->scheme].stages, ng = (int)b->groups.size();
+  for (int k = first * stages; k < (first + steps) * stages; k++)
+    for (int u : b->lanes[l]) {
+      const int s = k % stages, par = k & 1;
+      const hipError_t e = u < ng ? batch_group_stage(b, b->groups[u], dts, s, par, st)
+                                  : batch_solo_stage(b, b->solo[u - ng], dts, s, par, st);
       if (e != hipSuccess) return e;
     }
-    e = dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.deform, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
-                               dg::kModeRK, st);
-    if (e != hipSuccess) return e;
-  }
-  for (int i : b->solo) {
-    dg_solver* s = b->m[i];
-    const double A = kRk[b->scheme].A[k], Bk = kRk[b->scheme].B[k];
-    hipError_t e;
-    if (s->v.mixed) {
-      e = dg::launch_stage_mixed(s->v, s->cur, dts[i], A, Bk, dg::kModeRK, s->mix_tiles, st,
-                                 s->mix_concurrent ? &s->mix : nullptr);
-    } else if (s->v.gauss) {
-      e = dg::launch_stage_gauss(s->v, s->cur, dts[i], A, Bk, dg::kModeRK, st);
-    } else {  // spectral vanishing viscosity: the solver's own stage sequence
-      if (svv_folded(s)) {
-        if (s->v.visc_flux == DG_VISC_BR1) {
-          e = dg::launch_grad_svv(s->v, s->cur, s->svv, st);
-        } else {
-          e = dg::launch_gradient(s->v, s->cur, st);
-          if (e == hipSuccess) e = dg::launch_svv_flux(s->v, s->cur, s->svv, st);
-        }
-        dg::View vf = s->v;
-        vf.Fa = s->svv.Fa;
-        if (e == hipSuccess) e = dg::launch_stage(vf, s->cur, dts[i], A, Bk, dg::kModeRK, st);
-      } else {
-        e = s->v.viscous ? dg::launch_gradient(s->v, s->cur, st) : hipSuccess;
-        if (e == hipSuccess) e = dg::launch_stage(s->v, s->cur, dts[i], A, Bk, dg::kModeRK, st);
-        if (e == hipSuccess) e = dg::launch_svv(s->v, s->cur, s->svv, dts[i], Bk, dg::kModeRK, st);
-      }
+  return hipSuccess;
+}
+
+// run(l, c, stream) for every lane and chunk c < chunks, the lanes in turn within a chunk; lane 0 on
+// the batch's stream and the others on side streams forked from it and joined to it by events
+// (outside any capture).  Afterwards every member's state has moved to the buffer that `steps` steps
+// lead to.
+hipError_t batch_fork(dg_batch* b, int steps, int chunks, const std::function<hipError_t(int, int, hipStream_t)>& run) {
+  const int nl = (int)b->lanes.size();
+  hipError_t err = hipSuccess;
+  int forked = 0;
+  if (nl > 1 && chunks > 0) {
+    err = hipEventRecord(b->fork, b->stream);
+    for (int l = 1; l < nl && err == hipSuccess; l++) {
+      err = hipStreamWaitEvent(b->side[l - 1], b->fork, 0);
+      if (err == hipSuccess) forked = l;
     }
-    if (e != hipSuccess) return e;
   }
-  for (dg_solver* s : b->m) s->cur ^= 1;
+  for (int c = 0; c < chunks && err == hipSuccess; c++)
+    for (int l = nl - 1; l >= 0 && err == hipSuccess; l--) err = run(l, c, l ? b->side[l - 1] : b->stream);
+  for (int l = 1; l <= forked; l++) {  // also after a failed launch: no work of a lane is left unordered
+    hipError_t e = hipEventRecord(b->join[l - 1], b->side[l - 1]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(b->stream, b->join[l - 1], 0);
+    if (err == hipSuccess) err = e;
+  }
+  if (err != hipSuccess) return err;
+  if ((steps * kRk[b->scheme].stages) & 1)
+    for (dg_solver* s : b->m) s->cur ^= 1;
   return hipSuccess;
 }
 
@@ -1430,26 +1466,34 @@ int batch_capture(dg_batch* b, const double* dts, int steps) {
   for (size_t i = 0; i < n; i++) G.par[i] = b->m[i]->cur;
   G.dts.assign(dts, dts + n);
   G.steps = steps;
-  hipGraph_t g = nullptr;
-  hipError_t err = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
-  if (err == hipSuccess) {
-    for (int st = 0; st < steps && err == hipSuccess; st++)
-      for (int k = 0; k < kRk[b->scheme].stages && err == hipSuccess; k++)
-        err = batch_stage(b, dts, k, b->cap_stream);
-    const hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
-    if (err == hipSuccess) err = e2;
+  auto discard = [&] {
+    for (hipGraphExec_t e : G.exec) (void)hipGraphExecDestroy(e);
+  };
+  for (size_t l = 0; l < b->lanes.size(); l++) {
+    hipGraph_t g = nullptr;
+    hipError_t err = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
+    if (err == hipSuccess) {
+      err = batch_lane(b, (int)l, dts, 0, steps, b->cap_stream);
+      const hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
+      if (err == hipSuccess) err = e2;
+    }
+    if (err != hipSuccess) {
+      if (g) (void)hipGraphDestroy(g);
+      discard();
+      return hip_fail(err, "capture of a batch RK step");
+    }
+    hipGraphExec_t ex = nullptr;
+    err = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (err != hipSuccess) {
+      discard();
+      return hip_fail(err, "instantiation of the batch RK-step graph");
+    }
+    G.exec.push_back(ex);
   }
-  for (size_t i = 0; i < n; i++) b->m[i]->cur = G.par[i];  // capture launched nothing
-  if (err != hipSuccess) {
-    if (g) (void)hipGraphDestroy(g);
-    return hip_fail(err, "capture of a batch RK step");
-  }
-  err = hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(g);
-  if (err != hipSuccess) return hip_fail(err, "instantiation of the batch RK-step graph");
   if (b->graphs.size() == kBatchGraphs) {
     (void)hipStreamSynchronize(b->stream);
-    (void)hipGraphExecDestroy(b->graphs.front().exec);
+    for (hipGraphExec_t e : b->graphs.front().exec) (void)hipGraphExecDestroy(e);
     b->graphs.erase(b->graphs.begin());
   }
   b->graphs.push_back(std::move(G));
@@ -1502,8 +1546,36 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
     for (int i : g.idx) blocks += b->m[i]->E;
     if (blocks >= (1LL << 31)) return fail(DG_EINVAL, "a batched launch would exceed 2^31 workgroups");
   }
+  // the units to lanes, the largest first to the lane with the least work (nodes, twice where viscous)
+  const int ng = (int)b->groups.size(), nu = ng + (int)b->solo.size();
+  std::vector<double> load(nu, 0.0);
+  for (int u = 0; u < nu; u++) {
+    if (u < ng)
+      for (int i : b->groups[u].idx) load[u] += (double)b->m[i]->ntot * (b->groups[u].visc ? 2.0 : 1.0);
+    else
+      load[u] = (double)b->m[b->solo[u - ng]]->ntot * (b->m[b->solo[u - ng]]->v.viscous ? 2.0 : 1.0);
+  }
+  std::vector<int> order(nu);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return load[x] > load[y]; });
+  const int nl = std::min(nu, 1 + dg_batch::kBatchSide);
+  b->lanes.resize(nl);
+  std::vector<double> total(nl, 0.0);
+  for (int u : order) {
+    const int l = (int)(std::min_element(total.begin(), total.end()) - total.begin());
+    b->lanes[l].push_back(u);
+    total[l] += load[u];
+  }
   hipError_t e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
-  if (e != hipSuccess) return hip_fail(e, "capture stream");
+  if (e == hipSuccess && nl > 1) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
+  for (int l = 1; l < nl && e == hipSuccess; l++) {
+    e = hipStreamCreateWithFlags(&b->side[l - 1], hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join[l - 1], hipEventDisableTiming);
+  }
+  if (e != hipSuccess) {
+    dg_batch_destroy(b.release());
+    return hip_fail(e, "streams of the batch");
+  }
   *out = b.release();
   return DG_OK;
 } catch (...) {
@@ -1519,31 +1591,46 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
   const bool same = b->last_dts.size() == n && std::equal(dts, dts + n, b->last_dts.begin());
   const bool replay = b->use_graphs && nsteps > 0 && (nsteps > 1 || same);
   b->last_dts.assign(dts, dts + n);
-  for (int it = 0; it < nsteps;) {
-    if (!replay) {
-      for (int k = 0; k < kRk[b->scheme].stages; k++)
-        DG_HIP(batch_stage(b, dts, k, b->stream), "batch RK stage kernels");
-      it++;
-      continue;
-    }
-    // kMultiSteps steps per graph launch while that many remain, then single steps
-    const int steps = nsteps - it >= kMultiSteps ? kMultiSteps : 1;
-    const dg_batch::Graph* G = nullptr;
+  if (!replay) {
+    DG_HIP(batch_fork(b, nsteps, nsteps,
+                      [&](int l, int c, hipStream_t st) { return batch_lane(b, l, dts, c, 1, st); }),
+           "batch RK stage kernels");
+    return DG_OK;
+  }
+  const int stages = kRk[b->scheme].stages;
+  const std::vector<int> chunks = graph_chunks(nsteps);
+  std::vector<const dg_batch::Graph*> seq(chunks.size());
+  auto find = [&](int steps) -> const dg_batch::Graph* {
     for (const auto& g : b->graphs) {
       bool hit = g.steps == steps && std::equal(dts, dts + n, g.dts.begin());
       for (size_t i = 0; hit && i < n; i++) hit = g.par[i] == b->m[i]->cur;
-      if (hit) G = &g;
+      if (hit) return &g;
     }
-    if (!G) {
-      int rc = batch_capture(b, dts, steps);
-      if (rc) return rc;
-      G = &b->graphs.back();
+    return nullptr;
+  };
+  // (a capture may drop an old graph that the sequence also needs, hence a second look: the sequence
+  // has at most five different graphs, and eight are kept)
+  for (bool complete = false; !complete;) {
+    complete = true;
+    int flipped = 0, rc = DG_OK;
+    for (size_t i = 0; i < seq.size() && rc == DG_OK; i++) {
+      seq[i] = find(chunks[i]);
+      if (!seq[i]) {
+        rc = batch_capture(b, dts, chunks[i]);
+        complete = false;
+      }
+      if ((chunks[i] * stages) & 1) {  // the buffers the next graph starts from
+        flipped ^= 1;
+        for (dg_solver* s : b->m) s->cur ^= 1;
+      }
     }
-    DG_HIP(hipGraphLaunch(G->exec, b->stream), "batch RK-step graph launch");
-    const int flips = (steps * kRk[b->scheme].stages) & 1;  // each stage moves every state
-    for (dg_solver* s : b->m) s->cur ^= flips;
-    it += steps;
+    if (flipped)
+      for (dg_solver* s : b->m) s->cur ^= 1;
+    if (rc) return rc;
   }
+  DG_HIP(batch_fork(b, nsteps, (int)seq.size(),
+                    [&](int l, int c, hipStream_t st) { return hipGraphLaunch(seq[c]->exec[l], st); }),
+         "batch RK-step graph launch");
   return DG_OK;
 } catch (...) {
   return abi_exception();
@@ -1572,6 +1659,12 @@ void dg_batch_destroy(dg_batch* b) try {
   if (!b) return;
   batch_drop_graphs(b);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+  for (int l = 0; l < dg_batch::kBatchSide; l++) {
+    if (b->side[l]) (void)hipStreamSynchronize(b->side[l]);
+    if (b->side[l]) (void)hipStreamDestroy(b->side[l]);
+    if (b->join[l]) (void)hipEventDestroy(b->join[l]);
+  }
+  if (b->fork) (void)hipEventDestroy(b->fork);
   delete b;
 } catch (...) {
 }
