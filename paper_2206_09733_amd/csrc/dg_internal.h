@@ -98,8 +98,8 @@ struct View {
   // work-list range [mix_beg[b], mix_beg[b] + mix_cnt[b]) of the elements with
   // 64 b < nodes <= 64 (b + 1)
   int mix_beg[6], mix_cnt[6];
-  // face fluxes of mixed-order meshes: [E][6 faces][6][49], rows 0-4 the numerical flux on the
-  // element's face grid, row 5 its FP64 mass component (FP32-bulk)
+  // face fluxes of mixed-order meshes: kMixFaceDoubles per element, packed [6 faces][components][face
+  // points], the components being the numerical flux and (FP32-bulk) its FP64 mass component
   double* Fs;
   // spectral vanishing viscosity folded into the Navier-Stokes stage kernel (set only in the View
   // of that launch): the filtered contravariant flux [E][12][nn] of the stage's input state,

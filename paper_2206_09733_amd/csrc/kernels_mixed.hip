@@ -153,20 +153,22 @@ __device__ __forceinline__ int sdiv(int q, float inv_n) { return (int)(((float)q
 // +xi_d side) and R = nbr(L, +d), with L's metric Ja^d as the scaled normal.  Traces are staged
 // in LDS, interpolated to the mortar of the larger tangential orders (the identity where the
 // orders agree), the numerical flux is evaluated at the mortar points, and it is L2-projected
-// onto the face grids of both elements: Fs[e][f][c][p + n_a r], f = 2 d + side of element e,
-// c = 0..4 the flux and c = 5 its FP64 mass component (FP32-bulk).  Each face is evaluated once.
+// onto the face grids of both elements: Fs[e], packed in the order [f][c][p + n_a r], f = 2 d + side of
+// element e, c = 0..4 the flux and (FP32-bulk) c = 5 its FP64 mass component, so that the stage kernel
+// copies one contiguous block.  Each face is evaluated once.
 // In each tangential direction at most one side has fewer nodes than the mortar: only that side
 // is interpolated and projected along it (the other side's data already lies on the mortar
 // grid and is used in place), so every loop has a trip count and branches that are uniform over
 // the wave.
-constexpr int kFsFace = 6 * kMixNF;  // doubles per element face in Fs
-
 // XS: the extended surface fluxes (codes >= 4), compiled apart so that the others keep their
 // registers
-template <typename T, bool XS>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 : 4)))
+// CART: plain boxes: the scaled normal is cja[d] e_d, so only the two states are interpolated (with
+// their velocity components in the rotated frame) and no metric term is read.
+template <typename T, bool XS, bool CART>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 : (CART ? 5 : 4))))
     mixed_face_kernel(View v, int cur) {
   constexpr bool DEV = sizeof(T) == 4;
+  constexpr int NL = CART ? 5 : 8;  // L's fields: state, and its Ja^d
   constexpr int NC = DEV ? 6 : 5;
   static_assert(kMixNF <= 64, "a face grid, or a mortar matrix, fits one wave");
   const int fid = block_element(3 * v.E);
@@ -194,7 +196,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
   // sA: rows 0-4 L's state, 5-7 L's Ja^d (L's grid), rows 8-12 R's state (R's grid); later
   // rows 0-5 the flux on the mortar.  sB: the side interpolated along a (up to 8 rows), later
   // the flux projected along a onto that side's grid (up to 6 rows).
-  __shared__ double sA[13][kMixNF], sB[8][kMixNF];
+  // (CART: R's state in rows 5-9)
+  __shared__ double sA[NL + 5][kMixNF], sB[NL > NC ? NL : NC][kMixNF];
   // interpolation to the mortar and projection back, along a and along b (only the sides
   // that need them)
   __shared__ double sIa[kMixNF], sPa[kMixNF], sIb[kMixNF], sPb[kMixNF];
@@ -205,22 +208,32 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
   const int sRa = d == 0 ? nR0 : 1, sRb = d == 2 ? nR0 : nR0 * nR1;
   const int baseL = d == 0 ? nL0 - 1 : (d == 1 ? (nL1 - 1) * nL0 : (nL2 - 1) * nL0 * nL1);
   const long offL = fd.z, offR = fd.w, nnL = nL0 * nL1 * nL2, nnR = nR0 * nR1 * nR2;
-  double tL[8], tR[5];
+  double tL[NL], tR[5];
+  // component of the rotated frame's axis k (CART), or k itself
+  const int a0 = CART ? d : 0, a1 = CART ? (d == 2 ? 0 : d + 1) : 1, a2 = CART ? (d == 0 ? 2 : d - 1) : 2;
   {
     const int x = t < naL * nbL ? t : 0;
     const int r = sdiv(x, 1.0f / (float)naL), p = x - r * naL;
     const int q = baseL + p * sLa + r * sLb;
 #pragma unroll
-    for (int c = 0; c < 5; c++) tL[c] = Uin[offL * 5 + c * nnL + q];
+    for (int c = 0; c < 5; c++) {
+      const int cc = c == 1 ? 1 + a0 : (c == 2 ? 1 + a1 : (c == 3 ? 1 + a2 : c));
+      tL[c] = Uin[offL * 5 + cc * nnL + q];
+    }
+    if constexpr (!CART) {
 #pragma unroll
-    for (int c = 0; c < 3; c++) tL[5 + c] = v.Ja[offL * 9 + (3 * d + c) * nnL + q];
+      for (int c = 0; c < 3; c++) tL[5 + c] = v.Ja[offL * 9 + (3 * d + c) * nnL + q];
+    }
   }
   {
     const int y = t < naR * nbR ? t : 0;
     const int r = sdiv(y, 1.0f / (float)naR), p = y - r * naR;
     const int q = p * sRa + r * sRb;
 #pragma unroll
-    for (int c = 0; c < 5; c++) tR[c] = Uin[offR * 5 + c * nnR + q];
+    for (int c = 0; c < 5; c++) {
+      const int cc = c == 1 ? 1 + a0 : (c == 2 ? 1 + a1 : (c == 3 ? 1 + a2 : c));
+      tR[c] = Uin[offR * 5 + cc * nnR + q];
+    }
   }
   const double* mt = v.mtab;
   double tIa = 0.0, tPa = 0.0, tIb = 0.0, tPb = 0.0;
@@ -238,11 +251,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
   }
   if (t < naL * nbL) {
 #pragma unroll
-    for (int c = 0; c < 8; c++) sA[c][t] = tL[c];
+    for (int c = 0; c < NL; c++) sA[c][t] = tL[c];
   }
   if (t < naR * nbR) {
 #pragma unroll
-    for (int c = 0; c < 5; c++) sA[8 + c][t] = tR[c];
+    for (int c = 0; c < 5; c++) sA[NL + c][t] = tR[c];
   }
   if (sa >= 0 && t < ma * na_s) {
     sIa[t] = tIa;
@@ -257,19 +270,19 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
   // Each weight is read once and applied to every field (the sum over p of each field keeps its
   // order).
   if (sa >= 0) {
-    const int c0 = sa == 0 ? 0 : 8, nc = sa == 0 ? 8 : 5;
+    const int c0 = sa == 0 ? 0 : NL, nc = sa == 0 ? NL : 5;
     for (int y = t; y < ma * nb_a; y += 64) {
       const int r = sdiv(y, ima), pm = y - r * ma;
-      double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      double s[NL] = {};
       for (int p = 0; p < na_s; p++) {
         const double w = sIa[pm * na_s + p];
         const int x = p + na_s * r;
 #pragma unroll
-        for (int c = 0; c < 8; c++)
+        for (int c = 0; c < NL; c++)
           if (c < nc) s[c] += w * sA[c0 + c][x];
       }
 #pragma unroll
-      for (int c = 0; c < 8; c++)
+      for (int c = 0; c < NL; c++)
         if (c < nc) sB[c][y] = s[c];
     }
   }
@@ -279,51 +292,58 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
     const int x = t;
     const bool on = x < ma * mb;
     const int rm = sdiv(x, ima), pm = x - rm * ma;
-    double a[13];
-    // L's 8 fields (rows of sB if L was interpolated along a), then R's 5
+    double a[NL + 5];
+    // L's fields (rows of sB if L was interpolated along a), then R's 5
     const double(*rowsL)[kMixNF] = sa == 0 ? sB : sA;
-    const double(*rowsR)[kMixNF] = sa == 1 ? sB : sA + 8;
+    const double(*rowsR)[kMixNF] = sa == 1 ? sB : sA + NL;
     if (nbL == mb) {
 #pragma unroll
-      for (int c = 0; c < 8; c++) a[c] = on ? rowsL[c][pm + ma * rm] : 0.0;
+      for (int c = 0; c < NL; c++) a[c] = on ? rowsL[c][pm + ma * rm] : 0.0;
     } else {
 #pragma unroll
-      for (int c = 0; c < 8; c++) a[c] = 0.0;
+      for (int c = 0; c < NL; c++) a[c] = 0.0;
       if (on)
         for (int r = 0; r < nbL; r++) {
           const double w = sIb[rm * nbL + r];
 #pragma unroll
-          for (int c = 0; c < 8; c++) a[c] += w * rowsL[c][pm + ma * r];
+          for (int c = 0; c < NL; c++) a[c] += w * rowsL[c][pm + ma * r];
         }
     }
     if (nbR == mb) {
 #pragma unroll
-      for (int c = 0; c < 5; c++) a[8 + c] = on ? rowsR[c][pm + ma * rm] : 0.0;
+      for (int c = 0; c < 5; c++) a[NL + c] = on ? rowsR[c][pm + ma * rm] : 0.0;
     } else {
 #pragma unroll
-      for (int c = 0; c < 5; c++) a[8 + c] = 0.0;
+      for (int c = 0; c < 5; c++) a[NL + c] = 0.0;
       if (on)
         for (int r = 0; r < nbR; r++) {
           const double w = sIb[rm * nbR + r];
 #pragma unroll
-          for (int c = 0; c < 5; c++) a[8 + c] += w * rowsR[c][pm + ma * r];
+          for (int c = 0; c < 5; c++) a[NL + c] += w * rowsR[c][pm + ma * r];
         }
     }
     __syncthreads();  // every mortar point has read its data before the flux rows overwrite sA
     if (on) {
       const double uL[5] = {a[0], a[1], a[2], a[3], a[4]};
-      const double S[3] = {a[5], a[6], a[7]};
-      const double uR[5] = {a[8], a[9], a[10], a[11], a[12]};
+      const double uR[5] = {a[NL], a[NL + 1], a[NL + 2], a[NL + 3], a[NL + 4]};
+      double S[3] = {d == 0 ? v.cja[0] : (d == 1 ? v.cja[1] : v.cja[2]), 0.0, 0.0};
+      if constexpr (!CART) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) S[c] = a[5 + c];
+      }
       T F[5];
       if constexpr (DEV) {
         double F0d;
-        face_flux_dev<T>(v.surf, uL, uR, S, v.gamma, Rf, F, F0d);
+        face_flux_dev<T, CART>(v.surf, uL, uR, S, v.gamma, Rf, F, F0d);
         sA[5][x] = F0d;
       } else {
-        face_flux<XS>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
+        face_flux<XS, CART>(v.surf, uL, uR, S, v.gamma, F, XS && v.surf == 8 ? v.adapt[3] : 0.0);
       }
 #pragma unroll
-      for (int c = 0; c < 5; c++) sA[c][x] = (double)F[c];
+      for (int c = 0; c < 5; c++) {
+        const int cc = c == 1 ? 1 + a0 : (c == 2 ? 1 + a1 : (c == 3 ? 1 + a2 : c));
+        sA[cc][x] = (double)F[c];
+      }
     }
   }
   __syncthreads();
@@ -350,7 +370,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
   for (int side = 0; side < 2; side++) {
     const int na = side ? naR : naL, nb = side ? nbR : nbL;
     const double(*src)[kMixNF] = sa == side ? sB : sA;  // the flux along a on this side's grid
-    double* out = v.Fs + ((long)(side ? eR : e) * 6 + (side ? 2 * d : 2 * d + 1)) * kFsFace;
+    const int m0 = side ? nR0 : nL0, m1 = side ? nR1 : nL1, m2 = side ? nR2 : nL2, np = na * nb;
+    // faces of the element before this one, components and points packed (L's +side, R's -side)
+    const int before = d == 0 ? 0 : (d == 1 ? 2 * m1 * m2 : 2 * (m1 * m2 + m0 * m2));
+    double* out = v.Fs + (long)(side ? eR : e) * kMixFaceDoubles + NC * (before + (side ? 0 : np));
     const float ina = 1.0f / (float)na;
     for (int y = t; y < na * nb; y += 64) {
       const int ro = sdiv(y, ina), po = y - ro * na;
@@ -368,7 +391,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XS ? 3 
         }
       }
 #pragma unroll
-      for (int c = 0; c < NC; c++) out[c * kMixNF + y] = s[c];
+      for (int c = 0; c < NC; c++) out[c * np + y] = s[c];
     }
   }
 }
@@ -392,7 +415,17 @@ __host__ __device__ constexpr int mix_face_points(int nnmax) {
   return best;
 }
 
-template <int NNMAX, int NPL, typename T, bool KEP>
+// The volume term is that of the uniform-order stage kernel: a lane evaluates the two-point fluxes of
+// its node with the nodes at cyclic distance o = 1 .. (n-1)/2 on its line and hands each flux to the
+// partner through LDS (for even n the pairs at distance n/2 are evaluated by both nodes), so each
+// pair is evaluated once; n is uniform over the workgroup, so the barriers of an exchange are too.
+// CART: plain boxes, whose metric terms are constants: none is read and the fluxes are formed in a
+// frame rotated to the direction.
+// The loop over the directions is unrolled: the choices by direction disappear, and the RK register
+// can be requested before the last direction without holding registers through the others (126 ->
+// 116 VGPRs).  24^3, orders 2..6, RK3 step with the face pass, plain box: each pair from both nodes
+// 819 us, once and CART 712, packed face fluxes 639-653, unrolled 609.
+template <int NNMAX, int NPL, typename T, bool KEP, bool CART>
 __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
     mixed_stage_kernel(View v, int wbeg, int cur, double dt, double rkA, double rkB, int mode) {
   constexpr int BS = mix_lanes(NNMAX, NPL);
@@ -400,35 +433,33 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
   constexpr int NC = DEV ? 6 : 5;       // face flux components read (FP32-bulk: + FP64 mass)
   constexpr int NFS = NC * mix_face_points(NNMAX);
   constexpr int KF = (NFS + BS - 1) / BS;  // face flux values per lane
+  // two exchange buffers in turn need one barrier an exchange instead of two; the large buckets
+  // take one, which keeps three workgroups in a CU's LDS
+  constexpr int XB = NNMAX <= 192 ? 2 : 1;
   const int4 wi = v.work[wbeg + blockIdx.x];
   const int e = wi.x;
-  ElemInfo I;
-  I.n[0] = wi.y & 7;
-  I.n[1] = (wi.y >> 3) & 7;
-  I.n[2] = (wi.y >> 6) & 7;
-  I.off = wi.z;
-  I.nn = wi.w;
+  const int n0 = wi.y & 7, n1 = (wi.y >> 3) & 7, n2 = (wi.y >> 6) & 7;
   const int t = threadIdx.x;
-  const long off = I.off, nn = I.nn;
+  const long off = wi.z, nn = wi.w;
+  const int inn = wi.w;
   const double* __restrict__ Uin = state(v, cur);
-  const double* __restrict__ Fs = v.Fs + (long)e * 6 * kFsFace;
+  const double* __restrict__ Fs = v.Fs + (long)e * kMixFaceDoubles;
   const Ref Rf = make_ref(v.rho_r, v.p_r, v.gamma);
-  const int str[3] = {1, I.n[0], I.n[0] * I.n[1]};
-  const float inv0 = 1.0f / (float)I.n[0], inv01 = 1.0f / (float)str[2];
+  const float inv0 = 1.0f / (float)n0, inv01 = 1.0f / (float)(n0 * n1);
   // face points of the faces normal to each direction, and where face f's fluxes start in sFs
   // (the element's faces packed: f = 2 d + side, component-major within a face)
-  const int n0 = I.n[0], n1 = I.n[1], n2 = I.n[2];
   const int pt0 = n1 * n2, pt1 = n0 * n2, pt2 = n0 * n1;
-  const float ip0 = 1.0f / (float)pt0, ip1 = 1.0f / (float)pt1, ip2 = 1.0f / (float)pt2;
   const int fo1 = NC * pt0, fo2 = 2 * NC * pt0, fo3 = fo2 + NC * pt1, fo4 = fo2 + 2 * NC * pt1,
             fo5 = fo4 + NC * pt2, fend = fo4 + 2 * NC * pt2;
 
   __shared__ double sD[3][kMixNF], sw[3][kMixN];
   __shared__ T sP[5][NNMAX];             // rho, v1, v2, v3, beta (FP32-bulk: deviations)
-  constexpr int NV = DEV ? NNMAX : 1;
+  constexpr int NV = DEV ? NNMAX : 1, NM = CART ? 1 : NNMAX;
   __shared__ double sVd[3][NV];          // FP32-bulk: FP64 velocities for the mass flux
-  __shared__ double sJ3[3][NNMAX];       // Ja^d of the direction in work
+  __shared__ double sJ3[3][NM];          // Ja^d of the direction in work
   __shared__ double sFs[NFS];            // the element's face fluxes
+  __shared__ T sX[XB][DEV ? 4 : 5][NNMAX];  // the exchanged fluxes (FP32-bulk: 1..4, the FP64 mass flux in sX0)
+  __shared__ double sX0[XB][NV];
 
   // Every operand of the element is requested before any is used: state, the first direction's
   // metric terms, the face fluxes and the tables (the tables with clamped indices, so that no
@@ -437,34 +468,31 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
 #pragma unroll
   for (int s = 0; s < NPL; s++) {
     const int q = t + s * BS;
-    const int qc = q < I.nn ? q : 0;
+    const int qc = q < inn ? q : 0;
 #pragma unroll
     for (int c = 0; c < 5; c++) u[s][c] = Uin[off * 5 + c * nn + qc];
+    if constexpr (!CART) {
 #pragma unroll
-    for (int c = 0; c < 3; c++) jn[s][c] = v.Ja[off * 9 + c * nn + qc];
+      for (int c = 0; c < 3; c++) jn[s][c] = v.Ja[off * 9 + c * nn + qc];
+    }
   }
   double fv[KF];
 #pragma unroll
   for (int k = 0; k < KF; k++) {
     const int x = t + k * BS;
-    // face f of packed entry x, its component c and point q
-    const int f = x < fo1 ? 0 : (x < fo2 ? 1 : (x < fo3 ? 2 : (x < fo4 ? 3 : (x < fo5 ? 4 : 5))));
-    const int fb = f == 0 ? 0 : (f == 1 ? fo1 : (f == 2 ? fo2 : (f == 3 ? fo3 : (f == 4 ? fo4 : fo5))));
-    const int pf = f < 2 ? pt0 : (f < 4 ? pt1 : pt2);
-    const int c = sdiv(x - fb, f < 2 ? ip0 : (f < 4 ? ip1 : ip2)), q = x - fb - c * pf;
-    fv[k] = x < fend ? Fs[f * kFsFace + c * kMixNF + q] : 0.0;
+    fv[k] = x < fend ? Fs[x] : 0.0;
   }
   double tD[3], tw[3];
 #pragma unroll
   for (int d = 0; d < 3; d++) {
-    const int n = I.n[d];
+    const int n = d == 0 ? n0 : (d == 1 ? n1 : n2);
     tD[d] = tab_D(v, n)[t < n * n ? t : 0];
     tw[d] = tab_w(v, n)[t < n ? t : 0];
   }
   static_assert(BS >= kMixNF, "one table entry per lane");
 #pragma unroll
   for (int d = 0; d < 3; d++) {
-    const int n = I.n[d];
+    const int n = d == 0 ? n0 : (d == 1 ? n1 : n2);
     if (t < n * n) sD[d][t] = tD[d];
     if (t < n) sw[d][t] = tw[d];
   }
@@ -476,20 +504,20 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
 #pragma unroll
   for (int s = 0; s < NPL; s++) {
     const int q = t + s * BS;
-    const int k = sdiv(q, inv01), rem = q - k * str[2];
+    const int k = sdiv(q, inv01), rem = q - k * n0 * n1;
     const int j = sdiv(rem, inv0);
-    ii[s][0] = rem - j * I.n[0];
+    ii[s][0] = rem - j * n0;
     ii[s][1] = j;
     ii[s][2] = k;
-    if (q < I.nn) {
+    if (q < inn) {
       const Prim<T> P = DEV ? make_prim_dev<T>(u[s], v.gamma, Rf) : make_prim<T>(u[s], v.gamma);
       sP[0][q] = P.rho; sP[1][q] = P.v1; sP[2][q] = P.v2; sP[3][q] = P.v3;
       sP[4][q] = P.beta;
       if (DEV) {
         const double ir = rcp(u[s][0]);
-        sVd[0][q] = u[s][1] * ir;
-        sVd[1][q] = u[s][2] * ir;
-        sVd[2][q] = u[s][3] * ir;
+        sVd[0][DEV ? q : 0] = u[s][1] * ir;
+        sVd[1][DEV ? q : 0] = u[s][2] * ir;
+        sVd[2][DEV ? q : 0] = u[s][3] * ir;
       }
     }
   }
@@ -498,6 +526,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
   // surface lift of the face fluxes.  Slot s of the lane holds node t + s BS.
   T acc[NPL][5];
   double accm[NPL];  // FP32-bulk: FP64 mass accumulators
+  double du_in[NPL][5];
 #pragma unroll
   for (int s = 0; s < NPL; s++) {
 #pragma unroll
@@ -505,90 +534,164 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
     accm[s] = 0.0;
   }
   const T ce = (T)(0.5 / (v.gamma - 1.0)), gm1 = (T)(v.gamma - 1.0);
-  // Direction d's parameters are passed in, and every per-direction choice is a select of
-  // values: an array indexed by the runtime d, or a select between captured variables, would keep
-  // the lambda's captures (the kernel argument among them) in private memory.
-  //   n, sd: node count and node stride along d; pf: points of a face normal to d; flo, fhi:
-  //   where the fluxes of the faces at index 0 and n - 1 along d start in sFs
-  auto node_volume = [&](const int d, const int n, const int sd, const int pf, const int flo, const int fhi,
-                         const int q, const int* iq, T* acc, double& accm) {
-    const int id = d == 0 ? iq[0] : (d == 1 ? iq[1] : iq[2]);
-    const int b0 = q - id * sd;
-    Prim<T> A;
-    A.rho = sP[0][q]; A.v1 = sP[1][q]; A.v2 = sP[2][q]; A.v3 = sP[3][q];
-    A.beta = sP[4][q];
-    const double ja0 = sJ3[0][q], ja1 = sJ3[1][q], ja2 = sJ3[2][q];
-    for (int m = 0; m < n; m++) {
-      if (m == id) continue;
-      const int qm = b0 + m * sd;
-      Prim<T> B;
-      B.rho = sP[0][qm]; B.v1 = sP[1][qm]; B.v2 = sP[2][qm]; B.v3 = sP[3][qm];
-      B.beta = sP[4][qm];
-      const double md[3] = {ja0 + sJ3[0][qm], ja1 + sJ3[1][qm], ja2 + sJ3[2][qm]};
-      T F[5];
-      double F0d = 0.0;
-      if constexpr (DEV) {
-        const double va[3] = {sVd[0][q], sVd[1][q], sVd[2][q]};
-        const double vb[3] = {sVd[0][qm], sVd[1][qm], sVd[2][qm]};
-        if (v.vol == 0) {
-          const double vn64 = 0.5 * ((va[0] + vb[0]) * md[0] + (va[1] + vb[1]) * md[1] + (va[2] + vb[2]) * md[2]);
-          flux_ec_dev(A, B, (T)md[0], (T)md[1], (T)md[2], vn64, Rf, F, F0d);
-        } else {
-          flux_central_dev(A, B, (T)md[0], (T)md[1], (T)md[2], va, vb, md, Rf, F, F0d);
-        }
-      } else {
-        vol_flux<KEP>(v.vol, A, B, (T)md[0], (T)md[1], (T)md[2], ce, gm1, F);
-      }
-      const double Dm = sD[d][id * n + m];
+  const double cj0 = v.cja[0], cj1 = v.cja[1], cj2 = v.cja[2];
+  int xb = 0;  // exchange buffer in use
+  // (every per-direction choice is a select of values: an array indexed by the runtime d, or a select
+  // between captured variables, would keep the kernel argument in private memory)
 #pragma unroll
-      for (int c = 0; c < 5; c++) acc[c] += (T)Dm * F[c];
-      if (DEV) accm += Dm * F0d;
-    }
-    // the node's point on the faces normal to d (tangential indices in increasing direction)
-    const int qf = d == 0 ? iq[1] + n1 * iq[2] : (d == 1 ? iq[0] + n0 * iq[2] : iq[0] + n0 * iq[1]);
-    if (id == n - 1) {
-      const double iw = 1.0 / sw[d][n - 1];
-      const double* F = sFs + fhi;
-#pragma unroll
-      for (int c = 0; c < 5; c++) acc[c] += (T)(iw * F[c * pf + qf]);
-      if (DEV) accm += iw * F[5 * pf + qf];
-    }
-    if (id == 0) {
-      const double iw = 1.0 / sw[d][0];
-      const double* F = sFs + flo;
-#pragma unroll
-      for (int c = 0; c < 5; c++) acc[c] -= (T)(iw * F[c * pf + qf]);
-      if (DEV) accm -= iw * F[5 * pf + qf];
-    }
-  };
   for (int d = 0; d < 3; d++) {
-    __syncthreads();  // the previous direction's metric is no longer read
+    __syncthreads();  // primitives staged; the previous direction's LDS data is no longer read
+    if constexpr (!CART) {
 #pragma unroll
-    for (int s = 0; s < NPL; s++)
-      if (t + s * BS < I.nn)
+      for (int s = 0; s < NPL; s++)
+        if (t + s * BS < inn)
 #pragma unroll
-        for (int c = 0; c < 3; c++) sJ3[c][t + s * BS] = jn[s][c];
-    __syncthreads();
-    if (d < 2) {  // the next direction's metric terms, in flight during this direction's sums
+          for (int c = 0; c < 3; c++) sJ3[c][CART ? 0 : t + s * BS] = jn[s][c];
+      __syncthreads();
+      if (d < 2) {  // the next direction's metric terms, in flight during this direction's sums
+#pragma unroll
+        for (int s = 0; s < NPL; s++) {
+          const int q = t + s * BS;
+          const int qc = q < inn ? q : 0;
+#pragma unroll
+          for (int c = 0; c < 3; c++) jn[s][c] = v.Ja[off * 9 + (3 * (d + 1) + c) * nn + qc];
+        }
+      }
+    }
+    if (d == 2 && mode != kModeResidual && rkA != 0.0) {  // the RK register, in flight during the last direction
 #pragma unroll
       for (int s = 0; s < NPL; s++) {
-        const int q = t + s * BS;
-        const int qc = q < I.nn ? q : 0;
+        const int qc = t + s * BS < inn ? t + s * BS : 0;
 #pragma unroll
-        for (int c = 0; c < 3; c++) jn[s][c] = v.Ja[off * 9 + (3 * (d + 1) + c) * nn + qc];
+        for (int c = 0; c < 5; c++) du_in[s][c] = v.dU[off * 5 + c * nn + qc];
       }
     }
     const int n = d == 0 ? n0 : (d == 1 ? n1 : n2), sd = d == 0 ? 1 : (d == 1 ? n0 : n0 * n1);
     const int pf = d == 0 ? pt0 : (d == 1 ? pt1 : pt2);
     const int flo = d == 0 ? 0 : (d == 1 ? fo2 : fo4), fhi = d == 0 ? fo1 : (d == 1 ? fo3 : fo5);
-    // one call site (unrolled after inlining)
+    const int c0 = CART ? d : 0, c1 = CART ? (d == 2 ? 0 : d + 1) : 1, c2 = CART ? (d == 0 ? 2 : d - 1) : 2;
+    const double* Dd = sD[0] + d * kMixNF;
+    // flux of node q (index id on its line) with the node qm
+    auto pair_flux = [&](const int q, const int qm, T F[5], double& F0d) {
+      Prim<T> A, B;
+      A.rho = sP[0][q]; A.beta = sP[4][q];
+      B.rho = sP[0][qm]; B.beta = sP[4][qm];
+      double md[3] = {1.0, 0.0, 0.0};
+      if constexpr (!CART) {
 #pragma unroll
-    for (int s = 0; s < NPL; s++)
-      if (t + s * BS < I.nn) node_volume(d, n, sd, pf, flo, fhi, t + s * BS, ii[s], acc[s], accm[s]);
+        for (int c = 0; c < 3; c++) md[c] = sJ3[c][CART ? 0 : q] + sJ3[c][CART ? 0 : qm];
+      }
+      if constexpr (DEV) {
+        const double va[3] = {sVd[c0][DEV ? q : 0], sVd[c1][DEV ? q : 0], sVd[c2][DEV ? q : 0]};
+        const double vb[3] = {sVd[c0][DEV ? qm : 0], sVd[c1][DEV ? qm : 0], sVd[c2][DEV ? qm : 0]};
+        A.v1 = (T)va[0]; A.v2 = (T)va[1]; A.v3 = (T)va[2];
+        B.v1 = (T)vb[0]; B.v2 = (T)vb[1]; B.v3 = (T)vb[2];
+        if (v.vol == 0) {
+          const double vn64 = 0.5 * dotn<CART>(va[0] + vb[0], va[1] + vb[1], va[2] + vb[2], md[0], md[1], md[2]);
+          flux_ec_dev<CART>(A, B, (T)md[0], (T)md[1], (T)md[2], vn64, Rf, F, F0d);
+        } else {
+          flux_central_dev<CART>(A, B, (T)md[0], (T)md[1], (T)md[2], va, vb, md, Rf, F, F0d);
+        }
+      } else {
+        A.v1 = sP[1 + c0][q]; A.v2 = sP[1 + c1][q]; A.v3 = sP[1 + c2][q];
+        B.v1 = sP[1 + c0][qm]; B.v2 = sP[1 + c1][qm]; B.v3 = sP[1 + c2][qm];
+        vol_flux<KEP, CART>(v.vol, A, B, (T)md[0], (T)md[1], (T)md[2], ce, gm1, F);
+      }
+    };
+    T pa[NPL][5];
+    double pm[NPL];
+#pragma unroll
+    for (int s = 0; s < NPL; s++) {
+#pragma unroll
+      for (int c = 0; c < 5; c++) pa[s][c] = 0;
+      pm[s] = 0.0;
+    }
+    auto add = [&](const double D, const T F[5], const double F0d, T p[5], double& m) {
+      if constexpr (DEV) m += D * F0d;
+      else p[0] += (T)D * F[0];
+#pragma unroll
+      for (int c = 1; c < 5; c++) p[c] += (T)D * F[c];
+    };
+#pragma unroll 1
+    for (int o = 1; 2 * o <= n; o++) {
+      const bool half = 2 * o == n;
+      if (XB == 1 && o > 1 && !half) __syncthreads();  // the buffer's previous readers are done
+#pragma unroll
+      for (int s = 0; s < NPL; s++) {
+        const int q = t + s * BS;
+        if (q >= inn) continue;
+        const int id = d == 0 ? ii[s][0] : (d == 1 ? ii[s][1] : ii[s][2]);
+        const int j = id + o < n ? id + o : id + o - n;
+        T F[5];
+        double F0d = 0.0;
+        pair_flux(q, q + (j - id) * sd, F, F0d);
+        add(Dd[id * n + j], F, F0d, pa[s], pm[s]);
+        if (!half) {
+          if constexpr (DEV) sX0[xb][DEV ? q : 0] = F0d;
+#pragma unroll
+          for (int c = DEV ? 1 : 0; c < 5; c++) sX[xb][c - (DEV ? 1 : 0)][q] = F[c];
+        }
+      }
+      if (half) break;
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < NPL; s++) {
+        const int q = t + s * BS;
+        if (q >= inn) continue;
+        const int id = d == 0 ? ii[s][0] : (d == 1 ? ii[s][1] : ii[s][2]);
+        const int j = id - o >= 0 ? id - o : id - o + n;
+        const int qm = q + (j - id) * sd;
+        T F[5];
+#pragma unroll
+        for (int c = DEV ? 1 : 0; c < 5; c++) F[c] = sX[xb][c - (DEV ? 1 : 0)][qm];
+        add(Dd[id * n + j], F, DEV ? sX0[xb][DEV ? qm : 0] : 0.0, pa[s], pm[s]);
+      }
+      xb = XB == 2 ? xb ^ 1 : 0;
+    }
+    const double s64 = CART ? 2.0 * (d == 0 ? cj0 : (d == 1 ? cj1 : cj2)) : 1.0;
+#pragma unroll
+    for (int s = 0; s < NPL; s++) {
+      if (t + s * BS >= inn) continue;
+      const int i0 = ii[s][0], i1 = ii[s][1], i2 = ii[s][2];
+      const int id = d == 0 ? i0 : (d == 1 ? i1 : i2);
+      // back from the rotated frame: component x of it is pa[1 + (x - d) mod 3]
+      const T p1 = pa[s][1], p2 = pa[s][2], p3 = pa[s][3];
+      T q[5] = {pa[s][0], p1, p2, p3, pa[s][4]};
+      if constexpr (CART) {
+        q[1] = d == 0 ? p1 : (d == 1 ? p3 : p2);
+        q[2] = d == 0 ? p2 : (d == 1 ? p1 : p3);
+        q[3] = d == 0 ? p3 : (d == 1 ? p2 : p1);
+      }
+      double qm = pm[s];
+      if constexpr (CART) {
+        qm *= s64;
+#pragma unroll
+        for (int c = 0; c < 5; c++) q[c] *= (T)s64;
+      }
+      // the node's point on the faces normal to d (tangential indices in increasing direction)
+      const int qf = d == 0 ? i1 + n1 * i2 : (d == 1 ? i0 + n0 * i2 : i0 + n0 * i1);
+      if (id == n - 1) {
+        const double iw = rcp(sw[0][d * kMixN + n - 1]);
+        const double* F = sFs + fhi;
+#pragma unroll
+        for (int c = 0; c < 5; c++) q[c] += (T)(iw * F[c * pf + qf]);
+        if (DEV) qm += iw * F[5 * pf + qf];
+      }
+      if (id == 0) {
+        const double iw = rcp(sw[0][d * kMixN]);
+        const double* F = sFs + flo;
+#pragma unroll
+        for (int c = 0; c < 5; c++) q[c] -= (T)(iw * F[c * pf + qf]);
+        if (DEV) qm -= iw * F[5 * pf + qf];
+      }
+#pragma unroll
+      for (int c = 0; c < 5; c++) acc[s][c] += q[c];
+      accm[s] += qm;
+    }
   }
-  auto node_update = [&](const int q, const T* acc, const double accm) {
+  auto node_update = [&](const int q, const T* acc, const double accm, const double* du_in) {
     const long o = off * 5 + q;
-    const double ij = v.invJ[off + q];
+    const double ij = CART ? v.cij : v.invJ[off + q];
     double R[5];
 #pragma unroll
     for (int c = 0; c < 5; c++) R[c] = -(double)acc[c] * ij;
@@ -601,7 +704,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
       if (mode == kModeResidual) {
         v.R[o + c * nn] = R[c];
       } else {
-        const double du = (rkA == 0.0 ? 0.0 : rkA * v.dU[o + c * nn]) + (v.dtp ? *v.dtp : dt) * R[c];
+        const double du = (rkA == 0.0 ? 0.0 : rkA * du_in[c]) + (v.dtp ? *v.dtp : dt) * R[c];
         v.dU[o + c * nn] = du;
         state(v, cur ^ 1)[o + c * nn] = Uin[o + c * nn] + rkB * du;
       }
@@ -609,7 +712,7 @@ __global__ void __launch_bounds__(mix_lanes(NNMAX, NPL))
   };
 #pragma unroll
   for (int s = 0; s < NPL; s++)
-    if (t + s * BS < I.nn) node_update(t + s * BS, acc[s], accm[s]);
+    if (t + s * BS < inn) node_update(t + s * BS, acc[s], accm[s], du_in[s]);
 }
 
 // ------------------------------------------------------------------ diagnostics (FP64)
@@ -678,37 +781,45 @@ hipError_t launch_ic_mixed(const View& v, int cur, int ic, const double* params,
   return hipGetLastError();
 }
 
-template <int NNMAX, int NPL>
+template <int NNMAX, int NPL, bool CART>
 static hipError_t stage_bucket(const View& v, int b, int cur, double dt, double rkA, double rkB, int mode,
                                hipStream_t st) {
   const dim3 grid(v.mix_cnt[b]), block(mix_lanes(NNMAX, NPL));
   if (v.fp32)
-    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, float, false>), grid, block, 0, st, v, v.mix_beg[b], cur,
-                       dt, rkA, rkB, mode);
+    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, float, false, CART>), grid, block, 0, st, v, v.mix_beg[b],
+                       cur, dt, rkA, rkB, mode);
   else if (flux_family(v.vol, v.surf) & 1)
-    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, double, true>), grid, block, 0, st, v, v.mix_beg[b], cur,
-                       dt, rkA, rkB, mode);
+    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, double, true, CART>), grid, block, 0, st, v, v.mix_beg[b],
+                       cur, dt, rkA, rkB, mode);
   else
-    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, double, false>), grid, block, 0, st, v, v.mix_beg[b], cur,
-                       dt, rkA, rkB, mode);
+    hipLaunchKernelGGL((mixed_stage_kernel<NNMAX, NPL, double, false, CART>), grid, block, 0, st, v, v.mix_beg[b],
+                       cur, dt, rkA, rkB, mode);
   return hipGetLastError();
 }
 
 template <int NNMAX>
 static hipError_t stage_bucket_npl(const View& v, int b, int npl, int cur, double dt, double rkA, double rkB,
                                    int mode, hipStream_t st) {
-  return npl == 2 ? stage_bucket<NNMAX, 2>(v, b, cur, dt, rkA, rkB, mode, st)
-                  : stage_bucket<NNMAX, 1>(v, b, cur, dt, rkA, rkB, mode, st);
+  if (v.deform)
+    return npl == 2 ? stage_bucket<NNMAX, 2, false>(v, b, cur, dt, rkA, rkB, mode, st)
+                    : stage_bucket<NNMAX, 1, false>(v, b, cur, dt, rkA, rkB, mode, st);
+  return npl == 2 ? stage_bucket<NNMAX, 2, true>(v, b, cur, dt, rkA, rkB, mode, st)
+                  : stage_bucket<NNMAX, 1, true>(v, b, cur, dt, rkA, rkB, mode, st);
+}
+
+template <bool CART>
+static hipError_t faces_mixed(const View& v, int cur, hipStream_t st) {
+  if (v.fp32)
+    hipLaunchKernelGGL((mixed_face_kernel<float, false, CART>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
+  else if (v.surf >= 4)
+    hipLaunchKernelGGL((mixed_face_kernel<double, true, CART>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
+  else
+    hipLaunchKernelGGL((mixed_face_kernel<double, false, CART>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
+  return hipGetLastError();
 }
 
 hipError_t launch_faces_mixed(const View& v, int cur, hipStream_t st) {
-  if (v.fp32)
-    hipLaunchKernelGGL((mixed_face_kernel<float, false>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
-  else if (v.surf >= 4)
-    hipLaunchKernelGGL((mixed_face_kernel<double, true>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
-  else
-    hipLaunchKernelGGL((mixed_face_kernel<double, false>), dim3(3 * v.E), dim3(64), 0, st, v, cur);
-  return hipGetLastError();
+  return v.deform ? faces_mixed<false>(v, cur, st) : faces_mixed<true>(v, cur, st);
 }
 
 hipError_t launch_stage_mixed_bucket(const View& v, int b, int npl, int cur, double dt, double rkA, double rkB,

@@ -115,3 +115,35 @@ def test_batch_of_plain_and_deformed_boxes(dg, N, fp32):
         b.close()
         for s in ref + mem:
             s.close()
+
+
+@pytest.mark.parametrize("tiles", [0, 63])
+@pytest.mark.parametrize("deform", [False, True])
+@pytest.mark.parametrize("vol,surf", [("ec", "roe"), ("central", "llf"), ("ir", "es"), ("kg", "es_matrix")])
+def test_mixed_stage_forms(dg, orc, vol, surf, deform, tiles):
+    """Per-element orders 1..6 (every cyclic distance and both parities of the node count), plain and
+    deformed boxes, one and two nodes per lane."""
+    from paper_2206_09733_amd import synth
+    c = dict(ex=3, ey=2, ez=5, orders=synth.mixed_orders(30, seed=4, lo=1, hi=6), deform=deform, Ma=0.5, vol=vol,
+             surf=surf)
+    log(f"mixed forms {vol} {surf} {deform} {tiles}")
+    o80 = orc.OracleSolver(**c, precision="fp80")
+    o64 = orc.OracleSolver(**c)
+    g = np.random.Generator(np.random.PCG64(7))
+    U = []
+    for a in np.asarray(c["orders"]).reshape(-1, 3):
+        nn = int(np.prod(a + 1))
+        rho, p = np.exp(g.uniform(-1, 1, (2, nn)) * np.log(1.3))
+        v = g.uniform(-0.5, 0.5, (3, nn))
+        U.append(np.concatenate([rho, *(rho * v), p / 0.4 + 0.5 * rho * (v * v).sum(0)]))
+    U = np.concatenate(U)
+    for o in (o64, o80):
+        o.set_state(U)
+    s = dg.Solver(**c)
+    s.set_tiles(tiles)
+    s.set_state(U)
+    G, A, B = s.residual(), o64.residual(), o80.residual()
+    s.close()
+    scale, e64, eg = np.abs(B).max(), np.abs(A - B).max(), np.abs(G - B).max()
+    log(eg / scale, e64 / scale)
+    assert gate_ok(f"mixed forms {vol}+{surf}", [eg], [e64], [scale])
