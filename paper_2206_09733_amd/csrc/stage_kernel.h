@@ -34,9 +34,16 @@ namespace dg {
 // step 806 -> 657; deformed NS residual 13x11x9 N = 7 191 -> 120; plain Euler 41x36x28 N = 2
 // 322 -> 164; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 821 -> 547.
 //
-// occupancy target of the stage kernel: waves per SIMD the register allocation must allow
-__host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32) {
-  return N == 1 ? (fp32 ? 3 : 2) : (N <= 5 ? (fp32 && N != 3 ? 4 : 3) : 2);
+// occupancy target of the stage kernel: waves per SIMD the register allocation must allow.  Four
+// where that needs no spill: FP32-bulk (but order 3), the plain-box Navier-Stokes kernels of orders 3
+// and 4 without the filtered flux (24^3, N = 4: 511 -> 493 us per RK3 step; the extended surface
+// fluxes would spill).  Spills cost more than the fourth wave gives: deformed Euler at four waves with
+// 9 (N = 4) and 33 spilled (N = 5) took 364 -> 401 and 395 -> 657 us.
+__host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc, int fx, bool sva, bool cart) {
+  if (N == 1) return fp32 ? 3 : 2;
+  if (N > 5) return 2;
+  if (fp32) return N != 3 ? 4 : 3;
+  return cart && visc && !sva && (fx & 2) == 0 && (N == 3 || N == 4) ? 4 : 3;
 }
 
 // global operands of one face point of the stage kernel's face phase: the neighbour's and the
@@ -535,7 +542,7 @@ __device__ __forceinline__ void stage_body(char* lds, const View& v, const int w
 // FX: the flux family (see flux_family); each family is compiled as separate kernels
 template <int N, typename T, bool VISC, int FX, bool SVA, bool CART>
 __global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4))))
+    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, SVA, CART))))
     stage_kernel(View v, int cur, double dt, double rkA, double rkB, int mode) {
   __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
   stage_body<N, T, VISC, FX, SVA, CART>(lds, v, block_element(wg_count(N, v.E)), cur, dt, rkA, rkB, mode);
@@ -544,7 +551,7 @@ __global__ void __launch_bounds__(wg_lanes(N))
 // CART: every member is a plain box; otherwise each member takes the form of its own box
 template <int N, typename T, bool VISC, int FX, bool CART>
 __global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4))))
+    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, false, CART))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
   __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
   static_assert(StageLds<N, T, VISC, true>::bytes <= StageLds<N, T, VISC, CART>::bytes, "one LDS buffer for both");
