@@ -1,5 +1,4 @@
-// grad_body.h -- Navier-Stokes pass A for one element (the body of grad_kernel, shared with the
-// kernel that also forms the spectral-vanishing-viscosity flux of the same element).
+// grad_body.h -- Navier-Stokes pass A for one element (the body of grad_kernel and its batched entry).
 #pragma once
 
 #include <hip/hip_runtime.h>

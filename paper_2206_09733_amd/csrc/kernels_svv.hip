@@ -30,12 +30,16 @@
 #include <vector>
 
 #include "dg_device.h"
-#include "grad_body.h"
 #include "svv.h"
 
 namespace dg {
 
-template <int N>
+// GRAD: the same pass also forms the Navier-Stokes BR1 gradient of g = (v, T) and the face viscous
+// fluxes of the element, in the solver's precision T and with the operations of grad_body: the state,
+// the neighbours' face states and the metric terms are read once and the barriers are shared (as two
+// bodies one after the other in one launch 171 us at 24^3, N = 4, deformed, so 145).
+// CART: plain boxes, whose metric terms are constants.
+template <int N, typename T, bool GRAD, bool CART>
 __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const int cur, const SvvArgs& a) {
   constexpr int n = N + 1, nn = n * n * n, nf = n * n, NT = nthreads_for(N), NW = NT / 64;
   const int t = threadIdx.x;
@@ -52,6 +56,9 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
   double(*sW)[nn] = reinterpret_cast<double(*)[nn]>(sRaw);
   double(*sL)[4][nf] = reinterpret_cast<double(*)[4][nf]>(sRaw + 5 * nn);
   double(*sY)[nn] = reinterpret_cast<double(*)[nn]>(sRaw);
+  __shared__ T sG[4][GRAD ? nn : 1];
+  __shared__ T sJ[6][4][GRAD ? nf : 1];
+  const double Tref = GRAD && sizeof(T) == 4 ? v.p_r / v.rho_r : 0.0;
   for (int x = t; x < n * n; x += NT) {
     sD[x] = v.tab[2 * n + x];
     sQ[x] = a.filt[x];
@@ -74,15 +81,21 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
   };
   double un0[5];
   face_nb(t < 6 * nf ? t : 0, un0);
+  T g0[4] = {0, 0, 0, 0};
   if (act) {
     double u[5];
 #pragma unroll
     for (int c = 0; c < 5; c++) u[c] = Uin[base * 5 + c * nn + t];
-    const double ir = 1.0 / u[0];
+    const double ir = rcp(u[0]);
 #pragma unroll
     for (int c = 0; c < 3; c++) vel[c] = u[1 + c] * ir;
     const double p = g1 * (u[4] - 0.5 * u[0] * (vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2]));
-    const double b = u[0] / p;  // 1 / theta
+    const double b = u[0] * rcp(p);  // 1 / theta
+    if constexpr (GRAD) {
+      gvars(u, v.gamma, Tref, g0);
+#pragma unroll
+      for (int c = 0; c < 4; c++) sG[c][t] = g0[c];
+    }
     th = p * ir;
     rho = u[0];
     sW[0][t] = u[0];
@@ -93,7 +106,10 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
   __syncthreads();
   // the metric terms, requested before the face work so that their latency overlaps it
   double ja[9], J = 1.0, ij = 1.0;
-  if (act) {
+  if constexpr (CART) {
+    J = 0.125 * v.h[0] * v.h[1] * v.h[2];
+    ij = v.cij;
+  } else if (act) {
 #pragma unroll
     for (int c = 0; c < 9; c++) ja[c] = v.Ja[base * 9 + c * nn + t];
     J = v.J[base + t];
@@ -111,21 +127,47 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
     } else {
       face_nb(x, un);
     }
-    const double ir = 1.0 / un[0];
+    const double ir = rcp(un[0]);
     const double w1 = un[1] * ir, w2 = un[2] * ir, w3 = un[3] * ir;
     const double pn = g1 * (un[4] - 0.5 * un[0] * (w1 * w1 + w2 * w2 + w3 * w3));
-    const double b = un[0] / pn;
+    const double b = un[0] * rcp(pn);
+    if constexpr (GRAD) {
+      T gn[4];
+      gvars(un, v.gamma, Tref, gn);
+#pragma unroll
+      for (int c = 0; c < 4; c++) sJ[f][c][q] = (T)0.5 * (gn[c] - sG[c][io]);
+    }
     sL[f][0][q] = 0.5 * (b * w1 - sW[1][io]);
     sL[f][1][q] = 0.5 * (b * w2 - sW[2][io]);
     sL[f][2][q] = 0.5 * (b * w3 - sW[3][io]);
     sL[f][3][q] = 0.5 * (-b - sW[4][io]);
   }
   __syncthreads();
+  if constexpr (GRAD) {
+    if (act) {  // as grad_body: the lifted gradient's flux on the node's faces
+      const T* const gp[4] = {sG[0], sG[1], sG[2], sG[3]};
+      T Fvd[3][4];
+      gradient_and_viscous_flux<n, T, CART>(t, ti, tj, tk, sD, (T)v.iwN, (T)v.iw0, gp, sJ, ja, ij, v, Fvd);
+      T* Fvf = reinterpret_cast<T*>(v.Fvf) + (long)e * 6 * 4 * nf;
+#pragma unroll
+      for (int d = 0; d < 3; d++) {
+        const int qd = d == 0 ? tj + n * tk : (d == 1 ? ti + n * tk : ti + n * tj);
+        if (ii[d] == N) {
+#pragma unroll
+          for (int c = 0; c < 4; c++) Fvf[((2 * d + 1) * 4 + c) * nf + qd] = Fvd[d][c];
+        }
+        if (ii[d] == 0) {
+#pragma unroll
+          for (int c = 0; c < 4; c++) Fvf[((2 * d) * 4 + c) * nf + qd] = Fvd[d][c];
+        }
+      }
+    }
+  }
   // gradients of w2..w5 (lifted), the sensor's share of this node
   double G[4][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
   double sens = 0.0;
   if (act) {
-    const double iwN = 1.0 / sw[N], iw0 = 1.0 / sw[0];
+    const double iwN = v.iwN, iw0 = v.iw0;
     double g2 = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
@@ -149,16 +191,23 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
 #pragma unroll
         for (int c = 0; c < 4; c++) acc[1 + c] -= iw0 * sL[2 * d][c][qd];
       }
+      if constexpr (CART) {
 #pragma unroll
-      for (int x = 0; x < 3; x++) {
+        for (int c = 0; c < 4; c++) G[c][d] = ij * v.cja[d] * acc[1 + c];
+      } else {
 #pragma unroll
-        for (int c = 0; c < 4; c++) G[c][x] += ja[3 * d + x] * acc[1 + c];
+        for (int x = 0; x < 3; x++) {
+#pragma unroll
+          for (int c = 0; c < 4; c++) G[c][x] += ja[3 * d + x] * acc[1 + c];
+        }
       }
     }
+    if constexpr (!CART) {
 #pragma unroll
-    for (int c = 0; c < 4; c++)
+      for (int c = 0; c < 4; c++)
 #pragma unroll
-      for (int x = 0; x < 3; x++) G[c][x] *= ij;
+        for (int x = 0; x < 3; x++) G[c][x] *= ij;
+    }
     sens = sw[ti] * sw[tj] * sw[tk] * J * g2;
   }
   // element sum of the sensor (fixed order: lanes of a wave, then the waves)
@@ -284,6 +333,11 @@ __device__ __forceinline__ void svv_flux_body(const View& v, const int e, const 
   double* Fa = a.Fa + base * 12;
 #pragma unroll
   for (int d = 0; d < 3; d++) {  // Ja read again (this workgroup read it above: an L2 hit)
+    if constexpr (CART) {
+#pragma unroll
+      for (int c = 0; c < 4; c++) Fa[(4 * d + c) * nn + t] = v.cja[d] * F[d][c];
+      continue;
+    }
     const double j0 = v.Ja[base * 9 + (3 * d) * nn + t], j1 = v.Ja[base * 9 + (3 * d + 1) * nn + t],
                  j2 = v.Ja[base * 9 + (3 * d + 2) * nn + t];
 #pragma unroll
@@ -363,30 +417,32 @@ __global__ void __launch_bounds__(nthreads_for(N))
 }
 
 // occupancy target: 4 waves per SIMD up to order 6 (no spills), 3 at order 7
-template <int N>
+template <int N, bool CART>
 __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_per_eu(N <= 6 ? 4 : 3)))
     svv_flux_kernel(View v, int cur, SvvArgs a) {
-  svv_flux_body<N>(v, block_element(v.E), cur, a);
+  svv_flux_body<N, double, false, CART>(v, block_element(v.E), cur, a);
 }
 
-// Navier-Stokes pass A (BR1, in the solver's precision T) and the SVV flux (FP64) of the same
-// element in one workgroup: the second body reads the element's state, metric terms and
-// neighbour traces that the first has just read, from the L2 cache instead of HBM.  The two
-// bodies share no LDS and no results.
+// Navier-Stokes pass A (BR1, in the solver's precision T) and the SVV flux (FP64) in one pass
 template <int N, typename T, bool CART>
 __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_per_eu(N <= 6 ? 4 : 3)))
     grad_svv_kernel(View v, int cur, SvvArgs a) {
-  const int e = block_element(v.E);
-  __shared__ GradLds<N, T, false, 1> lds;
-  grad_body<N, T, false, CART, 1>(lds, v, e, cur);
-  svv_flux_body<N>(v, e, cur, a);
+  svv_flux_body<N, T, true, CART>(v, block_element(v.E), cur, a);
+}
+
+template <int N>
+static hipError_t launch_svv_flux_n(const View& v, int cur, const SvvArgs& a, hipStream_t st) {
+  if (v.deform)
+    hipLaunchKernelGGL((svv_flux_kernel<N, false>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
+  else
+    hipLaunchKernelGGL((svv_flux_kernel<N, true>), dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
+  return hipGetLastError();
 }
 
 template <int N>
 static hipError_t launch_svv_n(const View& v, int cur, const SvvArgs& a, double dt, double b, int mode,
                                hipStream_t st) {
-  hipLaunchKernelGGL(svv_flux_kernel<N>, dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
-  hipError_t err = hipGetLastError();
+  hipError_t err = launch_svv_flux_n<N>(v, cur, a, st);
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(svv_div_kernel<N>, dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a, dt, b, mode);
   return hipGetLastError();
@@ -396,12 +452,6 @@ template <int N>
 static hipError_t launch_svv_div_n(const View& v, int cur, const SvvArgs& a, double dt, double b, int mode,
                                    hipStream_t st) {
   hipLaunchKernelGGL(svv_div_kernel<N>, dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a, dt, b, mode);
-  return hipGetLastError();
-}
-
-template <int N>
-static hipError_t launch_svv_flux_n(const View& v, int cur, const SvvArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(svv_flux_kernel<N>, dim3(v.E), dim3(nthreads_for(N)), 0, st, v, cur, a);
   return hipGetLastError();
 }
 
