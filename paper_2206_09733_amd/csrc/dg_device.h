@@ -646,7 +646,8 @@ template <typename T, bool AX = false>
 __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], const double uR[5],
                                               const double S[3], double gamma, const Ref& R, T F[5],
                                               double& F0d) {
-  // FP64 parts: the central mass flux (F(uL) + F(uR))_rho . S / 2
+  // FP64 parts: the central mass flux (F(uL) + F(uR))_rho . S / 2; its fused operations are written
+  // out, so that every kernel forms the same mass flux bit by bit
   if (kind == 2) {
     const Prim<T> a = make_prim_dev<T>(uL, gamma, R), b = make_prim_dev<T>(uR, gamma, R);
     const double iL = rcp(uL[0]), iR = rcp(uR[0]);
@@ -656,14 +657,14 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
       for (int c = 0; c < 5; c++) F[c] *= (T)S[0];
       F0d *= S[0];
     } else {
-      const double mS = 0.5 * ((uL[1] * iL + uR[1] * iR) * S[0] + (uL[2] * iL + uR[2] * iR) * S[1] +
-                               (uL[3] * iL + uR[3] * iR) * S[2]);
+      const double v1 = fma(uR[1], iR, uL[1] * iL), v2 = fma(uR[2], iR, uL[2] * iL), v3 = fma(uR[3], iR, uL[3] * iL);
+      const double mS = 0.5 * fma(v3, S[2], fma(v2, S[1], v1 * S[0]));
       flux_ec_dev(a, b, (T)S[0], (T)S[1], (T)S[2], mS, R, F, F0d);
     }
     return;
   }
   const double cm = AX ? 0.5 * ((uL[1] + uR[1]) * S[0])
-                       : 0.5 * ((uL[1] + uR[1]) * S[0] + (uL[2] + uR[2]) * S[1] + (uL[3] + uR[3]) * S[2]);
+                       : 0.5 * fma(uL[3] + uR[3], S[2], fma(uL[2] + uR[2], S[1], (uL[1] + uR[1]) * S[0]));
   const T gm1 = (T)(gamma - 1.0);
   T area, n1, n2, n3;
   face_normal<AX>(S, area, n1, n2, n3);
@@ -710,7 +711,7 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
                      (T)((uR[4] - uL[4]) - R.H * (uR[0] - uL[0]))};
 #pragma unroll
     for (int c = 0; c < 5; c++) F[c] = (T)0.5 * area * (Fs[c] - lam * du[c]);
-    F0d = cm - 0.5 * (double)(area * lam) * (uR[0] - uL[0]);
+    F0d = fma(-0.5 * (double)(area * lam), uR[0] - uL[0], cm);
     F[0] = (T)F0d;
     return;
   }

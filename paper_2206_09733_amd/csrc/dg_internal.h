@@ -120,6 +120,23 @@ __host__ __device__ constexpr int wg_lanes(int N) {
   return ((N + 1) * (N + 1) * (N + 1) * wg_elems(N) + 63) / 64 * 64;
 }
 __host__ __device__ constexpr int wg_count(int N, int E) { return (E + wg_elems(N) - 1) / wg_elems(N); }
+// The shape of meshes too small to fill the chip, whose launches are one chain of latencies: one
+// element per workgroup, and lanes for all of its face points at once (orders 3 and 4: one wave more).
+// The results do not depend on the shape: every node and face point is evaluated by itself.
+__host__ __device__ constexpr int small_lanes(int N) {
+  const int nodes = (N + 1) * (N + 1) * (N + 1), faces = 6 * (N + 1) * (N + 1);
+  return ((nodes > faces ? nodes : faces) + 63) / 64 * 64;
+}
+// The orders whose small shape differs, and the most waves of a mesh that takes it: 7 per compute unit,
+// just under the 8 at which order 2 breaks even.  Microseconds of one pass over 8 steps (RK54, a copy of
+// the state included), usual shape -> small: order 1, 336 waves 173 -> 125, 1331 waves 174 -> 155, 3840
+// waves 194 -> 222; order 2, 294 waves 164 -> 141, 1331 194 -> 190, 1859 216 -> 217, 3840 281 -> 345;
+// order 3, 128 waves 156 -> 141, Navier-Stokes 1296 347 -> 330, 3718 486 -> 490; order 4 deformed
+// Navier-Stokes, 540 389 -> 346, 1344 504 -> 459, 3993 712 -> 804.
+constexpr int kSmallMaxOrder = 4, kSmallWaves = 1792;
+__host__ __device__ constexpr bool small_mesh(int N, int E) {
+  return N <= kSmallMaxOrder && (long)E * (small_lanes(N) / 64) <= kSmallWaves;
+}
 
 // Several solvers of one order and precision advanced by one launch: workgroup b of the grid
 // is workgroup b - start[m] of member m (start[m] <= b < start[m+1]); each member's View

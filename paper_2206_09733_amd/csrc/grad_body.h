@@ -12,7 +12,7 @@ namespace dg {
 // BR2 and interior penalty: see face_viscous_br2_ip).  The stage kernel averages the two sides.
 // XV: the BR2 / interior-penalty face fluxes (compiled apart, the BR1 kernels keep their registers).
 // CART: plain boxes, whose metric terms are constants (BR1 reads none).  EW elements per workgroup,
-// starting at e0 = EW wg; the last workgroup repeats the last element in its spare places.
+// (NT lanes) starting at e0 = EW wg; the last workgroup repeats the last element in its spare places.
 template <int N, typename T, bool XV, int EW>
 struct GradLds {
   static constexpr int n = N + 1;
@@ -22,9 +22,9 @@ struct GradLds {
   T Fb[XV ? EW * 6 : 1][4][XV ? n * n : 1];  // broken-gradient face fluxes
 };
 
-template <int N, typename T, bool XV, bool CART, int EW>
+template <int N, typename T, bool XV, bool CART, int EW, int NT>
 __device__ __forceinline__ void grad_body(GradLds<N, T, XV, EW>& lds, const View& v, const int wg, const int cur) {
-  constexpr int n = N + 1, nn = n * n * n, nf = n * n, NN = EW * nn, NT = (NN + 63) / 64 * 64;
+  constexpr int n = N + 1, nn = n * n * n, nf = n * n, NN = EW * nn;
   constexpr int NFP = EW * 6 * nf;
   const int t = threadIdx.x;
   const bool act = t < NN;

@@ -279,10 +279,11 @@ __global__ void ic_kernel(View v, int cur, int ic, IcParams P) {
 
 // ------------------------------------------------------------------ pass A (Navier-Stokes)
 // grad_body (grad_body.h): BR1 gradient and face viscous fluxes of one element
-template <int N, typename T, bool XV, bool CART>
-__global__ void __launch_bounds__(wg_lanes(N)) grad_kernel(View v, int cur) {
-  __shared__ GradLds<N, T, XV, wg_elems(N)> lds;
-  grad_body<N, T, XV, CART, wg_elems(N)>(lds, v, block_element(wg_count(N, v.E)), cur);
+template <int N, typename T, bool XV, bool CART, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N)) grad_kernel(View v, int cur) {
+  constexpr int EW = SMALL ? 1 : wg_elems(N);
+  __shared__ GradLds<N, T, XV, EW> lds;
+  grad_body<N, T, XV, CART, EW, SMALL ? small_lanes(N) : wg_lanes(N)>(lds, v, block_element((v.E + EW - 1) / EW), cur);
 }
 
 // CART: every member is a plain box; otherwise each member takes the form of its own box
@@ -293,9 +294,9 @@ __global__ void __launch_bounds__(wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
   batch_member(B, m, w);
   const View& v = *B.view[m];
   if (CART || (!XV && !v.deform))
-    grad_body<N, T, XV, true, wg_elems(N)>(lds, v, w, B.cur[m]);
+    grad_body<N, T, XV, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m]);
   else
-    grad_body<N, T, XV, false, wg_elems(N)>(lds, v, w, B.cur[m]);
+    grad_body<N, T, XV, false, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m]);
 }
 
 // ------------------------------------------------------------------ diagnostics (FP64)
@@ -533,16 +534,24 @@ static hipError_t geometry_n(const View& v, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int N, typename T, bool SMALL>
+static hipError_t gradient_nts(const View& v, int cur, hipStream_t st) {
+  const dim3 grid(SMALL ? v.E : wg_count(N, v.E)), block(SMALL ? small_lanes(N) : wg_lanes(N));
+  if (v.visc_flux != 0)
+    hipLaunchKernelGGL((grad_kernel<N, T, true, false, SMALL>), grid, block, 0, st, v, cur);
+  else if (v.deform)
+    hipLaunchKernelGGL((grad_kernel<N, T, false, false, SMALL>), grid, block, 0, st, v, cur);
+  else
+    hipLaunchKernelGGL((grad_kernel<N, T, false, true, SMALL>), grid, block, 0, st, v, cur);
+  return hipGetLastError();
+}
+
 template <int N, typename T>
 static hipError_t gradient_nt(const View& v, int cur, hipStream_t st) {
-  const dim3 grid(wg_count(N, v.E)), block(wg_lanes(N));
-  if (v.visc_flux != 0)
-    hipLaunchKernelGGL((grad_kernel<N, T, true, false>), grid, block, 0, st, v, cur);
-  else if (v.deform)
-    hipLaunchKernelGGL((grad_kernel<N, T, false, false>), grid, block, 0, st, v, cur);
-  else
-    hipLaunchKernelGGL((grad_kernel<N, T, false, true>), grid, block, 0, st, v, cur);
-  return hipGetLastError();
+  if constexpr (N <= kSmallMaxOrder) {
+    if (small_mesh(N, v.E)) return gradient_nts<N, T, true>(v, cur, st);
+  }
+  return gradient_nts<N, T, false>(v, cur, st);
 }
 
 template <int N>

@@ -68,9 +68,9 @@ constexpr int imax(int a, int b) { return a > b ? a : b; }
 //       their FP64 mass components);
 //     B (one direction of the volume phase): the direction's metric terms and contravariant
 //       viscous flux, and the exchanged two-point fluxes (FP32-bulk: and their FP64 mass parts).
-template <int N, typename T, bool VISC, bool CART>
+template <int N, typename T, bool VISC, bool CART, int EW>
 struct StageLds {
-  static constexpr int n = N + 1, nf = n * n, EW = wg_elems(N), NN = EW * n * n * n, K = (n - 1) / 2;
+  static constexpr int n = N + 1, nf = n * n, NN = EW * n * n * n, K = (n - 1) / 2;
   static constexpr bool DEV = sizeof(T) == 4;
   static constexpr int S = (int)sizeof(T);
   static constexpr int oD = 0;
@@ -92,12 +92,12 @@ struct StageLds {
 // as it is read) of the same state joins the viscous flux at the nodes, and on the faces the average of both sides'
 // stored values (as the viscous face fluxes; a face node's lane lifts it, the sum taken in the same
 // order from both sides), so the residual holds its term too
-template <int N, typename T, bool VISC, int FX, bool SVA, bool CART>
+template <int N, typename T, bool VISC, int FX, bool SVA, bool CART, int EW, int NT>
 __device__ __forceinline__ void stage_body(char* lds, const View& v, const int wg, const int cur, const double dt,
                                            const double rkA, const double rkB, const int mode) {
   static_assert(!SVA || VISC, "the folded SVV term needs the viscous kernel");
   constexpr int n = N + 1, nn = n * n * n, nf = n * n;
-  constexpr int EW = wg_elems(N), NT = wg_lanes(N), NN = EW * nn;
+  constexpr int NN = EW * nn;  // EW elements and NT lanes per workgroup
   constexpr int K = (n - 1) / 2;           // cyclic distances whose fluxes are exchanged
   constexpr bool HALF = n % 2 == 0;        // the distance n/2, evaluated by both nodes
   constexpr int NFP = EW * 6 * nf;         // face points of the workgroup
@@ -117,7 +117,7 @@ __device__ __forceinline__ void stage_body(char* lds, const View& v, const int w
   const double Tref = DEV ? Rf.por : 0.0;
 
   // LDS (see StageLds)
-  using L = StageLds<N, T, VISC, CART>;
+  using L = StageLds<N, T, VISC, CART, EW>;
   double* sD = reinterpret_cast<double*>(lds + L::oD);
   double* sDh = reinterpret_cast<double*>(lds + L::oDh);
   T(*sP)[NN] = reinterpret_cast<T(*)[NN]>(lds + L::oP);
@@ -539,13 +539,16 @@ __device__ __forceinline__ void stage_body(char* lds, const View& v, const int w
   }
 }
 
-// FX: the flux family (see flux_family); each family is compiled as separate kernels
-template <int N, typename T, bool VISC, int FX, bool SVA, bool CART>
-__global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, SVA, CART))))
+// FX: the flux family (see flux_family); each family is compiled as separate kernels.  SMALL: the
+// shape of small meshes
+template <int N, typename T, bool VISC, int FX, bool SVA, bool CART, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
+    __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, SVA, CART))))
     stage_kernel(View v, int cur, double dt, double rkA, double rkB, int mode) {
-  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
-  stage_body<N, T, VISC, FX, SVA, CART>(lds, v, block_element(wg_count(N, v.E)), cur, dt, rkA, rkB, mode);
+  constexpr int EW = SMALL ? 1 : wg_elems(N);
+  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART, EW>::bytes];
+  stage_body<N, T, VISC, FX, SVA, CART, EW, SMALL ? small_lanes(N) : wg_lanes(N)>(
+      lds, v, block_element((v.E + EW - 1) / EW), cur, dt, rkA, rkB, mode);
 }
 
 // CART: every member is a plain box; otherwise each member takes the form of its own box
@@ -553,15 +556,15 @@ template <int N, typename T, bool VISC, int FX, bool CART>
 __global__ void __launch_bounds__(wg_lanes(N))
     __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, false, CART))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
-  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART>::bytes];
-  static_assert(StageLds<N, T, VISC, true>::bytes <= StageLds<N, T, VISC, CART>::bytes, "one LDS buffer for both");
+  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART, wg_elems(N)>::bytes];
+  static_assert(StageLds<N, T, VISC, true, wg_elems(N)>::bytes <= StageLds<N, T, VISC, CART, wg_elems(N)>::bytes, "one LDS buffer for both");
   int m, w;
   batch_member(B, m, w);
   const View& v = *B.view[m];
   if (CART || !v.deform)
-    stage_body<N, T, VISC, FX, false, true>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+    stage_body<N, T, VISC, FX, false, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
   else
-    stage_body<N, T, VISC, FX, false, CART>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+    stage_body<N, T, VISC, FX, false, CART, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
 }
 
 // ------------------------------------------------------------------ launch helpers
@@ -571,15 +574,25 @@ inline hipError_t stage_ntxc(const View& v, int cur, double dt, double a, double
   const dim3 grid(wg_count(N, v.E)), block(wg_lanes(N));
   if constexpr (FX == 0) {
     if (v.viscous && v.Fa) {
-      hipLaunchKernelGGL((stage_kernel<N, T, true, 0, true, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
+      hipLaunchKernelGGL((stage_kernel<N, T, true, 0, true, CART, false>), grid, block, 0, st, v, cur, dt, a, b, mode);
       return hipGetLastError();
     }
   }
   if (v.Fa) return hipErrorInvalidValue;  // the folded SVV term: Navier-Stokes, standard fluxes
+  if constexpr (N <= kSmallMaxOrder) {
+    if (small_mesh(N, v.E)) {
+      const dim3 g1(v.E), b1(small_lanes(N));
+      if (v.viscous)
+        hipLaunchKernelGGL((stage_kernel<N, T, true, FX, false, CART, true>), g1, b1, 0, st, v, cur, dt, a, b, mode);
+      else
+        hipLaunchKernelGGL((stage_kernel<N, T, false, FX, false, CART, true>), g1, b1, 0, st, v, cur, dt, a, b, mode);
+      return hipGetLastError();
+    }
+  }
   if (v.viscous)
-    hipLaunchKernelGGL((stage_kernel<N, T, true, FX, false, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
+    hipLaunchKernelGGL((stage_kernel<N, T, true, FX, false, CART, false>), grid, block, 0, st, v, cur, dt, a, b, mode);
   else
-    hipLaunchKernelGGL((stage_kernel<N, T, false, FX, false, CART>), grid, block, 0, st, v, cur, dt, a, b, mode);
+    hipLaunchKernelGGL((stage_kernel<N, T, false, FX, false, CART, false>), grid, block, 0, st, v, cur, dt, a, b, mode);
   return hipGetLastError();
 }
 

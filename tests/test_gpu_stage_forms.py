@@ -117,6 +117,29 @@ def test_batch_of_plain_and_deformed_boxes(dg, N, fp32):
             s.close()
 
 
+@pytest.mark.parametrize("N,box", [(1, (7, 16, 16)), (1, (7, 16, 17)), (2, (5, 3, 3)), (2, (9, 10, 21)), (3, (3, 3, 3)),
+                                   (3, (14, 8, 8)), (4, (2, 3, 3)), (4, (9, 11, 7))])
+@pytest.mark.parametrize("fp32,Re,deform", [(False, 0.0, True), (False, 100.0, False), (True, 0.0, True), (True, 100.0, False)])
+def test_small_mesh_shape(dg, N, box, fp32, Re, deform):
+    """Meshes up to 1792 waves step alone in the small launch shape and as members of a batch in the
+    usual one: the states are bitwise the same, below, at and above the line."""
+    c = dict(ex=box[0], ey=box[1], ez=box[2], N=N, Re=Re, deform=deform, Ma=0.3,
+             precision="fp32_bulk" if fp32 else "fp64")
+    log("small shape", c)
+    S = [dg.Solver(**c) for _ in range(3)]
+    for s in S:
+        s.set_ic("tgv")
+    S[0].rk_step(1e-3, 3)
+    b = dg.Batch(S[1:])
+    b.rk_step([1e-3] * 2, 3)
+    U = [s.state() for s in S]
+    b.close()
+    for s in S:
+        s.close()
+    assert np.isfinite(U[0]).all()
+    assert np.array_equal(U[0], U[1]) and np.array_equal(U[0], U[2])
+
+
 @pytest.mark.parametrize("tiles", [0, 63])
 @pytest.mark.parametrize("deform", [False, True])
 @pytest.mark.parametrize("vol,surf", [("ec", "roe"), ("central", "llf"), ("ir", "es"), ("kg", "es_matrix")])
