@@ -107,8 +107,11 @@ __global__ void __launch_bounds__(nthreads_for(N)) gauss_trace_kernel(View v, in
 // BR1's face flux is linear in the gradient, so the traces are taken of the viscous stresses and the
 // heat flux (nine fields; on plain boxes, CART, only the four of the face's direction) and not of the
 // twelve gradient components: 162 -> 92 VGPRs (CART 72).  Plain 24^3, N = 4: 138 -> 52 us.
+// Waves per SIMD: three at order 4, where BR2 would otherwise stop two registers above their 168
+// (32^3: 432 -> 338 us).
 template <int N, int XV, bool CART>
-__global__ void __launch_bounds__(nthreads_for(N)) gauss_grad_kernel(View v, int cur) {
+__global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_per_eu(N == 4 && XV == 1 ? 3 : 1)))
+    gauss_grad_kernel(View v, int cur) {
   static_assert(XV == 0 || !CART, "plain-box form: BR1");
   constexpr int NR = (6 * (N + 1) * (N + 1) + nthreads_for(N) - 1) / nthreads_for(N);  // face points per lane
 
@@ -342,9 +345,11 @@ __global__ void __launch_bounds__(nthreads_for(N)) gauss_grad_kernel(View v, int
 // CART: plain boxes: constant metric terms (none read), face fluxes in a frame rotated to the
 // face's direction.  Bound by HBM: 326 B per node on plain boxes at N = 4 (both sides' traces and
 // face viscous fluxes are 173 of them), 442 on deformed ones; plain 24^3, N = 4 NS 157 -> 109 us,
-// 5.1 TB/s.
+// 5.1 TB/s.  Three waves per SIMD for the deformed viscous form at orders 3 and 4, which would
+// otherwise stop two to four registers above their 168 (32^3, N = 4: 367 -> 319 us).
 template <int N, bool XS, bool VISC, bool CART>
 __global__ void __launch_bounds__(nthreads_for(N))
+    __attribute__((amdgpu_waves_per_eu(VISC && !XS && !CART && (N == 3 || N == 4) ? 3 : 1)))
     gauss_stage_kernel(View v, int cur, double dt, double rkA, double rkB, int mode) {
   constexpr int n = N + 1, nn = n * n * n, nf = n * n, NT = nthreads_for(N);
   const int e = block_element(v.E);
