@@ -1432,14 +1432,17 @@ hipError_t batch_lane(dg_batch* b, int l, const double* dts, int first, int step
 }
 
 // run(l, c, stream) for every lane and chunk c < chunks, the lanes in turn within a chunk; lane 0 on
-// the batch's stream and the others on side streams forked from it and joined to it by events
-// (outside any capture).  Afterwards every member's state has moved to the buffer that `steps` steps
-// lead to.
+// the batch's stream and the others on side streams forked from it and joined to it by events; all on
+// the batch's stream where the caller is capturing it.  Afterwards every member's state has moved to
+// the buffer that `steps` steps lead to.
 hipError_t batch_fork(dg_batch* b, int steps, int chunks, const std::function<hipError_t(int, int, hipStream_t)>& run) {
   const int nl = (int)b->lanes.size();
   hipError_t err = hipSuccess;
   int forked = 0;
-  if (nl > 1 && chunks > 0) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (nl > 1 && b->stream) err = hipStreamIsCapturing(b->stream, &cap);
+  const bool serial = nl == 1 || cap != hipStreamCaptureStatusNone;
+  if (!serial && chunks > 0 && err == hipSuccess) {
     err = hipEventRecord(b->fork, b->stream);
     for (int l = 1; l < nl && err == hipSuccess; l++) {
       err = hipStreamWaitEvent(b->side[l - 1], b->fork, 0);
@@ -1447,7 +1450,7 @@ hipError_t batch_fork(dg_batch* b, int steps, int chunks, const std::function<hi
     }
   }
   for (int c = 0; c < chunks && err == hipSuccess; c++)
-    for (int l = nl - 1; l >= 0 && err == hipSuccess; l--) err = run(l, c, l ? b->side[l - 1] : b->stream);
+    for (int l = nl - 1; l >= 0 && err == hipSuccess; l--) err = run(l, c, serial || !l ? b->stream : b->side[l - 1]);
   for (int l = 1; l <= forked; l++) {  // also after a failed launch: no work of a lane is left unordered
     hipError_t e = hipEventRecord(b->join[l - 1], b->side[l - 1]);
     if (e == hipSuccess) e = hipStreamWaitEvent(b->stream, b->join[l - 1], 0);

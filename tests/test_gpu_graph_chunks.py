@@ -66,3 +66,32 @@ def test_batch_graph_chunks(dg, scheme):
     for s in sets[0] + sets[1]:
         s.close()
     sys.stdout.flush()
+
+
+def test_batch_steps_under_a_callers_capture(dg):
+    """Eager batch steps captured by the caller: the launches of every lane are one chain of the
+    captured stream, and each replay advances the members as eager steps do."""
+    import torch
+    print("batch under a caller's capture", flush=True)
+    kws = [dict(ex=2, ey=3, ez=1 + i % 3, N=2 + i % 3, Ma=0.2, Re=100.0 * (i % 2)) for i in range(6)]
+    sets = [[make(dg, "rk3", False, **k) for k in kws] for _ in range(2)]
+    dts = [1e-3 * (1 + 0.1 * i) for i in range(len(kws))]
+    side = torch.cuda.Stream()
+    A, B = dg.Batch(sets[0], stream=side), dg.Batch(sets[1])
+    A.use_graphs(False)
+    B.use_graphs(False)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        A.rk_step(dts, 2)  # an even number of stages: the state returns to its buffer
+    for _ in range(3):
+        g.replay()
+        torch.ones(1000, device="cuda").sum().item()
+        torch.cuda.synchronize()
+        B.rk_step(dts, 2)
+        for x, y in zip(*sets):
+            assert np.array_equal(x.state(), y.state())
+    A.close()
+    B.close()
+    for s in sets[0] + sets[1]:
+        s.close()
