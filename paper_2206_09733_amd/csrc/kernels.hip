@@ -1,8 +1,10 @@
 // kernels.hip -- gfx950 kernels of the DGSEM residual and low-storage RK3.
 //
-// One workgroup per hexahedral element, one lane per Gauss-Lobatto node (64-wide waves; the
-// (N+1)^3 nodes are padded to a multiple of 64).  The element's state, primitive variables
-// and metric terms are staged in LDS; the split-form two-point fluxes run on the VALU.  The
+// One workgroup per hexahedral element (orders 1 and 2: several elements in one wave), one lane
+// per Gauss-Lobatto node (64-wide waves; the nodes are padded to a multiple of 64).  A node's
+// state and metric terms stay in its lane's registers, its line partners read its primitive
+// variables and one direction's metric from LDS; plain boxes, whose metric is constant, read and
+// hold none.  The split-form two-point fluxes run on the VALU.  The
 // numerical flux on each face is evaluated by both adjacent elements, with identical
 // arguments in identical order (owner's +xi_d side first, the owner's metric as normal), so
 // the flux is single-valued without a face array or a grid-wide barrier; the state

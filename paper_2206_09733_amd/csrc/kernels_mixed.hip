@@ -1,14 +1,13 @@
 // kernels_mixed.hip -- kernels for meshes whose elements carry their own anisotropic orders
 // (N1, N2, N3) (section "Spatial p-adaptation": per-element and per-direction orders; mortar
-// coupling of p-nonconforming faces).  Euler equations, FP64.
+// coupling of p-nonconforming faces).  Euler equations, FP64 and FP32-bulk.
 //
-// One workgroup per element, taken from a work list sorted by node count (largest first) so
-// that the long elements start early; lanes loop over the element's nodes.  Faces whose two
+// A face kernel, one wave per face, then one workgroup per element, in buckets of a work list
+// sorted by node count (largest first) so that the long elements start early.  Faces whose two
 // sides have equal tangential orders are evaluated pointwise; on the others both traces and
 // the owner's normal are interpolated to the Lobatto grid of the larger tangential orders
 // (the mortar), the numerical flux is evaluated there, and the result is L2-projected back onto
-// the element's own face grid.  Both elements of a face evaluate the mortar flux with the same
-// code on the same data; the projections preserve its integral, so the totals are conserved.
+// both elements' face grids; the projections preserve its integral, so the totals are conserved.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -1,6 +1,7 @@
 // stage_kernel.h -- the stage kernel (residual of one element and the fused low-storage RK
 // update) and its batched entry, as templates over the order N, the arithmetic type T, the
-// viscous terms, the flux family FX and the plain-box form CART.  kernels.hip instantiates family
+// viscous terms, the flux family FX, the plain-box form CART and the shape of small meshes SMALL
+// (small_mesh).  kernels.hip instantiates family
 // 0 (and FP32-bulk), kernels_ext.hip the extended families 1..3, so the two compile in parallel.
 #pragma once
 
@@ -44,6 +45,14 @@ __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc
   if (N > 5) return 2;
   if (fp32) return N != 3 ? 4 : 3;
   return cart && visc && !sva && (fx & 2) == 0 && (N == 3 || N == 4) ? 4 : 3;
+}
+// the batched kernels, whose member's View is read through a pointer, hold more registers: four waves
+// spilled 12-22 of the plain-box FP64 Navier-Stokes kernels, and 4-24 of the FP32-bulk kernels that
+// hold both metric forms (24 solves of 12^3 to 20^3, orders 3 to 5, us per RK3 step: plain FP64
+// 3160 -> 3067, deformed FP32-bulk 3875 -> 3538)
+__host__ __device__ constexpr int batch_waves_per_eu(int N, bool fp32, bool visc, int fx, bool cart) {
+  const int w = stage_waves_per_eu(N, fp32, visc, fx, false, false);
+  return w == 4 && !cart ? 3 : w;
 }
 
 // global operands of one face point of the stage kernel's face phase: the neighbour's and the
@@ -554,7 +563,7 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
 // CART: every member is a plain box; otherwise each member takes the form of its own box
 template <int N, typename T, bool VISC, int FX, bool CART>
 __global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(stage_waves_per_eu(N, sizeof(T) == 4, VISC, FX, false, CART))))
+    __attribute__((amdgpu_waves_per_eu(batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, CART))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
   __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART, wg_elems(N)>::bytes];
   static_assert(StageLds<N, T, VISC, true, wg_elems(N)>::bytes <= StageLds<N, T, VISC, CART, wg_elems(N)>::bytes, "one LDS buffer for both");
