@@ -68,7 +68,7 @@ def _profile_rows(kernel, shape):
     return rows
 
 
-def profiled_traffic(kernel="dg::stage_kernel<4, double, true, 0, false>", shape="32768 x 128"):
+def profiled_traffic(kernel="dg::stage_kernel<4, double, true, 0, false, false, false>", shape="32768 x 128"):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary,
     or None when the kernel sources changed since the counters were taken."""
     for cells in _profile_rows(kernel, shape) or []:
@@ -77,7 +77,7 @@ def profiled_traffic(kernel="dg::stage_kernel<4, double, true, 0, false>", shape
     return None
 
 
-def profiled_limiter(kernel="dg::stage_kernel<4, double, true, 0, false>", shape="32768 x 128"):
+def profiled_limiter(kernel="dg::stage_kernel<4, double, true, 0, false, false, false>", shape="32768 x 128"):
     """What binds `kernel`, from the committed rocprofv3 SQ counters (None when stale): VALU busy
     share, mean resident waves per SIMD and the share of wave time spent waiting."""
     for cells in _profile_rows(kernel, shape) or []:
