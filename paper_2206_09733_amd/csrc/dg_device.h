@@ -39,6 +39,13 @@ __device__ __forceinline__ void batch_member(const BatchArgs& B, int& m, int& w)
   w = b - B.start[m];
 }
 
+// A member's View in device memory, which no launch writes, as constant memory: its fields are scalar
+// loads wherever they are used.  Through an ordinary pointer those after a store or barrier would be
+// vector loads into registers (24 solves of 12^3 to 20^3, orders 3 to 5, us per RK3 step: plain FP64
+// 2997 -> 2908, deformed FP32-bulk 3473 -> 3348; 24 FP32-bulk solves of 4^3 to 8^3, four steps 859 -> 840).
+typedef const __attribute__((address_space(4))) View ConstView;
+__device__ __forceinline__ ConstView& const_view(const View* p) { return *(ConstView*)p; }
+
 // node index of reference indices (i_d = id, tangential p, r) on a face normal to d
 template <int n>
 __device__ __forceinline__ int face_node(int d, int id, int p, int r) {
@@ -763,12 +770,12 @@ __device__ __forceinline__ void face_flux_dev(int kind, const double uL[5], cons
 // flux F~v^d = sum_x Ja^d_x Fv_x (momentum 1..3, energy) in each reference direction d.
 //   J grad g = sum_d Ja^d [ D_d g + (1/w_N)(g* - g) at xi_d=+1 - (1/w_0)(g* - g) at xi_d=-1 ]
 // (CART: Ja^d = cja[d] e_d, so the sum over d is one term and ja is not read)
-template <int n, typename T, bool CART>
+template <int n, typename T, bool CART, typename VW>
 __device__ __forceinline__ void gradient_and_viscous_flux(int t, int ti, int tj, int tk,
                                                           const double* sD, T iwN, T iw0,
                                                           const T* const sG[4],
                                                           const T (*sJ)[4][n * n], const double ja[9],
-                                                          double ij, const View& v, T Fvd[3][4]) {
+                                                          double ij, const VW& v, T Fvd[3][4]) {
   constexpr int N = n - 1, nf = n * n;
   const T mu = (T)v.mu, kappa = (T)v.kappa;
   T a[3][4];
@@ -913,8 +920,8 @@ __device__ __forceinline__ void broken_face_fluxes(int t, int ti, int tj, int tk
 // contravariant along this element's Ja^d at io (the owner's after the face normals were made
 // single-valued).  For the interior penalty the neighbour's g and J are read from global memory;
 // both elements evaluate the same expression on the same values, so the penalty is single-valued.
-template <int n, typename T>
-__device__ __forceinline__ void face_viscous_br2_ip(const View& v, int e, int cur, double Tref, int f, int q,
+template <int n, typename T, typename VW>
+__device__ __forceinline__ void face_viscous_br2_ip(const VW& v, int e, int cur, double Tref, int f, int q,
                                                     int io, int lo, int fo, T iwN, T iw0, const T* const sG[4],
                                                     const T (*sJ)[4][n * n], const T (*sFb)[4][n * n],
                                                     T Ff[4]) {

@@ -22,8 +22,8 @@ struct GradLds {
   T Fb[XV ? EW * 6 : 1][4][XV ? n * n : 1];  // broken-gradient face fluxes
 };
 
-template <int N, typename T, bool XV, bool CART, int EW, int NT>
-__device__ __forceinline__ void grad_body(GradLds<N, T, XV, EW>& lds, const View& v, const int wg, const int cur) {
+template <int N, typename T, bool XV, bool CART, int EW, int NT, typename VW>
+__device__ __forceinline__ void grad_body(GradLds<N, T, XV, EW>& lds, const VW& v, const int wg, const int cur) {
   constexpr int n = N + 1, nn = n * n * n, nf = n * n, NN = EW * nn;
   constexpr int NFP = EW * 6 * nf;
   const int t = threadIdx.x;

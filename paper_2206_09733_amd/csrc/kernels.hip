@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
   __shared__ GradLds<N, T, XV, wg_elems(N)> lds;
   int m, w;
   batch_member(B, m, w);
-  const View& v = *B.view[m];
+  ConstView& v = const_view(B.view[m]);
   if (CART || (!XV && !v.deform))
     grad_body<N, T, XV, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m]);
   else

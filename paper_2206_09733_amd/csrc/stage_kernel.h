@@ -46,10 +46,8 @@ __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc
   if (fp32) return N != 3 ? 4 : 3;
   return cart && visc && !sva && (fx & 2) == 0 && (N == 3 || N == 4) ? 4 : 3;
 }
-// the batched kernels, whose member's View is read through a pointer, hold more registers: four waves
-// spilled 12-22 of the plain-box FP64 Navier-Stokes kernels, and 4-24 of the FP32-bulk kernels that
-// hold both metric forms (24 solves of 12^3 to 20^3, orders 3 to 5, us per RK3 step: plain FP64
-// 3160 -> 3067, deformed FP32-bulk 3875 -> 3538)
+// the batched kernels hold a few registers more: four waves would spill 8-12 of the plain-box FP64
+// Navier-Stokes kernels and 4 of the FP32-bulk kernels of order 5 that hold both metric forms
 __host__ __device__ constexpr int batch_waves_per_eu(int N, bool fp32, bool visc, int fx, bool cart) {
   const int w = stage_waves_per_eu(N, fp32, visc, fx, false, false);
   return w == 4 && !cart ? 3 : w;
@@ -101,8 +99,8 @@ struct StageLds {
 // as it is read) of the same state joins the viscous flux at the nodes, and on the faces the average of both sides'
 // stored values (as the viscous face fluxes; a face node's lane lifts it, the sum taken in the same
 // order from both sides), so the residual holds its term too
-template <int N, typename T, bool VISC, int FX, bool SVA, bool CART, int EW, int NT>
-__device__ __forceinline__ void stage_body(char* lds, const View& v, const int wg, const int cur, const double dt,
+template <int N, typename T, bool VISC, int FX, bool SVA, bool CART, int EW, int NT, typename VW>
+__device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg, const int cur, const double dt,
                                            const double rkA, const double rkB, const int mode) {
   static_assert(!SVA || VISC, "the folded SVV term needs the viscous kernel");
   constexpr int n = N + 1, nn = n * n * n, nf = n * n;
@@ -569,7 +567,7 @@ __global__ void __launch_bounds__(wg_lanes(N))
   static_assert(StageLds<N, T, VISC, true, wg_elems(N)>::bytes <= StageLds<N, T, VISC, CART, wg_elems(N)>::bytes, "one LDS buffer for both");
   int m, w;
   batch_member(B, m, w);
-  const View& v = *B.view[m];
+  ConstView& v = const_view(B.view[m]);
   if (CART || !v.deform)
     stage_body<N, T, VISC, FX, false, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
   else
