@@ -30,7 +30,7 @@ namespace dg {
 // is (1, 0, 0).
 //
 // Bound by VALU issue and by the latency of an element's loads, not by HBM (the NS stage at 32^3,
-// N = 4 moves 1.09 GB in 350-360 us).  Measured, RK3 step before -> now, microseconds: deformed
+// N = 4 moves 1.39 GB in 355-365 us).  Measured, RK3 step before -> now, microseconds: deformed
 // NS 32^3 N = 4 FP64 1703 -> 1536, FP32-bulk 1445 -> 1312; deformed Euler RK4 20^3 N = 5 per
 // step 806 -> 657; deformed NS residual 13x11x9 N = 7 191 -> 120; plain Euler 41x36x28 N = 2
 // 322 -> 164; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 821 -> 547.
