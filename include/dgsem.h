@@ -354,7 +354,8 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
  * and joined to it by events: the launch groups are independent and run in up to four lanes.  Like
  * dg_rk_step, the launches of 8, 4, 2 and 1 steps are captured into HIP graphs and replayed when
  * several steps are taken or the same dts recur (a few graphs are kept, keyed by dts, the step
- * count and the members' buffer parities). */
+ * count and the members' buffer parities; all are dropped, after waiting for the batch's stream, when
+ * the FP32 reference state or the tile mask of a member launched on its own has changed). */
 int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps);
 /* enable = 0 disables graph replay of the batch (and drops its graphs). */
 int dg_batch_use_graphs(dg_batch* b, int enable);

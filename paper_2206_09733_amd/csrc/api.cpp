@@ -121,6 +121,9 @@ struct dg_solver {
   hipGraphExec_t graph[4][2] = {};
   double graph_dt[4][2] = {};
   double last_dt = 0.0;
+  // counts the changes of what captured launches hold by value (the FP32 reference state in the View,
+  // the tile mask): a batch compares it before it replays launches of this solver
+  unsigned long long captured = 0;
   // adaptive-step graphs: agraph[p] advances one step from buffer p with the step size chosen on
   // the device for CFL number agraph_cfl[p]
   hipGraphExec_t agraph[2] = {nullptr, nullptr};
@@ -440,6 +443,7 @@ int update_reference(dg_solver* s) {
     return fail(DG_ENONFINITE, "state has no positive finite mean density and pressure");
   s->v.rho_r = h[0] / h[13];
   s->v.p_r = h[14] / h[13];
+  s->captured++;
   return upload_view(s);
 }
 
@@ -1115,6 +1119,7 @@ int dg_solver_set_tiles(dg_solver* s, int tiles) try {
   }
   if (tiles < 0 || tiles >= (1 << dg::kMixBuckets)) return fail(DG_EINVAL, "tiles must be a 6-bit mask");
   s->mix_tiles = tiles;
+  s->captured++;
   drop_graphs(s);
   return DG_OK;
 } catch (...) {
@@ -1164,6 +1169,7 @@ int dg_autotune(dg_solver* s, int* tiles, double* us) try {
   (void)hipEventDestroy(b);
   if (err != hipSuccess) return hip_fail(err, "autotune");
   s->mix_tiles = best_tiles;
+  s->captured++;
   drop_graphs(s);
   if (tiles) *tiles = best_tiles;
   if (us) *us = total;
@@ -1345,6 +1351,9 @@ struct dg_batch {
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;
   std::vector<Graph> graphs;    // most recent last
+  // dg_solver::captured of every solo member when the graphs were captured (their launches hold the
+  // member's View by value; those of a group read it from device memory)
+  std::vector<unsigned long long> captured;
   std::vector<double> last_dts;
   bool use_graphs = true;
   int scheme = DG_RK3_WILLIAMSON;  // the members' common time scheme
@@ -1591,6 +1600,12 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
   const size_t n = b->m.size();
   for (size_t i = 0; i < n; i++)
     if (!std::isfinite(dts[i]) || !(dts[i] > 0)) return fail(DG_EINVAL, "every dt must be positive and finite");
+  std::vector<unsigned long long> captured;
+  for (int i : b->solo) captured.push_back(b->m[i]->captured);
+  if (captured != b->captured) {
+    batch_drop_graphs(b);
+    b->captured = std::move(captured);
+  }
   const bool same = b->last_dts.size() == n && std::equal(dts, dts + n, b->last_dts.begin());
   const bool replay = b->use_graphs && nsteps > 0 && (nsteps > 1 || same);
   b->last_dts.assign(dts, dts + n);
