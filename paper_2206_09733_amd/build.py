@@ -3,6 +3,11 @@
 Every translation unit is compiled by hipcc for gfx950 only.  Packed FP32 instructions are
 disabled for the device code (-packed-fp32-ops); the host pass warns that it does not know
 the feature, which is harmless.
+
+Multiply-adds are fused within an expression only (-ffp-contract=on).  hipcc's default fuses across
+statements after inlining, so the same inlined flux rounds differently in one kernel than in another:
+the batched kernels and those of small meshes, which promise bitwise the states of the usual ones,
+then differed by an ulp (order 3, deformed boxes, surface fluxes of the extended families).
 """
 import concurrent.futures as cf
 import os
@@ -18,7 +23,7 @@ SOURCES = ["kernels.hip", "kernels_ext.hip", "kernels_mixed.hip", "kernels_gauss
            "kernels_halo.hip", "api.cpp", "gll_host.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-ffp-contract=on",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 

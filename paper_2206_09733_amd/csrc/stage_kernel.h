@@ -35,15 +35,22 @@ namespace dg {
 // step 806 -> 657; deformed NS residual 13x11x9 N = 7 191 -> 120; plain Euler 41x36x28 N = 2
 // 322 -> 164; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 821 -> 547.
 //
+// The plain-box FP32-bulk Euler kernels of orders 5 and 6 read the RK update's input state after the
+// last direction (see stage_body): 100 -> 90 VGPRs, five waves per SIMD.
+__host__ __device__ constexpr bool late_state(int N, bool fp32, bool visc, bool cart) {
+  return fp32 && cart && !visc && (N == 5 || N == 6);
+}
 // occupancy target of the stage kernel: waves per SIMD the register allocation must allow.  Four
-// where that needs no spill: FP32-bulk (but order 3), the plain-box Navier-Stokes kernels of orders 3
+// for FP32-bulk (at order 3 with the filtered flux only) and for the plain-box Navier-Stokes kernels of orders 3
 // and 4 without the filtered flux (24^3, N = 4: 511 -> 493 us per RK3 step; the extended surface
 // fluxes would spill).  Spills cost more than the fourth wave gives: deformed Euler at four waves with
-// 9 (N = 4) and 33 spilled (N = 5) took 364 -> 401 and 395 -> 657 us.
+// 9 (N = 4) and 33 spilled (N = 5) took 364 -> 401 and 395 -> 657 us.  Spilled as it is: 4 VGPRs by the
+// deformed FP32-bulk kernel of order 5 with the filtered flux, 6 by its FP64 twin.
 __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc, int fx, bool sva, bool cart) {
   if (N == 1) return fp32 ? 3 : 2;
+  if (late_state(N, fp32, visc, cart)) return 5;
   if (N > 5) return 2;
-  if (fp32) return N != 3 ? 4 : 3;
+  if (fp32) return N != 3 || sva ? 4 : 3;
   return cart && visc && !sva && (fx & 2) == 0 && (N == 3 || N == 4) ? 4 : 3;
 }
 // the batched kernels hold a few registers more: four waves would spill 8-12 of the plain-box FP64
@@ -344,6 +351,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
   }
 
   // ---- volume, one direction at a time
+  constexpr bool kLateState = late_state(N, DEV, VISC, CART);
   const long o5 = base * 5 + tl;
   double u_in[5], du_in[5];
   const T ce = (T)(0.5 / (v.gamma - 1.0)), gm1 = (T)(v.gamma - 1.0);
@@ -370,7 +378,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
     if (d == 2 && act && mode != kModeResidual) {
 #pragma unroll
       for (int c = 0; c < 5; c++) {
-        u_in[c] = Uin[o5 + c * nn];
+        if constexpr (!kLateState) u_in[c] = Uin[o5 + c * nn];
         du_in[c] = rkA == 0.0 ? 0.0 : v.dU[o5 + c * nn];
       }
     }
@@ -535,6 +543,10 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
 #pragma unroll
     for (int c = 0; c < 5; c++) v.R[o5 + c * nn] = R[c];
     return;
+  }
+  if constexpr (kLateState) {
+#pragma unroll
+    for (int c = 0; c < 5; c++) u_in[c] = Uin[o5 + c * nn];
   }
   double* __restrict__ Uout = v.U[cur ^ 1];
   const double h = v.dtp ? *v.dtp : dt;
