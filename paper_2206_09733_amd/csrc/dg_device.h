@@ -117,23 +117,26 @@ __device__ __forceinline__ Prim<T> make_prim(const double u[5], double gamma) {
 // short.  Three tiers by u: below 1e-4 (neighbouring nodes of a resolved flow) four terms; below
 // 0.04 (ratios up to 1.5) twelve terms, truncated below 1e-18; beyond, the argument is halved until
 // they suffice (a library logarithm there would cost every kernel its registers: 126 -> 154 in
-// the mixed-order stage kernel).  A wave takes the later tiers only if one of its lanes needs them, and each lane's tier depends on its own
+// the mixed-order stage kernel).  Relative error about 1e-15 up to ratios of 1e300.  A wave takes the
+// later tiers only if one of its lanes needs them, and each lane's tier depends on its own
 // operands alone.  Without the two logarithms per node of the (ln x_a - ln x_b) form, the nodes
 // keep five primitive variables instead of seven.
 constexpr double kSmallU = 1e-4;
 __device__ __forceinline__ double atanh_ratio(double xa, double xb, double u) {
-  double k = 1.0;
+  // two values of the wrong sign have no logarithmic mean
+  double k = xa + xb > 0.0 ? 1.0 : __builtin_nan("");
   if (u >= 0.04) {
-    // tanh(x/2) = tanh x / (1 + c), c = sqrt(1 - u): S(u) = 2 g S(g^2 u), g = 1/(1 + c); at first
-    // 1 - u = 4 x_a x_b / (x_a + x_b)^2, without cancellation.  Eight halvings reach ratios of 1e22.
-    const double s = xa + xb;
-    double w = 4.0 * xa * xb * rcp(s * s);
+    // tanh(x/2) = tanh x / (1 + c), c = sqrt(1 - u): S(u) = 2 g S(g^2 u), g = 1/(1 + c).  w = 1 - u is
+    // formed without cancellation: 4 x_a x_b / (x_a + x_b)^2 at first, then 1 - g^2 u = 2 c g.  Eleven
+    // halvings bring every ratio that a double can hold below 0.04.
+    const double r = rcp(xa + xb);
+    double w = 4.0 * (xa * r) * (xb * r);
 #pragma unroll 1
-    for (int i = 0; i < 8 && u >= 0.04; i++) {
-      const double g = rcp(1.0 + w * rsq(w));
+    for (int i = 0; i < 11 && u >= 0.04; i++) {
+      const double c = w * rsq(w), g = rcp(1.0 + c);
       k *= 2.0 * g;
       u *= g * g;
-      w = 1.0 - u;
+      w = 2.0 * c * g;
     }
   }
   double s = 1.0 / 23.0;
