@@ -74,28 +74,36 @@ constexpr int imax(int a, int b) { return a > b ? a : b; }
 
 // LDS of a stage workgroup (byte offsets):
 //   D, Dhat; the primitive variables rho, v1, v2, v3, beta (FP32-bulk: deviations of rho, beta);
-//   FP32-bulk: FP64 velocities for the mass flux, and the face fluxes, which it lifts beside each
-//   direction's volume sum (they largely cancel; in FP64 the order does not matter and the lifts
-//   are taken with phase A);
+//   FP32-bulk: FP64 velocities for the mass flux;
+//   FP32-bulk and orders 1 and 2: the face fluxes, lifted beside each direction's volume sum (the two
+//   largely cancel; the other kernels take the lifts with phase A: see lifts_beside_volume);
 //   one region that holds each phase's arrays in turn:
 //     A (face phase): with viscosity temperature and half jumps of g; the face fluxes (FP32-bulk:
 //       their FP64 mass components);
 //     B (one direction of the volume phase): the direction's metric terms and contravariant
 //       viscous flux, and the exchanged two-point fluxes (FP32-bulk: and their FP64 mass parts).
+// Whether the lifts of the face fluxes join each direction's volume sum or are summed first.  With
+// the lifts summed first the FP64 residual of random states was further from the long-double oracle's
+// at low orders (central volume flux, deformed boxes, rms: order 1 1.12 and order 2 1.03 times that of
+// lifts beside the volume from a pair list; so 1.07 and 1.02; below 1.005 from order 3 on).  The
+// fluxes' LDS outlives phase A then: order 2 Euler 6.6 -> 10 KB, times within 3%.
+__host__ __device__ constexpr bool lifts_beside_volume(int N, bool fp32) { return fp32 || N <= 2; }
+
 template <int N, typename T, bool VISC, bool CART, int EW>
 struct StageLds {
   static constexpr int n = N + 1, nf = n * n, NN = EW * n * n * n, K = (n - 1) / 2;
   static constexpr bool DEV = sizeof(T) == 4;
+  static constexpr bool BESIDE = lifts_beside_volume(N, DEV);
   static constexpr int S = (int)sizeof(T);
   static constexpr int oD = 0;
   static constexpr int oDh = oD + nf * 8;
   static constexpr int oP = align16(oDh + (VISC ? nf * 8 : 0));
   static constexpr int oVd = align16(oP + 5 * NN * S);
   static constexpr int oFk = align16(oVd + (DEV ? 3 * NN * 8 : 0));
-  static constexpr int oR = align16(oFk + (DEV ? EW * 30 * nf * S : 0));
+  static constexpr int oR = align16(oFk + (BESIDE ? EW * 30 * nf * S : 0));
   static constexpr int bT = VISC ? align16(NN * S) : 0;
   static constexpr int bJ = VISC ? align16(EW * 24 * nf * S) : 0;
-  static constexpr int bytesA = bT + bJ + EW * (DEV ? 6 : 30) * nf * 8;
+  static constexpr int bytesA = bT + bJ + EW * (DEV ? 6 : (BESIDE ? 0 : 30)) * nf * 8;
   static constexpr int bM = CART ? 0 : 3 * NN * 8;
   static constexpr int bV = VISC ? align16(4 * NN * S) : 0;
   static constexpr int bX = DEV ? K * NN * 8 + 4 * K * NN * 4 : 5 * K * NN * 8;
@@ -139,7 +147,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
   T(*sFk)[5][nf] = reinterpret_cast<T(*)[5][nf]>(lds + L::oFk);
   T* sT = reinterpret_cast<T*>(lds + L::oR);
   T(*sJ)[4][nf] = reinterpret_cast<T(*)[4][nf]>(lds + L::oR + L::bT);
-  double(*sFa)[5][nf] = reinterpret_cast<double(*)[5][nf]>(lds + L::oR + L::bT + L::bJ);
+  double(*sFa)[5][nf] = reinterpret_cast<double(*)[5][nf]>(lds + (L::BESIDE ? L::oFk : L::oR + L::bT + L::bJ));
   double(*sF0)[nf] = reinterpret_cast<double(*)[nf]>(lds + L::oR + L::bT + L::bJ);
   double(*sM)[NN] = reinterpret_cast<double(*)[NN]>(lds + L::oR);
   T(*sFv)[NN] = reinterpret_cast<T(*)[NN]>(lds + L::oR + L::bM);
@@ -322,7 +330,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
   double acc0d = 0.0;  // FP32-bulk mass accumulator
   T Fvd[3][4];         // contravariant viscous flux of this node
   if (act) {
-    // lift of the face fluxes (FP32-bulk: of their FP64 mass components)
+    // lift of the face fluxes (FP32-bulk: of their FP64 mass components; the others beside the volume)
 #pragma unroll
     for (int d = 0; d < 3; d++) {
       const int id = ii[d], ff = 6 * el + 2 * d;
@@ -330,7 +338,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
       if (id == N) {
         if constexpr (DEV) {
           acc0d += v.iwN * sF0[ff + 1][line];
-        } else {
+        } else if constexpr (!L::BESIDE) {
 #pragma unroll
           for (int c = 0; c < 5; c++) acc[c] += iwN * sFa[ff + 1][c][line];
         }
@@ -338,7 +346,7 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
       if (id == 0) {
         if constexpr (DEV) {
           acc0d -= v.iw0 * sF0[ff][line];
-        } else {
+        } else if constexpr (!L::BESIDE) {
 #pragma unroll
           for (int c = 0; c < 5; c++) acc[c] -= iw0 * sFa[ff][c][line];
         }
@@ -528,6 +536,18 @@ __device__ __forceinline__ void stage_body(char* lds, const VW& v, const int wg,
         acc[1 + c1] += CART ? sc * pa[2] : pa[2];
         acc[1 + c2] += CART ? sc * pa[3] : pa[3];
         acc[4] += CART ? sc * pa[4] : pa[4];
+        if constexpr (L::BESIDE) {
+          const int ff = 6 * el + 2 * d;
+          const int line = d == 0 ? tj + n * tk : (d == 1 ? ti + n * tk : ti + n * tj);
+          if (id == N) {
+#pragma unroll
+            for (int c = 0; c < 5; c++) acc[c] += iwN * sFa[ff + 1][c][line];
+          }
+          if (id == 0) {
+#pragma unroll
+            for (int c = 0; c < 5; c++) acc[c] -= iw0 * sFa[ff][c][line];
+          }
+        }
       }
     }
   }
