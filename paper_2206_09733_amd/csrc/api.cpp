@@ -1329,7 +1329,7 @@ struct dg_batch {
     bool fp32, visc;
     int fx;   // flux family
     bool xv;  // BR2 or interior-penalty face viscous flux
-    bool deform;  // some member lies on a deformed box (the kernels of plain boxes read no metric)
+    dg::BoxForm form;  // the members' boxes (the kernels of plain boxes read no metric)
     std::vector<int> idx;
   };
   struct Graph {
@@ -1390,10 +1390,10 @@ hipError_t batch_group_stage(dg_batch* b, const dg_batch::Group& g, const double
     B.start[j + 1] = B.start[j] + dg::wg_count(g.N, (int)s->E);
   }
   if (g.visc) {
-    hipError_t e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.deform, st);
+    hipError_t e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.form, st);
     if (e != hipSuccess) return e;
   }
-  return dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.deform, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
+  return dg::launch_stage_batch(B, g.N, g.fp32, g.visc, g.form, g.fx, kRk[b->scheme].A[k], kRk[b->scheme].B[k],
                                 dg::kModeRK, st);
 }
 
@@ -1540,16 +1540,17 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
     }
     const bool fp32 = s->v.fp32 != 0, visc = s->v.viscous != 0;
     const int fx = dg::flux_family(s->v.vol, s->v.surf);
-    const bool xv = s->v.viscous && s->v.visc_flux != 0, deform = s->v.deform != 0;
+    const bool xv = s->v.viscous && s->v.visc_flux != 0;
+    const dg::BoxForm form = s->v.deform ? dg::BoxForm::deformed : dg::BoxForm::plain;
     dg_batch::Group* g = nullptr;
     for (auto& x : b->groups)
       if (x.N == s->v.N && x.fp32 == fp32 && x.visc == visc && x.fx == fx && x.xv == xv && (int)x.idx.size() < dg::kMaxBatch)
         g = &x;
     if (!g) {
-      b->groups.push_back({s->v.N, fp32, visc, fx, xv, false, {}});
+      b->groups.push_back({s->v.N, fp32, visc, fx, xv, form, {}});
       g = &b->groups.back();
     }
-    g->deform = g->deform || deform;
+    if (g->form != form) g->form = dg::BoxForm::both;
     g->idx.push_back(i);
   }
   long long blocks = 0;

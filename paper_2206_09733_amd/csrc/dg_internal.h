@@ -138,6 +138,10 @@ __host__ __device__ constexpr bool small_mesh(int N, int E) {
   return N <= kSmallMaxOrder && (long)E * (small_lanes(N) / 64) <= kSmallWaves;
 }
 
+// The boxes of a launch's members: plain ones (constant metric terms), deformed ones, or some of each
+// (every member then takes the form of its own box).
+enum class BoxForm { plain, deformed, both };
+
 // Several solvers of one order and precision advanced by one launch: workgroup b of the grid
 // is workgroup b - start[m] of member m (start[m] <= b < start[m+1]); each member's View
 // lives in device memory (a copy inside the member's own buffer).
@@ -161,10 +165,10 @@ hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rk
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st);
 hipError_t launch_diag_final(const View& v, int parts, hipStream_t st);  // partials -> diag, fixed order
 // batched Navier-Stokes gradient pass and stage of members of order N (all viscous, or all
-// inviscid for the stage), FP32-bulk or FP64; deform: some member lies on a deformed box
-hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, bool deform,
+// inviscid for the stage), FP32-bulk or FP64
+hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, BoxForm form,
                                  hipStream_t st);  // xv: BR2/IP
-hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, bool deform, int fx, double rkA,
+hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, BoxForm form, int fx, double rkA,
                               double rkB, int mode, hipStream_t st);  // fx: the members' flux family
 // Gauss-Legendre nodes: face traces of U[cur], then the weak-form residual / RK stage
 hipError_t launch_stage_gauss(const View& v, int cur, double dt, double rkA, double rkB, int mode, hipStream_t st);
@@ -180,7 +184,7 @@ hipError_t launch_step_size(const View& v, int cur, double cfl, double hmin, dou
 // the extended flux families 1..3 (FP64), in kernels_ext.hip; called by the two launchers above
 hipError_t launch_stage_ext(const View& v, int fx, int cur, double dt, double rkA, double rkB, int mode,
                             hipStream_t st);
-hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, bool deform, int fx, double rkA, double rkB,
+hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, BoxForm form, int fx, double rkA, double rkB,
                                   int mode, hipStream_t st);
 
 // mixed-order meshes (kernels_mixed.hip).  The stage runs one launch per bucket of elements

@@ -288,17 +288,22 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N)) grad_ker
   grad_body<N, T, XV, CART, EW, SMALL ? small_lanes(N) : wg_lanes(N)>(lds, v, block_element((v.E + EW - 1) / EW), cur);
 }
 
-// CART: every member is a plain box; otherwise each member takes the form of its own box
-template <int N, typename T, bool XV, bool CART>
+// FORM: the members' boxes (see stage_batch_kernel); XV: the general form only
+template <int N, typename T, bool XV, BoxForm FORM>
 __global__ void __launch_bounds__(wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
-  __shared__ GradLds<N, T, XV, wg_elems(N)> lds;
+  constexpr int EW = wg_elems(N), NT = wg_lanes(N);
+  __shared__ GradLds<N, T, XV, EW> lds;
   int m, w;
   batch_member(B, m, w);
   ConstView& v = const_view(B.view[m]);
-  if (CART || (!XV && !v.deform))
-    grad_body<N, T, XV, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m]);
-  else
-    grad_body<N, T, XV, false, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m]);
+  if constexpr (FORM != BoxForm::both) {
+    grad_body<N, T, XV, FORM == BoxForm::plain, EW, NT>(lds, v, w, B.cur[m]);
+  } else {
+    if (v.deform)
+      grad_body<N, T, XV, false, EW, NT>(lds, v, w, B.cur[m]);
+    else
+      grad_body<N, T, XV, true, EW, NT>(lds, v, w, B.cur[m]);
+  }
 }
 
 // ------------------------------------------------------------------ diagnostics (FP64)
@@ -614,28 +619,30 @@ hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rk
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st) { DG_DISPATCH(diag_n, v, cur, st) }
 
 template <int N, typename T>
-static hipError_t gradient_batch_nt(const BatchArgs& B, bool xv, bool deform, hipStream_t st) {
+static hipError_t gradient_batch_nt(const BatchArgs& B, bool xv, BoxForm form, hipStream_t st) {
   const dim3 grid(B.start[B.n]), block(wg_lanes(N));
   if (xv)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, true, false>), grid, block, 0, st, B);
-  else if (deform)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, false>), grid, block, 0, st, B);
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, true, BoxForm::deformed>), grid, block, 0, st, B);
+  else if (form == BoxForm::plain)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::plain>), grid, block, 0, st, B);
+  else if (form == BoxForm::deformed)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::deformed>), grid, block, 0, st, B);
   else
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, true>), grid, block, 0, st, B);
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::both>), grid, block, 0, st, B);
   return hipGetLastError();
 }
 
 template <int N>
-static hipError_t gradient_batch_n(const BatchArgs& B, bool fp32, bool xv, bool deform, hipStream_t st) {
-  return fp32 ? gradient_batch_nt<N, float>(B, xv, deform, st) : gradient_batch_nt<N, double>(B, xv, deform, st);
+static hipError_t gradient_batch_n(const BatchArgs& B, bool fp32, bool xv, BoxForm form, hipStream_t st) {
+  return fp32 ? gradient_batch_nt<N, float>(B, xv, form, st) : gradient_batch_nt<N, double>(B, xv, form, st);
 }
 
 template <int N>
-static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, bool deform, int fx, double a, double b,
+static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, BoxForm form, int fx, double a, double b,
                                 int mode, hipStream_t st) {
-  if (fp32) return stage_batch_nt<N, float, 0>(B, visc, deform, a, b, mode, st);
-  if (fx != 0) return launch_stage_batch_ext(B, N, visc, deform, fx, a, b, mode, st);
-  return stage_batch_nt<N, double, 0>(B, visc, deform, a, b, mode, st);
+  if (fp32) return stage_batch_nt<N, float, 0>(B, visc, form, a, b, mode, st);
+  if (fx != 0) return launch_stage_batch_ext(B, N, visc, form, fx, a, b, mode, st);
+  return stage_batch_nt<N, double, 0>(B, visc, form, a, b, mode, st);
 }
 
 #define DG_DISPATCH_N(NV, FN, ...)                    \
@@ -650,16 +657,16 @@ static hipError_t stage_batch_n(const BatchArgs& B, bool fp32, bool visc, bool d
     default: return hipErrorInvalidValue;             \
   }
 
-hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, bool deform, hipStream_t st) {
+hipError_t launch_gradient_batch(const BatchArgs& B, int N, bool fp32, bool xv, BoxForm form, hipStream_t st) {
   if (B.n < 1 || B.n > kMaxBatch) return hipErrorInvalidValue;
-  DG_DISPATCH_N(N, gradient_batch_n, B, fp32, xv, deform, st)
+  DG_DISPATCH_N(N, gradient_batch_n, B, fp32, xv, form, st)
 }
 
-hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, bool deform, int fx, double rkA,
+hipError_t launch_stage_batch(const BatchArgs& B, int N, bool fp32, bool visc, BoxForm form, int fx, double rkA,
                               double rkB, int mode, hipStream_t st) {
   if (B.n < 1 || B.n > kMaxBatch) return hipErrorInvalidValue;
   if (fx < 0 || fx > 3 || (fp32 && fx != 0)) return hipErrorInvalidValue;
-  DG_DISPATCH_N(N, stage_batch_n, B, fp32, visc, deform, fx, rkA, rkB, mode, st)
+  DG_DISPATCH_N(N, stage_batch_n, B, fp32, visc, form, fx, rkA, rkB, mode, st)
 }
 
 hipError_t launch_adapt_reset(const View& v, hipStream_t st) {

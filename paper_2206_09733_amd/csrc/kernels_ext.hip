@@ -21,12 +21,12 @@ static hipError_t stage_ext_n(const View& v, int fx, int cur, double dt, double 
 }
 
 template <int N>
-static hipError_t stage_batch_ext_n(const BatchArgs& B, bool visc, bool deform, int fx, double a, double b,
+static hipError_t stage_batch_ext_n(const BatchArgs& B, bool visc, BoxForm form, int fx, double a, double b,
                                     int mode, hipStream_t st) {
   switch (fx) {
-    case 1: return stage_batch_nt<N, double, 1>(B, visc, deform, a, b, mode, st);
-    case 2: return stage_batch_nt<N, double, 2>(B, visc, deform, a, b, mode, st);
-    case 3: return stage_batch_nt<N, double, 3>(B, visc, deform, a, b, mode, st);
+    case 1: return stage_batch_nt<N, double, 1>(B, visc, form, a, b, mode, st);
+    case 2: return stage_batch_nt<N, double, 2>(B, visc, form, a, b, mode, st);
+    case 3: return stage_batch_nt<N, double, 3>(B, visc, form, a, b, mode, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -48,9 +48,9 @@ hipError_t launch_stage_ext(const View& v, int fx, int cur, double dt, double rk
   DG_EXT_DISPATCH(v.N, stage_ext_n, v, fx, cur, dt, rkA, rkB, mode, st)
 }
 
-hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, bool deform, int fx, double rkA, double rkB,
+hipError_t launch_stage_batch_ext(const BatchArgs& B, int N, bool visc, BoxForm form, int fx, double rkA, double rkB,
                                   int mode, hipStream_t st) {
-  DG_EXT_DISPATCH(N, stage_batch_ext_n, B, visc, deform, fx, rkA, rkB, mode, st)
+  DG_EXT_DISPATCH(N, stage_batch_ext_n, B, visc, form, fx, rkA, rkB, mode, st)
 }
 
 }  // namespace dg

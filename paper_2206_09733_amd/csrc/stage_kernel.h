@@ -53,11 +53,14 @@ __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc
   if (fp32) return N != 3 || sva ? 4 : 3;
   return cart && visc && !sva && (fx & 2) == 0 && (N == 3 || N == 4) ? 4 : 3;
 }
-// the batched kernels hold a few registers more: four waves would spill 8-12 of the plain-box FP64
-// Navier-Stokes kernels and 4 of the FP32-bulk kernels of order 5 that hold both metric forms
-__host__ __device__ constexpr int batch_waves_per_eu(int N, bool fp32, bool visc, int fx, bool cart) {
-  const int w = stage_waves_per_eu(N, fp32, visc, fx, false, false);
-  return w == 4 && !cart ? 3 : w;
+// The batched kernels hold a few registers more (the member's View and start).  FP64: three waves, four
+// would spill 6-8 of the plain-box Navier-Stokes kernels.  Those that hold both metric forms: three, two at order 1
+// (at one more, 6 to 12 VGPRs of FP32-bulk kernels spilled).
+__host__ __device__ constexpr int batch_waves_per_eu(int N, bool fp32, bool visc, int fx, BoxForm form) {
+  const int w = stage_waves_per_eu(N, fp32, visc, fx, false, form == BoxForm::plain);
+  if (form == BoxForm::both) return N == 1 ? 2 : (w > 3 ? 3 : w);
+  if (!fp32 && N == 2 && !visc && form == BoxForm::plain) return 4;  // (130 VGPRs without: 306 -> 336 us at 16 x 10^3)
+  return !fp32 && w > 3 ? 3 : w;
 }
 
 // global operands of one face point of the stage kernel's face phase: the neighbour's and the
@@ -590,20 +593,27 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
       lds, v, block_element((v.E + EW - 1) / EW), cur, dt, rkA, rkB, mode);
 }
 
-// CART: every member is a plain box; otherwise each member takes the form of its own box
-template <int N, typename T, bool VISC, int FX, bool CART>
+// FORM: the members' boxes.  Deformed members have kernels of their own since the registers of both forms
+// in one kernel spilled: 16 solves of 10^3, N = 4 Navier-Stokes FP64, deformed, 3791 us for four RK3 steps
+// (3166 so, 3534 with one general form before there was a plain one).
+template <int N, typename T, bool VISC, int FX, BoxForm FORM>
 __global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, CART))))
+    __attribute__((amdgpu_waves_per_eu(batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, FORM))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
-  __shared__ __align__(16) char lds[StageLds<N, T, VISC, CART, wg_elems(N)>::bytes];
-  static_assert(StageLds<N, T, VISC, true, wg_elems(N)>::bytes <= StageLds<N, T, VISC, CART, wg_elems(N)>::bytes, "one LDS buffer for both");
+  constexpr int EW = wg_elems(N), NT = wg_lanes(N);
+  __shared__ __align__(16) char lds[StageLds<N, T, VISC, FORM == BoxForm::plain, EW>::bytes];
+  static_assert(StageLds<N, T, VISC, true, EW>::bytes <= StageLds<N, T, VISC, false, EW>::bytes, "one LDS buffer for both");
   int m, w;
   batch_member(B, m, w);
   ConstView& v = const_view(B.view[m]);
-  if (CART || !v.deform)
-    stage_body<N, T, VISC, FX, false, true, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
-  else
-    stage_body<N, T, VISC, FX, false, CART, wg_elems(N), wg_lanes(N)>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+  if constexpr (FORM != BoxForm::both) {
+    stage_body<N, T, VISC, FX, false, FORM == BoxForm::plain, EW, NT>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+  } else {
+    if (v.deform)
+      stage_body<N, T, VISC, FX, false, false, EW, NT>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+    else
+      stage_body<N, T, VISC, FX, false, true, EW, NT>(lds, v, w, B.cur[m], B.dt[m], rkA, rkB, mode);
+  }
 }
 
 // ------------------------------------------------------------------ launch helpers
@@ -641,21 +651,24 @@ inline hipError_t stage_ntx(const View& v, int cur, double dt, double a, double 
                   : stage_ntxc<N, T, FX, true>(v, cur, dt, a, b, mode, st);
 }
 
-template <int N, typename T, int FX, bool CART>
-inline hipError_t stage_batch_ntc(const BatchArgs& B, bool visc, double a, double b, int mode, hipStream_t st) {
+template <int N, typename T, int FX, BoxForm FORM>
+inline hipError_t stage_batch_ntf(const BatchArgs& B, bool visc, double a, double b, int mode, hipStream_t st) {
   const dim3 grid(B.start[B.n]), block(wg_lanes(N));
   if (visc)
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX, CART>), grid, block, 0, st, B, a, b, mode);
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX, FORM>), grid, block, 0, st, B, a, b, mode);
   else
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX, CART>), grid, block, 0, st, B, a, b, mode);
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX, FORM>), grid, block, 0, st, B, a, b, mode);
   return hipGetLastError();
 }
 
 template <int N, typename T, int FX>
-inline hipError_t stage_batch_nt(const BatchArgs& B, bool visc, bool deform, double a, double b, int mode,
+inline hipError_t stage_batch_nt(const BatchArgs& B, bool visc, BoxForm form, double a, double b, int mode,
                                  hipStream_t st) {
-  return deform ? stage_batch_ntc<N, T, FX, false>(B, visc, a, b, mode, st)
-                : stage_batch_ntc<N, T, FX, true>(B, visc, a, b, mode, st);
+  switch (form) {
+    case BoxForm::plain: return stage_batch_ntf<N, T, FX, BoxForm::plain>(B, visc, a, b, mode, st);
+    case BoxForm::deformed: return stage_batch_ntf<N, T, FX, BoxForm::deformed>(B, visc, a, b, mode, st);
+    default: return stage_batch_ntf<N, T, FX, BoxForm::both>(B, visc, a, b, mode, st);
+  }
 }
 
 }  // namespace dg
