@@ -1330,6 +1330,7 @@ struct dg_batch {
     int fx;   // flux family
     bool xv;  // BR2 or interior-penalty face viscous flux
     dg::BoxForm form;  // the members' boxes (the kernels of plain boxes read no metric)
+    bool small;        // launches in the shape of small meshes
     std::vector<int> idx;
   };
   struct Graph {
@@ -1381,13 +1382,14 @@ hipError_t batch_group_stage(dg_batch* b, const dg_batch::Group& g, const double
   dg::BatchArgs B;
   std::memset(&B, 0, sizeof(B));
   B.n = (int)g.idx.size();
+  B.small = g.small;
   B.start[0] = 0;
   for (int j = 0; j < B.n; j++) {
     dg_solver* s = b->m[g.idx[j]];
     B.view[j] = s->dev_view;
     B.cur[j] = s->cur ^ par;
     B.dt[j] = dts[g.idx[j]];
-    B.start[j + 1] = B.start[j] + dg::wg_count(g.N, (int)s->E);
+    B.start[j + 1] = B.start[j] + (g.small ? (int)s->E : dg::wg_count(g.N, (int)s->E));
   }
   if (g.visc) {
     hipError_t e = dg::launch_gradient_batch(B, g.N, g.fp32, g.xv, g.form, st);
@@ -1547,7 +1549,7 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
       if (x.N == s->v.N && x.fp32 == fp32 && x.visc == visc && x.fx == fx && x.xv == xv && (int)x.idx.size() < dg::kMaxBatch)
         g = &x;
     if (!g) {
-      b->groups.push_back({s->v.N, fp32, visc, fx, xv, form, {}});
+      b->groups.push_back({s->v.N, fp32, visc, fx, xv, form, false, {}});
       g = &b->groups.back();
     }
     if (g->form != form) g->form = dg::BoxForm::both;
@@ -1559,6 +1561,9 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
     for (int i : g.idx) blocks += b->m[i]->E;
     if (blocks >= (1LL << 31)) return fail(DG_EINVAL, "a batched launch would exceed 2^31 workgroups");
   }
+  long long waves = 0;  // of all members that run together
+  for (const dg_solver* s : b->m) waves += s->E * ((s->ntot / s->E + 63) / 64);
+  for (auto& g : b->groups) g.small = g.N <= dg::kBatchSmallMaxOrder && waves <= dg::kBatchSmallWaves;
   // the units to lanes, the largest first to the lane with the least work (nodes, twice where viscous)
   const int ng = (int)b->groups.size(), nu = ng + (int)b->solo.size();
   std::vector<double> load(nu, 0.0);

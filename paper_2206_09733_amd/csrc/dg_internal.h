@@ -152,7 +152,14 @@ struct BatchArgs {
   int cur[kMaxBatch];
   double dt[kMaxBatch];
   int n;
+  int small;  // the launch takes the shape of small meshes (host only; start counts its workgroups)
 };
+// Batches whose members' elements make at most kBatchSmallWaves waves, all members counted since the
+// launch groups run together, give order 1 the small shape too.  Packed / small time over FP64, extended
+// fluxes, FP32-bulk, plain and deformed boxes, Euler to interior penalty (mean, least): 256 waves 1.46, 1.34;
+// 768 1.29, 1.16; 1536 1.09, 1.02; 1728 1.07, 0.95; 2592 1.00, 0.93; 4096 0.78, 0.69.  Packed below the line, order
+// 1 took up to 1.14 times one element per wave with fewer face lanes (the first batched kernels); order 2 never did.
+constexpr int kBatchSmallMaxOrder = 1, kBatchSmallWaves = 1536;
 
 // Launchers (kernels.hip).  All enqueue on `st` and return the hipError_t of the launch.
 hipError_t launch_geometry(const View& v, hipStream_t st);

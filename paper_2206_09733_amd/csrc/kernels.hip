@@ -289,9 +289,9 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N)) grad_ker
 }
 
 // FORM: the members' boxes (see stage_batch_kernel); XV: the general form only
-template <int N, typename T, bool XV, BoxForm FORM>
-__global__ void __launch_bounds__(wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
-  constexpr int EW = wg_elems(N), NT = wg_lanes(N);
+template <int N, typename T, bool XV, BoxForm FORM, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N)) grad_batch_kernel(BatchArgs B) {
+  constexpr int EW = SMALL ? 1 : wg_elems(N), NT = SMALL ? small_lanes(N) : wg_lanes(N);
   __shared__ GradLds<N, T, XV, EW> lds;
   int m, w;
   batch_member(B, m, w);
@@ -618,18 +618,26 @@ hipError_t launch_stage(const View& v, int cur, double dt, double rkA, double rk
 
 hipError_t launch_diagnostics(const View& v, int cur, hipStream_t st) { DG_DISPATCH(diag_n, v, cur, st) }
 
+template <int N, typename T, bool SMALL>
+static hipError_t gradient_batch_nts(const BatchArgs& B, bool xv, BoxForm form, hipStream_t st) {
+  const dim3 grid(B.start[B.n]), block(SMALL ? small_lanes(N) : wg_lanes(N));
+  if (xv)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, true, BoxForm::deformed, SMALL>), grid, block, 0, st, B);
+  else if (form == BoxForm::plain)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::plain, SMALL>), grid, block, 0, st, B);
+  else if (form == BoxForm::deformed)
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::deformed, SMALL>), grid, block, 0, st, B);
+  else
+    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::both, SMALL>), grid, block, 0, st, B);
+  return hipGetLastError();
+}
+
 template <int N, typename T>
 static hipError_t gradient_batch_nt(const BatchArgs& B, bool xv, BoxForm form, hipStream_t st) {
-  const dim3 grid(B.start[B.n]), block(wg_lanes(N));
-  if (xv)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, true, BoxForm::deformed>), grid, block, 0, st, B);
-  else if (form == BoxForm::plain)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::plain>), grid, block, 0, st, B);
-  else if (form == BoxForm::deformed)
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::deformed>), grid, block, 0, st, B);
-  else
-    hipLaunchKernelGGL((grad_batch_kernel<N, T, false, BoxForm::both>), grid, block, 0, st, B);
-  return hipGetLastError();
+  if constexpr (N <= kBatchSmallMaxOrder) {
+    if (B.small) return gradient_batch_nts<N, T, true>(B, xv, form, st);
+  }
+  return gradient_batch_nts<N, T, false>(B, xv, form, st);
 }
 
 template <int N>

@@ -596,11 +596,12 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
 // FORM: the members' boxes.  Deformed members have kernels of their own since the registers of both forms
 // in one kernel spilled: 16 solves of 10^3, N = 4 Navier-Stokes FP64, deformed, 3791 us for four RK3 steps
 // (3166 so, 3534 with one general form before there was a plain one).
-template <int N, typename T, bool VISC, int FX, BoxForm FORM>
-__global__ void __launch_bounds__(wg_lanes(N))
-    __attribute__((amdgpu_waves_per_eu(batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, FORM))))
+// SMALL: the shape of small meshes (batch_small)
+template <int N, typename T, bool VISC, int FX, BoxForm FORM, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
+    __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, FORM))))
     stage_batch_kernel(BatchArgs B, double rkA, double rkB, int mode) {
-  constexpr int EW = wg_elems(N), NT = wg_lanes(N);
+  constexpr int EW = SMALL ? 1 : wg_elems(N), NT = SMALL ? small_lanes(N) : wg_lanes(N);
   __shared__ __align__(16) char lds[StageLds<N, T, VISC, FORM == BoxForm::plain, EW>::bytes];
   static_assert(StageLds<N, T, VISC, true, EW>::bytes <= StageLds<N, T, VISC, false, EW>::bytes, "one LDS buffer for both");
   int m, w;
@@ -651,14 +652,22 @@ inline hipError_t stage_ntx(const View& v, int cur, double dt, double a, double 
                   : stage_ntxc<N, T, FX, true>(v, cur, dt, a, b, mode, st);
 }
 
+template <int N, typename T, int FX, BoxForm FORM, bool SMALL>
+inline hipError_t stage_batch_nts(const BatchArgs& B, bool visc, double a, double b, int mode, hipStream_t st) {
+  const dim3 grid(B.start[B.n]), block(SMALL ? small_lanes(N) : wg_lanes(N));
+  if (visc)
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX, FORM, SMALL>), grid, block, 0, st, B, a, b, mode);
+  else
+    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX, FORM, SMALL>), grid, block, 0, st, B, a, b, mode);
+  return hipGetLastError();
+}
+
 template <int N, typename T, int FX, BoxForm FORM>
 inline hipError_t stage_batch_ntf(const BatchArgs& B, bool visc, double a, double b, int mode, hipStream_t st) {
-  const dim3 grid(B.start[B.n]), block(wg_lanes(N));
-  if (visc)
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, true, FX, FORM>), grid, block, 0, st, B, a, b, mode);
-  else
-    hipLaunchKernelGGL((stage_batch_kernel<N, T, false, FX, FORM>), grid, block, 0, st, B, a, b, mode);
-  return hipGetLastError();
+  if constexpr (N <= kBatchSmallMaxOrder) {
+    if (B.small) return stage_batch_nts<N, T, FX, FORM, true>(B, visc, a, b, mode, st);
+  }
+  return stage_batch_nts<N, T, FX, FORM, false>(B, visc, a, b, mode, st);
 }
 
 template <int N, typename T, int FX>

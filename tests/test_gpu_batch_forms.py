@@ -1,7 +1,8 @@
 """Every form of the batched stage and gradient kernels against the same solver stepped alone: bitwise
 the same states, whatever launch shape either of them takes (a small mesh alone runs one element per
-workgroup; in a batch orders 1 and 2 are packed, with a remainder here: 15 elements in workgroups of
-8 or 2).  The solvers alone are checked against the oracle elsewhere."""
+workgroup, and so does order 1 in a small batch; otherwise orders 1 and 2 are packed, with a remainder
+here: 15 elements in workgroups of 2, 2028 in workgroups of 8).  The solvers alone are checked against
+the oracle elsewhere."""
 import numpy as np
 import pytest
 
@@ -78,12 +79,15 @@ def test_fp32_bulk_batch_forms_equal_alone(dg, N, vol, surf):
 def test_plain_and_deformed_members_equal_alone(dg, N, precision):
     for visc in VISCOUS:
         compare(dg, [((3, 1, 5), False), ((2, 3, 3), True), ((1, 1, 1), False)], N=N, precision=precision, **visc)
+    if N == 1:  # packed: 8 elements per workgroup, a remainder in each member
+        for visc in VISCOUS:
+            compare(dg, [((9, 10, 9), False), ((7, 11, 13), True)], N=N, precision=precision, **visc)
 
 
-@pytest.mark.parametrize("N,cells", [(1, (13, 12, 13)), (2, (13, 12, 13)), (3, (9, 10, 11)), (4, (9, 9, 9))])
+@pytest.mark.parametrize("N,cells", [(1, (13, 12, 13)), (1, (17, 15, 13)), (2, (13, 12, 13)), (3, (9, 10, 11)), (4, (9, 9, 9))])
 @pytest.mark.parametrize("vol,surf", FLUXES)
 def test_batch_forms_equal_alone_above_the_small_shape(dg, N, cells, vol, surf):
-    """Meshes that alone take the usual shape too."""
-    for visc in (dict(), dict(Re=50.0)):
+    """Meshes that take the usual shape alone and in the batch (order 1: 8 elements per workgroup)."""
+    for visc in VISCOUS:
         for deform in (False, True):
             compare(dg, [(cells, deform)], steps=1, N=N, vol=vol, surf=surf, **visc)
