@@ -274,8 +274,8 @@ enum { DG_RK3_WILLIAMSON = 0, DG_RK4_CARPENTER_KENNEDY = 1 };
  * use one scheme).  Errors: DG_EINVAL for an unknown scheme. */
 int dg_solver_set_scheme(dg_solver* s, int scheme);
 /* Graph replay of RK steps (on by default).  When dg_rk_step runs several steps, or the same
- * dt as its previous call, the launches of 8 steps while at least 8 remain, then of 4, 2 and
- * 1 steps, are captured once per starting state buffer into HIP graphs (on a stream the library owns;
+ * dt as its previous call, the launches of 8 steps while at least 8 remain, then of single steps or,
+ * where the dt recurs, of 4, 2 and 1 steps, are captured once per starting state buffer into HIP graphs (on a stream the library owns;
  * no memory operations are recorded) and replayed on the solver's stream; the results equal
  * those of eager launches bit for bit.  Graphs are dropped when the state or its FP32
  * reference changes, after dg_autotune and when disabled; steps inside a profile region run
@@ -352,7 +352,8 @@ int dg_batch_create(dg_solver* const* solvers, int n, void* hip_stream, dg_batch
 /* Advance every member nsteps steps of the members' scheme, member i with step dts[i] (n
  * doubles).  Only enqueues work on the batch's stream and on streams of its own that are forked from
  * and joined to it by events: the launch groups are independent and run in up to four lanes.  Like
- * dg_rk_step, the launches of 8, 4, 2 and 1 steps are captured into HIP graphs and replayed when
+ * dg_rk_step, the launches of 8 and 1 steps, for recurring dts of 8, 4, 2 and 1, are captured into HIP
+ * graphs and replayed when
  * several steps are taken or the same dts recur (a few graphs are kept, keyed by dts, the step
  * count and the members' buffer parities; all are dropped, after waiting for the batch's stream, when
  * the FP32 reference state or the tile mask of a member launched on its own has changed). */

@@ -518,13 +518,15 @@ int capture_steps(dg_solver* s, double dt, int lg) {
   return rc;
 }
 
-// The graphs of a call of nsteps steps: eight steps each while that many remain, then the rest in
-// powers of two (few graph launches, and few different graphs whatever numbers of steps recur).
-std::vector<int> graph_chunks(int nsteps) {
-  std::vector<int> c(nsteps / 8, 8);
-  for (int k = 4; k >= 1; k /= 2)
-    if (nsteps % 8 & k) c.push_back(k);
-  return c;
+// The steps of the next graph of a call with `left` steps to go: eight while that many remain, then, for a
+// step size that recurs, the rest in powers of two (few graph launches, and few different graphs
+// whatever numbers of steps recur).  A new step size takes the rest in single steps: a graph of four
+// steps is not worth its capture for one launch (first call of a new solver, four steps: 11 x 10 x 19,
+// N = 1 417 -> 297 us, 5 x 8 x 10, N = 3 390 -> 270 us; a new step size each call, 4^3, N = 3: five
+// steps 292 -> 256, seven 418 -> 331).
+int graph_chunk(int left, bool recurs) {
+  if (left >= 8) return 8;
+  return !recurs ? 1 : (left >= 4 ? 4 : (left >= 2 ? 2 : 1));
 }
 
 // the launches of one adaptive step: step size, then the stages (s->v.dtp is set by the caller)
@@ -1027,13 +1029,15 @@ int dg_rk_step(dg_solver* s, double dt, int nsteps) try {
   if (!std::isfinite(dt) || !(dt > 0)) return fail(DG_EINVAL, "dt must be positive and finite");
   // replay a captured step when the same dt recurs (several steps in this call, or the same dt
   // as the previous call); a step size seen once runs eagerly
-  const bool replay = s->use_graphs && !s->profiling && nsteps > 0 && (nsteps > 1 || dt == s->last_dt);
+  const bool recurs = dt == s->last_dt;
+  const bool replay = s->use_graphs && !s->profiling && nsteps > 0 && (nsteps > 1 || recurs);
   s->last_dt = dt;
   if (!replay) {
     for (int it = 0; it < nsteps; it++) DG_HIP(run_step(s, dt), "RK stage kernels");
     return DG_OK;
   }
-  for (int steps : graph_chunks(nsteps)) {
+  for (int left = nsteps, steps = 0; left > 0; left -= steps) {
+    steps = graph_chunk(left, recurs);
     const int lg = steps == 8 ? 3 : (steps == 4 ? 2 : steps - 1);
     const int par = s->cur;
     if (!s->graph[lg][par] || s->graph_dt[lg][par] != dt) {
@@ -1622,7 +1626,14 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
     return DG_OK;
   }
   const int stages = kRk[b->scheme].stages;
-  const std::vector<int> chunks = graph_chunks(nsteps);
+  // the call's graphs: that of eight steps `eights` times (an even number of stages: it starts from the
+  // same buffers each time), then one of each further chunk
+  const int eights = nsteps / 8;
+  bool recurs = same;  // also when a set of step sizes alternates with others
+  for (const auto& g : b->graphs) recurs = recurs || std::equal(dts, dts + n, g.dts.begin());
+  std::vector<int> chunks;
+  if (eights > 0) chunks.push_back(8);
+  for (int left = nsteps % 8; left > 0; left -= chunks.back()) chunks.push_back(graph_chunk(left, recurs));
   std::vector<const dg_batch::Graph*> seq(chunks.size());
   auto find = [&](int steps) -> const dg_batch::Graph* {
     for (const auto& g : b->graphs) {
@@ -1633,7 +1644,7 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
     return nullptr;
   };
   // (a capture may drop an old graph that the sequence also needs, hence a second look: the sequence
-  // has at most five different graphs, and eight are kept)
+  // has at most four different graphs, and kBatchGraphs are kept)
   for (bool complete = false; !complete;) {
     complete = true;
     int flipped = 0, rc = DG_OK;
@@ -1652,8 +1663,11 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
       for (dg_solver* s : b->m) s->cur ^= 1;
     if (rc) return rc;
   }
-  DG_HIP(batch_fork(b, nsteps, (int)seq.size(),
-                    [&](int l, int c, hipStream_t st) { return hipGraphLaunch(seq[c]->exec[l], st); }),
+  const int skip = eights > 0 ? eights - 1 : 0;  // launch c replays chunk 0 up to c = skip
+  DG_HIP(batch_fork(b, nsteps, skip + (int)seq.size(),
+                    [&](int l, int c, hipStream_t st) {
+                      return hipGraphLaunch(seq[c < skip ? 0 : c - skip]->exec[l], st);
+                    }),
          "batch RK-step graph launch");
   return DG_OK;
 } catch (...) {
