@@ -1366,7 +1366,7 @@ struct dg_batch {
 
 namespace {
 
-constexpr size_t kBatchGraphs = 8;  // one- and multi-step graphs of both parities, twice
+constexpr size_t kBatchGraphs = 16;  // 8, 4, 2 and 1 steps from both parities, for two sets of step sizes
 
 void batch_drop_graphs(dg_batch* b) {
   if (b->graphs.empty()) return;
