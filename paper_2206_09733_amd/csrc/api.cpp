@@ -1403,8 +1403,8 @@ hipError_t batch_group_stage(dg_batch* b, const dg_batch::Group& g, const double
                                 dg::kModeRK, st);
 }
 
-// the same of a member with launches of its own
-hipError_t batch_solo_stage(dg_batch* b, int i, const double* dts, int k, int par, hipStream_t st) {
+// the same of a member with launches of its own (fork: a mixed-order member may run its buckets side by side)
+hipError_t batch_solo_stage(dg_batch* b, int i, const double* dts, int k, int par, hipStream_t st, bool fork) {
   dg_solver* s = b->m[i];
   const int cur = s->cur ^ par;
   const double A = kRk[b->scheme].A[k], Bk = kRk[b->scheme].B[k];
@@ -1412,7 +1412,7 @@ hipError_t batch_solo_stage(dg_batch* b, int i, const double* dts, int k, int pa
   if (e != hipSuccess) return e;
   if (s->v.mixed)
     return dg::launch_stage_mixed(s->v, cur, dts[i], A, Bk, dg::kModeRK, s->mix_tiles, st,
-                                  s->mix_concurrent ? &s->mix : nullptr);
+                                  fork && s->mix_concurrent ? &s->mix : nullptr);
   if (s->v.gauss) return dg::launch_stage_gauss(s->v, cur, dts[i], A, Bk, dg::kModeRK, st);
   // spectral vanishing viscosity: the solver's own stage sequence
   if (svv_folded(s)) {
@@ -1433,30 +1433,32 @@ hipError_t batch_solo_stage(dg_batch* b, int i, const double* dts, int k, int pa
   return e;
 }
 
-// RK steps first .. first + steps - 1 of a call, of lane l's units, on stream st
-hipError_t batch_lane(dg_batch* b, int l, const double* dts, int first, int steps, hipStream_t st) {
+// RK steps first .. first + steps - 1 of a call, of lane l's units, on stream st.  Under capture (the
+// batch's own or a caller's) nothing forks: the launches recorded are one chain.
+hipError_t batch_lane(dg_batch* b, int l, const double* dts, int first, int steps, hipStream_t st, bool capturing) {
   const int stages = kRk[b->scheme].stages, ng = (int)b->groups.size();
   for (int k = first * stages; k < (first + steps) * stages; k++)
     for (int u : b->lanes[l]) {
       const int s = k % stages, par = k & 1;
       const hipError_t e = u < ng ? batch_group_stage(b, b->groups[u], dts, s, par, st)
-                                  : batch_solo_stage(b, b->solo[u - ng], dts, s, par, st);
+                                  : batch_solo_stage(b, b->solo[u - ng], dts, s, par, st, !capturing);
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
 }
 
-// run(l, c, stream) for every lane and chunk c < chunks, the lanes in turn within a chunk; lane 0 on
+// run(l, c, stream, capturing) for every lane and chunk c < chunks, the lanes in turn within a chunk; lane 0 on
 // the batch's stream and the others on side streams forked from it and joined to it by events; all on
 // the batch's stream where the caller is capturing it.  Afterwards every member's state has moved to
 // the buffer that `steps` steps lead to.
-hipError_t batch_fork(dg_batch* b, int steps, int chunks, const std::function<hipError_t(int, int, hipStream_t)>& run) {
+hipError_t batch_fork(dg_batch* b, int steps, int chunks,
+                      const std::function<hipError_t(int, int, hipStream_t, bool)>& run) {
   const int nl = (int)b->lanes.size();
   hipError_t err = hipSuccess;
   int forked = 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (nl > 1 && b->stream) err = hipStreamIsCapturing(b->stream, &cap);
-  const bool serial = nl == 1 || cap != hipStreamCaptureStatusNone;
+  if (b->stream) err = hipStreamIsCapturing(b->stream, &cap);
+  const bool capturing = cap != hipStreamCaptureStatusNone, serial = nl == 1 || capturing;
   if (!serial && chunks > 0 && err == hipSuccess) {
     err = hipEventRecord(b->fork, b->stream);
     for (int l = 1; l < nl && err == hipSuccess; l++) {
@@ -1465,7 +1467,8 @@ hipError_t batch_fork(dg_batch* b, int steps, int chunks, const std::function<hi
     }
   }
   for (int c = 0; c < chunks && err == hipSuccess; c++)
-    for (int l = nl - 1; l >= 0 && err == hipSuccess; l--) err = run(l, c, serial || !l ? b->stream : b->side[l - 1]);
+    for (int l = nl - 1; l >= 0 && err == hipSuccess; l--)
+      err = run(l, c, serial || !l ? b->stream : b->side[l - 1], capturing);
   for (int l = 1; l <= forked; l++) {  // also after a failed launch: no work of a lane is left unordered
     hipError_t e = hipEventRecord(b->join[l - 1], b->side[l - 1]);
     if (e == hipSuccess) e = hipStreamWaitEvent(b->stream, b->join[l - 1], 0);
@@ -1491,7 +1494,7 @@ int batch_capture(dg_batch* b, const double* dts, int steps) {
     hipGraph_t g = nullptr;
     hipError_t err = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
     if (err == hipSuccess) {
-      err = batch_lane(b, (int)l, dts, 0, steps, b->cap_stream);
+      err = batch_lane(b, (int)l, dts, 0, steps, b->cap_stream, true);
       const hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
       if (err == hipSuccess) err = e2;
     }
@@ -1621,7 +1624,7 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
   b->last_dts.assign(dts, dts + n);
   if (!replay) {
     DG_HIP(batch_fork(b, nsteps, nsteps,
-                      [&](int l, int c, hipStream_t st) { return batch_lane(b, l, dts, c, 1, st); }),
+                      [&](int l, int c, hipStream_t st, bool cap) { return batch_lane(b, l, dts, c, 1, st, cap); }),
            "batch RK stage kernels");
     return DG_OK;
   }
@@ -1665,7 +1668,7 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
   }
   const int skip = eights > 0 ? eights - 1 : 0;  // launch c replays chunk 0 up to c = skip
   DG_HIP(batch_fork(b, nsteps, skip + (int)seq.size(),
-                    [&](int l, int c, hipStream_t st) {
+                    [&](int l, int c, hipStream_t st, bool) {
                       return hipGraphLaunch(seq[c < skip ? 0 : c - skip]->exec[l], st);
                     }),
          "batch RK-step graph launch");
