@@ -36,7 +36,6 @@ inline int tab_size(int n) { return 2 * n + 2 * n * n; }
 // Lobatto basis function l at Gauss point q, g = tab_size(n); then, formed from the tables above,
 // the weak derivative matrix Dw_im = -D_mi w_m / w_i [g + n + 2n^2, + n^2) and the lift factors
 // l_i(-1)/w_i, l_i(+1)/w_i (2 n)
-inline int tab_gauss_geo_size(int n) { return n + 2 * n * n; }
 __host__ __device__ constexpr int tab_gauss_Dw(int n) { return 2 * n + 2 * n * n + n + 2 * n * n; }
 __host__ __device__ constexpr int tab_gauss_lift(int n) { return tab_gauss_Dw(n) + n * n; }
 __host__ __device__ constexpr int tab_gauss_size(int n) { return tab_gauss_lift(n) + 2 * n; }
@@ -122,7 +121,8 @@ __host__ __device__ constexpr int wg_lanes(int N) {
 __host__ __device__ constexpr int wg_count(int N, int E) { return (E + wg_elems(N) - 1) / wg_elems(N); }
 // The shape of meshes too small to fill the chip, whose launches are one chain of latencies: one
 // element per workgroup, and lanes for all of its face points at once (orders 3 and 4: one wave more).
-// The results do not depend on the shape: every node and face point is evaluated by itself.
+// The results do not depend on the shape: every node and face point is evaluated by itself, and its
+// multiply-adds are fused within an expression only (the build's -ffp-contract=on).
 __host__ __device__ constexpr int small_lanes(int N) {
   const int nodes = (N + 1) * (N + 1) * (N + 1), faces = 6 * (N + 1) * (N + 1);
   return ((nodes > faces ? nodes : faces) + 63) / 64 * 64;

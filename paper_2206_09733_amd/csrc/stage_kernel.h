@@ -31,9 +31,9 @@ namespace dg {
 //
 // Bound by VALU issue and by the latency of an element's loads, not by HBM (the NS stage at 32^3,
 // N = 4 moves 1.39 GB in 355-365 us).  Measured, RK3 step before -> now, microseconds: deformed
-// NS 32^3 N = 4 FP64 1703 -> 1536, FP32-bulk 1445 -> 1312; deformed Euler RK4 20^3 N = 5 per
-// step 806 -> 657; deformed NS residual 13x11x9 N = 7 191 -> 120; plain Euler 41x36x28 N = 2
-// 322 -> 164; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 821 -> 547.
+// NS 32^3 N = 4 FP64 1727 -> 1541, FP32-bulk 1460 -> 1312; deformed Euler RK4 20^3 N = 5 per
+// step 809 -> 654; deformed NS residual 13x11x9 N = 7 191 -> 116; plain Euler 41x36x28 N = 2
+// 322 -> 162; plain NS 18x23x20 N = 5 (Pirozzoli + ES) 823 -> 547.
 //
 // The plain-box FP32-bulk Euler kernels of orders 5 and 6 read the RK update's input state after the
 // last direction (see stage_body): 100 -> 90 VGPRs, five waves per SIMD.
@@ -44,8 +44,9 @@ __host__ __device__ constexpr bool late_state(int N, bool fp32, bool visc, bool 
 // for FP32-bulk (at order 3 with the filtered flux only) and for the plain-box Navier-Stokes kernels of orders 3
 // and 4 without the filtered flux (24^3, N = 4: 511 -> 493 us per RK3 step; the extended surface
 // fluxes would spill).  Spills cost more than the fourth wave gives: deformed Euler at four waves with
-// 9 (N = 4) and 33 spilled (N = 5) took 364 -> 401 and 395 -> 657 us.  Spilled as it is: 4 VGPRs by the
-// deformed FP32-bulk kernel of order 5 with the filtered flux, 6 by its FP64 twin.
+// 9 (N = 4) and 33 spilled (N = 5) took 364 -> 401 and 395 -> 657 us.  Order 1, whose wave evaluates three
+// rounds of face points: two waves in FP64 and three in FP32-bulk, one more would spill 10-41 and 25-43.
+// Spilled as it is: one VGPR, by the deformed FP32-bulk kernel of order 5 with the filtered flux.
 __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc, int fx, bool sva, bool cart) {
   if (N == 1) return fp32 ? 3 : 2;
   if (late_state(N, fp32, visc, cart)) return 5;
@@ -55,7 +56,7 @@ __host__ __device__ constexpr int stage_waves_per_eu(int N, bool fp32, bool visc
 }
 // The batched kernels hold a few registers more (the member's View and start).  FP64: three waves, four
 // would spill 6-8 of the plain-box Navier-Stokes kernels.  Those that hold both metric forms: three, two at order 1
-// (at one more, 6 to 12 VGPRs of FP32-bulk kernels spilled).
+// (at one more, 6 to 12 VGPRs of FP32-bulk kernels spilled; as it is 6 of the FP64 Navier-Stokes kernel of order 4).
 __host__ __device__ constexpr int batch_waves_per_eu(int N, bool fp32, bool visc, int fx, BoxForm form) {
   const int w = stage_waves_per_eu(N, fp32, visc, fx, false, form == BoxForm::plain);
   if (form == BoxForm::both) return N == 1 ? 2 : (w > 3 ? 3 : w);
@@ -596,7 +597,7 @@ __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
 // FORM: the members' boxes.  Deformed members have kernels of their own since the registers of both forms
 // in one kernel spilled: 16 solves of 10^3, N = 4 Navier-Stokes FP64, deformed, 3791 us for four RK3 steps
 // (3166 so, 3534 with one general form before there was a plain one).
-// SMALL: the shape of small meshes (batch_small)
+// SMALL: the shape of small meshes (kBatchSmallWaves)
 template <int N, typename T, bool VISC, int FX, BoxForm FORM, bool SMALL>
 __global__ void __launch_bounds__(SMALL ? small_lanes(N) : wg_lanes(N))
     __attribute__((amdgpu_waves_per_eu(SMALL ? 2 : batch_waves_per_eu(N, sizeof(T) == 4, VISC, FX, FORM))))
