@@ -1613,12 +1613,6 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
   const size_t n = b->m.size();
   for (size_t i = 0; i < n; i++)
     if (!std::isfinite(dts[i]) || !(dts[i] > 0)) return fail(DG_EINVAL, "every dt must be positive and finite");
-  std::vector<unsigned long long> captured;
-  for (int i : b->solo) captured.push_back(b->m[i]->captured);
-  if (captured != b->captured) {
-    batch_drop_graphs(b);
-    b->captured = std::move(captured);
-  }
   const bool same = b->last_dts.size() == n && std::equal(dts, dts + n, b->last_dts.begin());
   const bool replay = b->use_graphs && nsteps > 0 && (nsteps > 1 || same);
   b->last_dts.assign(dts, dts + n);
@@ -1627,6 +1621,12 @@ int dg_batch_rk_step(dg_batch* b, const double* dts, int nsteps) try {
                       [&](int l, int c, hipStream_t st, bool cap) { return batch_lane(b, l, dts, c, 1, st, cap); }),
            "batch RK stage kernels");
     return DG_OK;
+  }
+  std::vector<unsigned long long> captured;
+  for (int i : b->solo) captured.push_back(b->m[i]->captured);
+  if (captured != b->captured) {
+    batch_drop_graphs(b);
+    b->captured = std::move(captured);
   }
   const int stages = kRk[b->scheme].stages;
   // the call's graphs: that of eight steps `eights` times (an even number of stages: it starts from the
