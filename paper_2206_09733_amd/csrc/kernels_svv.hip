@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_p
 }
 
 // Navier-Stokes pass A (BR1, in the solver's precision T) and the SVV flux (FP64) in one pass
-// (three waves at order 1, where four would spill 18 registers: 46^3 deformed, 2069 -> 1968 us per four steps)
+// (three waves at order 1, where four would spill 18 registers: 37 x 38 x 36 deformed, 2069 -> 1968 us for four steps)
 template <int N, typename T, bool CART>
 __global__ void __launch_bounds__(nthreads_for(N)) __attribute__((amdgpu_waves_per_eu(N == 1 ? 3 : (N <= 6 ? 4 : 3))))
     grad_svv_kernel(View v, int cur, SvvArgs a) {
